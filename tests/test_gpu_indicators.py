@@ -138,3 +138,36 @@ def test_expected_utility_closed_forms(P, O):
     # no row counts: -inf
     assert P.expected_utility(F, np.eye(3), np.zeros(500, np.uint8)) == -np.inf
     assert P.expected_utility(np.zeros((0, 3), np.float32), np.eye(3)) == -np.inf
+
+
+@pytest.mark.parametrize("n", [15, 16, 17, 63, 255, 256, 257, 272, 2049])
+@pytest.mark.parametrize("kind", ["front", "ties", "outside"])
+def test_hypervolume_at_workgroup_edges(P, O, n, kind):
+    """Row counts at the edges of the ordering's 16-row workgroups and 256-point
+    steps and of the terms' 64-point steps, on a front (long left minima, early
+    ends), with equal coordinates and with rows that do not count."""
+    rng = np.random.default_rng(n + len(kind))
+    if kind == "front":
+        w = rng.exponential(size=(n, 3))
+        F = (0.9 * (1 + 0.05 * rng.random((n, 1))) * w / np.linalg.norm(w, axis=1)[:, None]).astype(np.float32)
+        valid = np.ones(n, np.uint8)
+    else:
+        F, valid = random_rows(rng, n, 3, kind)
+    got = P.hypervolume(F, valid)
+    want = O.hypervolume(F.astype(np.float64), valid)
+    assert abs(got - want) <= hv_tol(n) * abs(want) + 1e-300, (got, want)
+
+
+@pytest.mark.parametrize("m,n,nw", [(2, 1023, 7), (3, 1024, 2047), (3, 1025, 2048), (2, 2100, 4097),
+                                    (4, 300, 8191), (6, 37, 8193), (7, 1, 9), (8, 5000, 33)])
+def test_expected_utility_over_weight_tiles(P, O, m, n, nw):
+    """Weight counts at the edges of the weights-per-workgroup choices, rows at
+    the edges of the 1,024-row tiles, some rows not counting."""
+    rng = np.random.default_rng(nw)
+    F, valid = random_rows(rng, n, m, "outside")
+    if n == 1:
+        F, valid = rng.random((1, m)).astype(np.float32), np.ones(1, np.uint8)
+    W = rng.random((nw, m))
+    got = P.expected_utility(F, W, valid)
+    want = O.expected_utility(F.astype(np.float64), W, valid)
+    assert abs(got - want) <= 1e-13 * abs(want), (got, want)
