@@ -29,8 +29,9 @@ namespace rvea {
 // rows does not matter: it only decides where each child's genes are stored.
 
 // Prepare generation gen = t_done + 1 from population p = t_done (one
-// kernel): reset the selection's per-vector minima and the survivors'
-// extremes, flag the parent slots that take part (valid, finite F) with
+// kernel; runs whose k_newpop does this itself take it only after
+// initialization and after the state is set from the host): reset the
+// selection's per-vector minima, flag the parent slots that take part (valid, finite F) with
 // their share of the ideal point, list the valid slots in ascending order
 // (block offsets from the per-block counts left by the previous generation's
 // k_newpop, or by k_stamp), and hand out free gene rows for the offspring
@@ -60,11 +61,7 @@ __device__ __forceinline__ void prep_body(const RunView &R, int64_t bx)
         for (int k = 0; k < kMaxM; ++k)
             if (k < R.m) fj[k] = Fm[j * R.m + k];
     }
-    if (j < R.K) R.key[j] = ~0ull;
-    if (j < R.m) {
-        R.rbits[j] = 0xffffffffu;  // survivors' minimum
-        R.rbits[R.m + j] = 0u;     // survivors' maximum
-    }
+    if (j < R.K) key_of(R, gen)[j] = ~0ull;
     // Eq. 4 penalty factor m (t/t_max)^alpha of this generation, computed by
     // the last block (free rows only, the least work), off the others' path
     if (bx == (R.K + R.N + 255) / 256 - 1 && threadIdx.x == 0)
@@ -114,7 +111,7 @@ __device__ __forceinline__ void prep_body(const RunView &R, int64_t bx)
     if (v)  // the slot and its row: a parent's genes are one lookup away
         reinterpret_cast<int2 *>(R.vs)[offset + pos] = make_int2((int32_t)j, rowj);
     const int64_t nblk = (R.K + 255) / 256;
-    if (bx == nblk - 1 && threadIdx.x == 0) *R.nvalid = offset + tot;
+    if (bx == nblk - 1 && threadIdx.x == 0) *nvalid_of(R, p) = offset + tot;
     if (threadIdx.x < R.m) {
         const int k = threadIdx.x;
         const uint32_t e = min(min(zw[0][k], zw[1][k]), min(zw[2][k], zw[3][k]));
@@ -122,9 +119,9 @@ __device__ __forceinline__ void prep_body(const RunView &R, int64_t bx)
     }
     // free rows of this block: one atomic reserves their places
     __shared__ int fbase;
-    if (threadIdx.x == 0) fbase = ftot ? atomicAdd(R.freecnt, ftot) : 0;
+    if (threadIdx.x == 0) fbase = ftot ? atomicAdd(R.freecnt + (R.turn ? p & 1 : 0), ftot) : 0;
     __syncthreads();
-    if (fr && fbase + fpos < R.N) R.off_row[fbase + fpos] = (int32_t)j;
+    if (fr && (R.turn || fbase + fpos < R.N)) off_row_of(R, gen)[fbase + fpos] = (int32_t)j;
 }
 
 __global__ __launch_bounds__(256) void k_prep(RunView R) { prep_body(R, blockIdx.x); }
@@ -147,8 +144,10 @@ __device__ __forceinline__ void stamp_body(const RunView &R, int64_t bx)
     __syncthreads();
     if (threadIdx.x == 0) {
         R.bcount[bx] = wc[0] + wc[1] + wc[2] + wc[3];
-        if (bx == 0) *R.freecnt = 0;
+        if (bx == 0) R.freecnt[0] = R.freecnt[1] = 0;
     }
+    if (bx == 0 && threadIdx.x < 4 * R.m)  // both parities' extremes: minima, then maxima
+        R.rbits[threadIdx.x] = threadIdx.x / R.m % 2 ? 0u : 0xffffffffu;
 }
 
 __global__ __launch_bounds__(256) void k_stamp(RunView R) { stamp_body(R, blockIdx.x); }
@@ -427,7 +426,7 @@ __device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx)
     float *Fm = fm_of(R, pop);
     const int64_t o1 = p, o2 = p + P;
     const bool has2 = o2 < R.N;
-    const uint32_t nv = (uint32_t)*R.nvalid;
+    const uint32_t nv = (uint32_t)*nvalid_of(R, pop);
     if (nv == 0) {  // no parent left (every row was non-finite): offspring are empty
         if (active && lane == 0 && sp == 0) {
             for (int k = 0; k < R.m; ++k) {
@@ -452,8 +451,9 @@ __device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx)
     // the children's rows: they do not depend on the mating, so their loads
     // are issued before the sites are drawn (clamped indices for inactive
     // segments and a missing second child, values unused)
-    const int32_t orow1 = R.off_row[active ? o1 : 0];
-    const int32_t orow2 = R.off_row[active && has2 ? o2 : 0];
+    const int32_t *orow = off_row_of(R, t);
+    const int32_t orow1 = orow[active ? o1 : 0];
+    const int32_t orow2 = orow[active && has2 ? o2 : 0];
 
     // mutation sites of both children
     int n1 = 0, n2 = 0;
@@ -693,7 +693,7 @@ __device__ __forceinline__ void offspring_finish_body(const RunView &R, int64_t 
     const int64_t o = bx * 256 + threadIdx.x;
     const int64_t P = (R.N + 1) / 2;
     const int64_t pop = *R.t_done;
-    if (*R.nvalid == 0) return;  // no parent: the offspring kernel left empty children
+    if (*nvalid_of(R, pop) == 0) return;  // no parent: the offspring kernel left empty children
     float *Fm = fm_of(R, pop);
     const bool has = o < R.N;
     float f[kMaxM] = {};
@@ -703,7 +703,7 @@ __device__ __forceinline__ void offspring_finish_body(const RunView &R, int64_t 
         const int ns = R.osplit;
         double g = 0.0;
         for (int k = 0; k < ns; ++k) g += R.gpart[(p * ns + k) * 2 + c];
-        const float *row = R.X + (int64_t)R.off_row[o] * R.ld;
+        const float *row = R.X + (int64_t)off_row_of(R, pop + 1)[o] * R.ld;
         float pos[kMaxM];
 #pragma unroll
         for (int k = 0; k < kMaxM - 1; ++k) pos[k] = k < R.m - 1 ? row[k] : 0.f;
@@ -854,6 +854,7 @@ hipError_t launch_init(const RunView &R, hipStream_t s)
     if (e == hipSuccess && R.problem == kPolicy)  // objectives of the initial slots by rollouts
         e = launch_rollout(R, s, false);
     if (e == hipSuccess) e = launch_stamp(R, s);
+    if (e == hipSuccess && R.turn) e = launch_prepare(R, s);
     return e;
 }
 

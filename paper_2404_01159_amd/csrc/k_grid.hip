@@ -719,16 +719,10 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
                 R.lidx[o] = st.j[q];
                 ++o;
             }
-            if (lane == 0) {
-                R.lstart[c] = (int32_t)base;
-                R.lcnt[c] = n;
-            }
+            if (lane == 0) R.lcnt[c] = n;
         }
     }
-    if (full && lane == 0) {
-        R.lstart[c] = -1;
-        R.lcnt[c] = -1;
-    }
+    if (full && lane == 0) R.lcnt[c] = -1;
 }
 
 // ----------------------------------------------------------- association
@@ -759,24 +753,34 @@ __device__ __forceinline__ void assoc_grid_body(const RunView &R, int64_t bx)
     n2 = fma(f[2], f[2], n2);
     const double nrm = sqrt(n2);
     const bool live = act && nrm > 0.0;
-    int32_t st = -1, n = 0;
+    // the cell's list: its length and, beside it (the cell's slot is at a
+    // fixed place, whatever it holds), this lane's first two records
+    int32_t n = 0;
+    int64_t st = 0;
+    double4 v0 = make_double4(0.0, 0.0, 0.0, 1.0), v1 = v0;
+    int32_t j0 = 0, j1 = 0;
+    const double4 *rec = reinterpret_cast<const double4 *>(R.lrec);
     if (live) {
         const int c = cell_of(f[0], f[1], f[2], R.gr, R.gG);
         if (c >= 0) {
-            st = R.lstart[c];
+            st = (int64_t)c * kSlot;
             n = R.lcnt[c];
+            v0 = rec[st + sub];
+            j0 = R.lidx[st + sub];
+            v1 = rec[st + sub + kGridRowLanes];
+            j1 = R.lidx[st + sub + kGridRowLanes];
         }
     }
-    const bool full = live && (st < 0 || n <= 0);
+    const bool full = live && n <= 0;
     // the best cosine, its vector and that vector's gamma (loaded with the
     // candidate, so the APD needs no further round trip)
     double best = -INFINITY, bg = 0.0;
     int64_t bj = R.K;
     if (live && !full) {
-        const double4 *rec = reinterpret_cast<const double4 *>(R.lrec) + st;
         for (int e = sub; e < n; e += kGridRowLanes) {
-            const double4 v = rec[e];
-            const int64_t j = R.lidx[st + e];
+            const bool third = e >= 2 * kGridRowLanes;
+            const double4 v = e == sub ? v0 : third ? rec[st + e] : v1;
+            const int64_t j = e == sub ? j0 : third ? R.lidx[st + e] : j1;
             const double gj = R.gamma[j];
             double s = f[0] * v.x;
             s = fma(f[1], v.y, s);
@@ -830,7 +834,7 @@ __device__ __forceinline__ void assoc_grid_body(const RunView &R, int64_t bx)
     if (!live) {  // the row is the ideal point: vector 0, APD 0
         R.assoc[i] = 0;
         R.apd[i] = 0.0;
-        atomicMin(&R.key[0], (unsigned long long)i);
+        atomicMin(&key_of(R, pop + 1)[0], (unsigned long long)i);
         return;
     }
     if (full) atomicAdd(&R.counters[1], 1ull);
@@ -842,7 +846,7 @@ __device__ __forceinline__ void assoc_grid_body(const RunView &R, int64_t bx)
     R.assoc[i] = (int32_t)bj;
     R.apd[i] = a;
     const unsigned long long ab = (unsigned long long)__double_as_longlong(a);
-    atomicMin(&R.key[bj], ((ab >> R.kb) << R.kb) | (unsigned long long)i);
+    atomicMin(&key_of(R, pop + 1)[bj], ((ab >> R.kb) << R.kb) | (unsigned long long)i);
 }
 
 // One lane per merged row (two objectives): f' and |f'| as the re-rank forms
@@ -869,7 +873,7 @@ __device__ __forceinline__ void assoc_line_body(const RunView &R, int64_t bx)
     if (!(nrm > 0.0)) {  // the row is the ideal point: vector 0, APD 0
         R.assoc[i] = 0;
         R.apd[i] = 0.0;
-        atomicMin(&R.key[0], (unsigned long long)i);
+        atomicMin(&key_of(R, pop + 1)[0], (unsigned long long)i);
         return;
     }
     const int G = R.gG;
@@ -937,7 +941,7 @@ __device__ __forceinline__ void assoc_line_body(const RunView &R, int64_t bx)
     R.assoc[i] = (int32_t)bj;
     R.apd[i] = a;
     const unsigned long long ab = (unsigned long long)__double_as_longlong(a);
-    atomicMin(&R.key[bj], ((ab >> R.kb) << R.kb) | (unsigned long long)i);
+    atomicMin(&key_of(R, pop + 1)[bj], ((ab >> R.kb) << R.kb) | (unsigned long long)i);
 }
 
 // Eq. 5's gamma of each vector on the line (one lane per vector): the walk

@@ -106,7 +106,8 @@ __device__ __forceinline__ void operator_body(const RunView &R, int64_t bx)
     float *Fm = fm_of(R, pop);
     const int64_t o1 = u, o2 = u + P;  // CSO: the loser's child and the winner's copy
     const bool has2 = OP == OP_CSO && o2 < R.N;
-    const uint32_t nv = (uint32_t)*R.nvalid;
+    const uint32_t nv = (uint32_t)*nvalid_of(R, pop);
+    const int32_t *orow = off_row_of(R, t);
     if (nv == 0) {  // no member left: the offspring are empty, as for the genetic operators
         if (active && lane == 0) {
             for (int k = 0; k < R.m; ++k) {
@@ -128,7 +129,7 @@ __device__ __forceinline__ void operator_body(const RunView &R, int64_t bx)
     int32_t pa = -1, pb = -1;  // reported pair (CSO: winner, loser)
 
     if (active) {
-        float *c1 = R.X + (int64_t)R.off_row[o1] * R.ld;
+        float *c1 = R.X + (int64_t)orow[o1] * R.ld;
         if constexpr (OP == OP_DE) {
             const DeDraws D = de_draws(R, (uint32_t)o1, t, nv);
             const float *xt = R.X + (int64_t)vs[D.tgt].y * R.ld;
@@ -162,7 +163,7 @@ __device__ __forceinline__ void operator_body(const RunView &R, int64_t bx)
             const int32_t ri = vs[below(ws.w[0], nv)].y, rl = vs[below(ws.w[1], nv)].y;
             const float *xi = R.X + (int64_t)ri * R.ld, *xl = R.X + (int64_t)rl * R.ld;
             const float *vi = R.Vel + (int64_t)ri * R.ld;
-            float *v1 = R.Vel + (int64_t)R.off_row[o1] * R.ld;
+            float *v1 = R.Vel + (int64_t)orow[o1] * R.ld;
             const double wi = R.op_a, cc = R.op_b;
             for (int q = lane; q < Q; q += S) {
                 const W4 w = draw(R, (uint32_t)q, (uint32_t)o1, t, TAG_OPGENE);
@@ -201,9 +202,9 @@ __device__ __forceinline__ void operator_body(const RunView &R, int64_t bx)
             pb = los.x;
             const float *xw = R.X + (int64_t)win.y * R.ld, *xl = R.X + (int64_t)los.y * R.ld;
             const float *vw = R.Vel + (int64_t)win.y * R.ld, *vl = R.Vel + (int64_t)los.y * R.ld;
-            float *v1 = R.Vel + (int64_t)R.off_row[o1] * R.ld;
-            float *c2 = has2 ? R.X + (int64_t)R.off_row[o2] * R.ld : nullptr;
-            float *v2 = has2 ? R.Vel + (int64_t)R.off_row[o2] * R.ld : nullptr;
+            float *v1 = R.Vel + (int64_t)orow[o1] * R.ld;
+            float *c2 = has2 ? R.X + (int64_t)orow[o2] * R.ld : nullptr;
+            float *v2 = has2 ? R.Vel + (int64_t)orow[o2] * R.ld : nullptr;
             for (int q = lane; q < Q; q += S) {
                 const float4 a = ld4(xw + 4 * q), b = ld4(xl + 4 * q), c = ld4(vl + 4 * q);
                 const float xwq[4] = {a.x, a.y, a.z, a.w}, xlq[4] = {b.x, b.y, b.z, b.w};

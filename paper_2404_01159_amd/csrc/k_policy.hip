@@ -99,12 +99,12 @@ struct RolloutLds {
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_rollout(RunView R, int64_t n, int offspring)
 {
     const int check_nv = offspring;
-    const int32_t *rows = offspring ? R.off_row : slot_row_of(R, 0);
+    const int32_t *rows = offspring ? off_row_of(R, *R.t_done + 1) : slot_row_of(R, 0);
     float *F = offspring ? fm_of(R, *R.t_done) + R.K * R.m : fm_of(R, 0);
     __shared__ RolloutLds sh;
     const int wv = threadIdx.x >> 6;
     const int64_t q = (int64_t)blockIdx.x * kRollWaves + wv;
-    const bool active = q < n && !(check_nv && *R.nvalid == 0);
+    const bool active = q < n && !(check_nv && *nvalid_of(R, *R.t_done) == 0);
     const int l = threadIdx.x & 63;
     const int c = l & 15;  // MFMA row of the A operand / column (rollout) of B and D
     const int g = l >> 4;  // lane group: k-slots 8g..8g+7 of A and B, rows 4g..4g+3 of D

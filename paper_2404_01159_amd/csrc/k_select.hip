@@ -639,7 +639,7 @@ __device__ __forceinline__ void rerank_body(const RunView &R, int64_t bx, int ga
     if (!GAMMA && st == 2) {
         R.assoc[row_i] = 0;
         R.apd[row_i] = 0.0;
-        atomicMin(&R.key[0], (unsigned long long)row_i);  // APD 0
+        atomicMin(&key_of(R, *R.t_done + 1)[0], (unsigned long long)row_i);  // APD 0
         return;
     }
     double best = s_rb[t];
@@ -661,7 +661,171 @@ __device__ __forceinline__ void rerank_body(const RunView &R, int64_t bx, int ga
     // >= 0) above the row index, its lowest kb bits dropped; the minimum
     // names the survivor directly, the lowest row among equal APDs
     const unsigned long long ab = (unsigned long long)__double_as_longlong(a);
-    atomicMin(&R.key[bj], ((ab >> R.kb) << R.kb) | (unsigned long long)row_i);
+    atomicMin(&key_of(R, *R.t_done + 1)[bj], ((ab >> R.kb) << R.kb) | (unsigned long long)row_i);
+}
+
+// What generation g leaves reset for the next ones: z* of g+2 and the
+// survivors' extremes of g+1 (one workgroup).
+__device__ __forceinline__ void next_resets(const RunView &R, int64_t g)
+{
+    if (threadIdx.x < R.m) zbuf(R, g + 2)[threadIdx.x] = 0xffffffffu;
+    if (threadIdx.x < 2 * R.m) rbits_of(R, g + 1)[threadIdx.x] = threadIdx.x < R.m ? 0xffffffffu : 0u;
+}
+
+// k_newpop and the next generation's k_prep in one pass (RunView::turn), one
+// kernel boundary (about 4.5 us) fewer per generation.  Nothing here waits for
+// another workgroup:
+//   - new slots (the first ceil(K/1024) workgroups): slot j <- its survivor as
+//     in newpop_body; its place in the ascending list of valid slots counts
+//     the earlier workgroups' survivors straight from their keys (final since
+//     the association), up to 15 eight-byte loads per thread at the largest K
+//     taken here;
+//   - free rows: the old slots' rows (same workgroups) and the rows that were
+//     handed out or spare in this generation (ceil((K+N)/1024) workgroups more)
+//     of individuals that no key names.  A merged row lives exactly if its
+//     vector's key holds its index, so no pass over stamped rows is needed.
+// The buffers that this kernel reads and the ones it writes alternate by
+// generation parity (keys, row lists, counts).  Bound by its chain of memory
+// round trips (counter; keys and rows; the survivors' values; one returned
+// atomic), so loads are issued unconditionally where an index is at hand, and
+// workgroups are as large as they can be: fewer earlier keys per thread, fewer
+// atomics on the one counter.
+constexpr int kTurnBlock = 1024, kTurnWaves = kTurnBlock / 64;
+__device__ __forceinline__ void turn_body(const RunView &R, int64_t bx)
+{
+    __shared__ uint32_t smin[kTurnWaves][kMaxM], smax[kTurnWaves][kMaxM];
+    __shared__ int wsum[3][kTurnWaves];
+    __shared__ int fbase;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int64_t nbk = (R.K + kTurnBlock - 1) / kTurnBlock;
+    const unsigned long long mask = (1ull << R.kb) - 1;
+    const bool slots = bx < nbk;  // uniform
+    const int64_t j = (slots ? bx : bx - nbk) * kTurnBlock + threadIdx.x;
+    // loads that do not depend on the generation counter: the vector of the
+    // slot's (the offspring's) merged row, and the slot's key of either parity
+    int32_t aj = -1;
+    unsigned long long ka = ~0ull, kb = ~0ull;
+    if (slots ? j < R.K : j < R.N) aj = R.assoc[slots ? j : R.K + j];
+    if (slots && j < R.K) {
+        ka = R.key[j];
+        kb = R.key[R.K + j];
+    }
+    const int64_t g = *R.t_done + 1;
+    const unsigned long long *key = key_of(R, g);
+    const int32_t *rows = off_row_of(R, g);
+    if (bx == 0) next_resets(R, g);
+    if (bx == 0 && threadIdx.x == 0) R.freecnt[(g + 1) & 1] = 0;
+
+    // the old individual's row: free unless its vector's key names it
+    int v = 0, fr = 0, pre = 0;
+    int32_t rowold = 0, rownew = 0;
+    float fs[kMaxM];
+#pragma unroll
+    for (int k = 0; k < kMaxM; ++k) fs[k] = 0.f;
+    const unsigned long long kk = aj >= 0 ? key[aj] : ~0ull;
+    if (slots) {
+        const unsigned long long kj = (g & 1) ? kb : ka;
+        const int64_t si = (int64_t)(kj & mask);
+        v = (kj != ~0ull && si < R.M) ? 1 : 0;
+        const int32_t *row0 = slot_row_of(R, g - 1);
+        int vold = 0;
+        if (j < R.K) {
+            vold = valid_of(R, g - 1)[j];
+            rowold = row0[j];
+        }
+        if (v) {
+            rownew = *(si < R.K ? row0 + si : rows + (si - R.K));
+            const float *F0 = fm_of(R, g - 1);
+#pragma unroll
+            for (int k = 0; k < kMaxM; ++k)
+                if (k < R.m) fs[k] = F0[si * R.m + k];
+        }
+#pragma unroll 4
+        for (int64_t q = threadIdx.x; q < bx * kTurnBlock; q += kTurnBlock)
+            pre += key[q] != ~0ull ? 1 : 0;
+        fr = vold && (kk == ~0ull || (int64_t)(kk & mask) != j);
+    } else if (j < R.M) {  // the generation's row list (unset beyond its M - nvalid rows)
+        rowold = rows[j];
+        const int32_t nv0 = *nvalid_of(R, g - 1);
+        // spare rows (j >= N) have no vector
+        fr = j < R.M - nv0 && (kk == ~0ull || (int64_t)(kk & mask) != R.K + j);
+    }
+    // the workgroup's sums in one scan: earlier survivors, its own, its free rows
+    const int x0 = wave_incl_scan(pre), x1 = wave_incl_scan(v), x2 = wave_incl_scan(fr);
+    if (lane == 63) {
+        wsum[0][wid] = x0;
+        wsum[1][wid] = x1;
+        wsum[2][wid] = x2;
+    }
+    __syncthreads();
+    int offset = 0, tot = 0, ftot = 0, before1 = 0, before2 = 0;
+#pragma unroll
+    for (int w = 0; w < kTurnWaves; ++w) {
+        offset += wsum[0][w];
+        tot += wsum[1][w];
+        ftot += wsum[2][w];
+        before1 += w < wid ? wsum[1][w] : 0;
+        before2 += w < wid ? wsum[2][w] : 0;
+    }
+    const int64_t nb = nbk + (R.M + kTurnBlock - 1) / kTurnBlock;
+    if (threadIdx.x == 0) {
+        fbase = ftot ? atomicAdd(&R.freecnt[g & 1], ftot) : 0;
+        // every workgroup has read t_done (its value was used before the
+        // barrier above) before it reports; the last one counts the generation
+        if (atomicAdd(R.ndone, 1u) == (uint32_t)nb - 1) {
+            *R.t_done = g;
+            *R.ndone = 0;
+        }
+    }
+    const bool ext = g % R.period == 0;  // an adaptation follows: extremes needed
+    if (slots) {
+#pragma unroll
+        for (int k = 0; k < kMaxM; ++k) {
+            if (k >= R.m) break;
+            const uint32_t e = v ? ord_enc(fs[k]) : 0xffffffffu;
+            const uint32_t lo = wave_min(e);
+            const uint32_t hi = ext ? wave_max(v ? e : 0u) : 0u;
+            if (lane == 0) {
+                smin[wid][k] = lo;
+                smax[wid][k] = hi;
+            }
+        }
+        if (j < R.K) {
+            R.surv[j] = v ? (int32_t)(((g & 1) ? kb : ka) & mask) : -1;
+            valid_of(R, g)[j] = (uint8_t)v;
+            slot_row_of(R, g)[j] = v ? rownew : rowold;
+            R.mvalid[j] = (uint8_t)v;  // survivors took part, so they are finite
+            key_of(R, g + 1)[j] = ~0ull;
+            float *F1 = fm_of(R, g);
+#pragma unroll
+            for (int k = 0; k < kMaxM; ++k)
+                if (k < R.m) F1[j * R.m + k] = v ? fs[k] : __int_as_float(0x7fc00000);
+        }
+        if (v)
+            reinterpret_cast<int2 *>(R.vs)[offset + before1 + x1 - 1] = make_int2((int32_t)j, rownew);
+        if (bx == nbk - 1 && threadIdx.x == 0) *nvalid_of(R, g) = offset + tot;
+    }
+    // Eq. 4's penalty factor of generation g+1, by the workgroup with the least work
+    if (bx == nb - 1 && threadIdx.x == 64)
+        *R.pen = (double)R.m * pow((double)(g + 1) / (double)R.t_max, R.alpha);
+    __syncthreads();
+    if (slots && threadIdx.x < R.m) {
+        const int k = threadIdx.x;
+        uint32_t lo = smin[0][k], hi = smax[0][k];
+#pragma unroll
+        for (int w = 1; w < kTurnWaves; ++w) {
+            lo = min(lo, smin[w][k]);
+            hi = max(hi, smax[w][k]);
+        }
+        if (lo != 0xffffffffu) {  // the parents' share of z* of g+1
+            atomicMin(&zbuf(R, g + 1)[k], lo);
+            if (ext) {
+                atomicMin(&rbits_of(R, g)[k], lo);
+                atomicMax(&rbits_of(R, g)[R.m + k], hi);
+            }
+        }
+    }
+    if (fr) off_row_of(R, g + 1)[fbase + before2 + x2 - 1] = rowold;
 }
 
 // The new population g (Alg. 1) written into the other buffer of
@@ -686,7 +850,7 @@ __device__ __forceinline__ void newpop_body(const RunView &R, int64_t bx)
         smin[threadIdx.x] = 0xffffffffu;
         smax[threadIdx.x] = 0u;
     }
-    if (bx == 0 && threadIdx.x < R.m) zbuf(R, g + 1)[threadIdx.x] = 0xffffffffu;
+    if (bx == 0) next_resets(R, g);
     if (bx == 0 && threadIdx.x == 0) *R.freecnt = 0;
     const int32_t *row0 = slot_row_of(R, g - 1);
     const float *F0 = fm_of(R, g - 1);
@@ -699,7 +863,7 @@ __device__ __forceinline__ void newpop_body(const RunView &R, int64_t bx)
     float fs[kMaxM];
     int32_t row = 0;
     if (v) {
-        row = s < R.K ? row0[s] : R.off_row[s - R.K];
+        row = s < R.K ? row0[s] : off_row_of(R, g)[s - R.K];
 #pragma unroll
         for (int k = 0; k < kMaxM; ++k)
             if (k < R.m) fs[k] = F0[(int64_t)s * R.m + k];
@@ -743,8 +907,9 @@ __device__ __forceinline__ void newpop_body(const RunView &R, int64_t bx)
     if ((threadIdx.x & 63) == 0) wc[threadIdx.x >> 6] = __popcll(b);
     __syncthreads();
     if (ext && threadIdx.x < R.m) {
-        if (smin[threadIdx.x] != 0xffffffffu) atomicMin(&R.rbits[threadIdx.x], smin[threadIdx.x]);
-        atomicMax(&R.rbits[R.m + threadIdx.x], smax[threadIdx.x]);
+        uint32_t *rb = rbits_of(R, g);
+        if (smin[threadIdx.x] != 0xffffffffu) atomicMin(&rb[threadIdx.x], smin[threadIdx.x]);
+        atomicMax(&rb[R.m + threadIdx.x], smax[threadIdx.x]);
     }
     if (threadIdx.x == 0) {
         R.bcount[bx] = wc[0] + wc[1] + wc[2] + wc[3];
@@ -771,6 +936,7 @@ __global__ __launch_bounds__(64) void k_rerank(RunView R, int gate)
     rerank_body<MD, GAMMA, ROWS>(R, blockIdx.x, gate);
 }
 __global__ __launch_bounds__(256) void k_newpop(RunView R) { newpop_body(R, blockIdx.x); }
+__global__ __launch_bounds__(kTurnBlock) void k_turn(RunView R) { turn_body(R, blockIdx.x); }
 
 // ----------------------------------------------------- batched (many runs)
 // blockIdx.x is decoded into (run, local block) through the span table; for
@@ -826,6 +992,11 @@ __global__ __launch_bounds__(256) void kb_newpop(const RunView *runs, const Span
 {
     const int s = find_span(sp, n, blockIdx.x);
     newpop_body(runs[sp[s].run], blockIdx.x - sp[s].start);
+}
+__global__ __launch_bounds__(kTurnBlock) void kb_turn(const RunView *runs, const Span *sp, int n)
+{
+    const int s = find_span(sp, n, blockIdx.x);
+    turn_body(runs[sp[s].run], blockIdx.x - sp[s].start);
 }
 
 // ------------------------------------------------------------- launchers
@@ -909,9 +1080,23 @@ hipError_t launch_gamma(const RunView &R, hipStream_t s, int force)
 
 hipError_t launch_select_back(const RunView &R, hipStream_t s)
 {
-    k_newpop<<<blocks(R.K, 256), 256, 0, s>>>(R);
+    if (R.turn)
+        k_turn<<<(unsigned)newpop_blocks(R), kTurnBlock, 0, s>>>(R);
+    else
+        k_newpop<<<(unsigned)newpop_blocks(R), 256, 0, s>>>(R);
     return hipGetLastError();
 }
+
+int64_t newpop_blocks(const RunView &R)
+{
+    if (!R.turn) return (R.K + 255) / 256;
+    return (R.K + kTurnBlock - 1) / kTurnBlock + (R.M + kTurnBlock - 1) / kTurnBlock;
+}
+
+// Runs whose k_newpop also prepares the next generation.  Each workgroup reads
+// all earlier keys, so the reads grow with K^2: at 16,384 vectors up to 15
+// loads a thread, at 100,128 they would be 39 MB per generation.
+bool turn_rule(int64_t K) { return K <= 16384; }
 
 int assoc_rows_per_block() { return 256 * 4; }
 int rerank_rows_per_wave() { return kBatchRows; }
@@ -928,7 +1113,12 @@ hipError_t launch_batch_select(int phase, int cls, const RunView *runs, const Sp
     constexpr int RR = 4;
     const dim3 g((unsigned)blocks);
     switch (phase) {
-    case BP_NEWPOP: kb_newpop<<<g, 256, 0, s>>>(runs, sp, n); break;
+    case BP_NEWPOP:  // class: RunView::turn
+        if (cls)
+            kb_turn<<<g, kTurnBlock, 0, s>>>(runs, sp, n);
+        else
+            kb_newpop<<<g, 256, 0, s>>>(runs, sp, n);
+        break;
     case BP_ASSOC:
 #define RVEA_BA(MV) kb_assoc<MV, RR, false><<<g, 256, 0, s>>>(runs, sp, n)
         RVEA_M_DISPATCH(cls, RVEA_BA);

@@ -88,9 +88,11 @@ __device__ __forceinline__ void adapt_v_body(const RunView &R, int64_t bx, bool 
 {
     const int64_t j = bx * 256 + threadIdx.x;
     double r[kMaxM];
-    bool ok = !check_due || (*R.t_done % R.period) == 0;
+    const int64_t g = *R.t_done;
+    const uint32_t *rb = rbits_of(R, g);
+    bool ok = !check_due || (g % R.period) == 0;
     for (int k = 0; k < R.m && ok; ++k) {
-        const uint32_t lo = R.rbits[k], hi = R.rbits[R.m + k];
+        const uint32_t lo = rb[k], hi = rb[R.m + k];
         if (lo == 0xffffffffu) {
             ok = false;
             break;
@@ -181,6 +183,7 @@ int batch_phase_class(int phase, const RunView &R)
         return offspring_segment(R.d, R.N) |
                (R.eta_c == 20.0 && R.eta_m == 20.0 ? kDefaultIndices : 0);
     if (phase == BP_ASSOC && R.gG > 0) return kIndexedClass | R.m;
+    if (phase == BP_NEWPOP) return R.turn;
     if (phase == BP_GRID_CELLS) return R.m;  // the grid's cells, or the line's gamma
     if (phase == BP_ASSOC || phase == BP_RERANK || phase == BP_GAMMA_ASSOC ||
         phase == BP_GAMMA_RERANK)
@@ -200,7 +203,7 @@ int64_t batch_phase_blocks(int phase, const RunView &R)
     if (phase == BP_ASSOC && R.gG > 0) return grid_phase_blocks(phase, R);
     if (phase == BP_RERANK && R.gG > 0) return 0;  // the indexed association ranks in full
     switch (phase) {
-    case BP_PREP: return (R.K + R.N + 255) / 256;
+    case BP_PREP: return R.turn ? 0 : (R.K + R.N + 255) / 256;
     case BP_OFFSPRING: {
         if (R.op != OP_GA) return operator_blocks(R);
         const int S = offspring_segment(R.d, R.N);
@@ -212,7 +215,7 @@ int64_t batch_phase_blocks(int phase, const RunView &R)
     case BP_GAMMA_ASSOC: return batch_phase_nbx(phase, R) * R.KC;
     case BP_RERANK: return (R.M + rerank_rows_per_wave() - 1) / rerank_rows_per_wave();
     case BP_GAMMA_RERANK: return (R.K + rerank_rows_per_wave() - 1) / rerank_rows_per_wave();
-    case BP_NEWPOP:
+    case BP_NEWPOP: return newpop_blocks(R);
     case BP_ADAPT: return (R.K + 255) / 256;
     }
     return 0;

@@ -48,7 +48,11 @@ struct RunView {
     // pair below; generation p+1 reads it and writes population p+1 into
     // the other buffer, so the new population needs no copy-back.
     int32_t *slot_rows; // 2 x K: physical row of each slot
-    int32_t *off_row;   // N: physical row of each offspring this generation
+    // physical row of each offspring of a generation (its first N entries).
+    // turn: 2 x (K+N), by generation parity, every row that no individual of
+    // the parents' population holds; else N
+    int32_t *off_row;
+    int turn;           // 1: k_newpop also prepares the next generation (k_turn's rule)
     uint8_t *valids;    // 2 x K
     float *Fms;         // 2 x M x m merged objectives (slots, then offspring)
     uint8_t *mvalid;    // M: row takes part in the selection
@@ -71,7 +75,6 @@ struct RunView {
     double *gvh;        // K x 4: by cell, their unit directions (grid) or
                         // (v, |v|) (line)
     int32_t *lcnt;      // cells: candidate-list length (-1: full scan; grid only)
-    int32_t *lstart;    // cells: first record of each list (-1: full scan; grid only)
     unsigned long long *gtot;  // 4: the allocator of the cells' vector ranges (build),
                                // 1 when the build left some vector's gamma,
                                // 1 when some vector is outside the
@@ -79,22 +82,24 @@ struct RunView {
     double *lrec;       // gcap x 4: (v, |v|) of the list entries
     int32_t *lidx;      // gcap: vector id of each record
     int32_t *vs;        // K x 2: valid slots, ascending, each with its physical row
-    int32_t *nvalid;    // 1
+    int32_t *nvalid;    // 2: individuals of population p, by its parity
     int32_t *stamp;     // K+N: the generation that will read the row (rows of
                         // the current population carry t_done + 1)
     int32_t *bcount;    // per-256-slot-block valid counts of the current population
-    int32_t *freecnt;   // 1: free rows handed out (prepare)
+    int32_t *freecnt;   // 2: free rows handed out (turn: by the parity of the generation that counts them)
     double *V0, *V;     // K x m
     float *V32;         // K x 4 or K x 8 (padded with zeros)
     double *vn;         // K norms of V
     double *gamma;      // K
-    uint32_t *zbits;    // 2 x m ordered-encoded ideal point, by generation parity
-    uint32_t *rbits;    // 2m ordered-encoded survivor min / max
+    uint32_t *zbits;    // 3 x m ordered-encoded ideal point, by generation modulo 3
+    uint32_t *rbits;    // 2 x 2m ordered-encoded survivor min / max, by generation parity
     float *pmax;        // KC x M chunk maxima
     uint32_t *pmask;    // KC x M candidate-tile masks
     int32_t *assoc;     // M
     double *apd;        // M
-    unsigned long long *key;  // K: min over associated rows of (APD, row), packed
+    // K (turn: 2 x K, by generation parity): min over associated rows of (APD,
+    // row), packed
+    unsigned long long *key;
     int kb;             // row-index bits of a key: M < 2^kb
     int32_t *surv;      // K: survivor's merged row of the last selection, or -1
     int64_t *t_done;    // completed generations
@@ -120,6 +125,26 @@ __device__ __forceinline__ uint8_t *valid_of(const RunView &R, int64_t p)
 __device__ __forceinline__ float *fm_of(const RunView &R, int64_t p)
 {
     return R.Fms + (p & 1) * R.M * R.m;
+}
+
+__device__ __forceinline__ int32_t *nvalid_of(const RunView &R, int64_t p)
+{
+    return R.nvalid + (p & 1);
+}
+
+// buffers of generation gen: its offspring's rows, its keys, the extremes of
+// its survivors
+__device__ __forceinline__ int32_t *off_row_of(const RunView &R, int64_t gen)
+{
+    return R.off_row + (R.turn ? (gen & 1) * R.M : 0);
+}
+__device__ __forceinline__ unsigned long long *key_of(const RunView &R, int64_t gen)
+{
+    return R.key + (R.turn ? (gen & 1) * R.K : 0);
+}
+__device__ __forceinline__ uint32_t *rbits_of(const RunView &R, int64_t gen)
+{
+    return R.rbits + (gen & 1) * 2 * R.m;
 }
 
 // cells of an index of side G: a G x G grid for three objectives, a line of
@@ -380,12 +405,13 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v)
     return max(max(a, b), max(c, d));
 }
 
-// Ideal point z* of generation gen (Alg. 1): two buffers alternate by
-// parity, so a generation's minima can be reset by the generation before and
-// the last selection's z* stays readable.
+// Ideal point z* of generation gen (Alg. 1): three buffers take turns, so
+// that while k_newpop of generation g lowers z* of g+1 by the survivors (or
+// k_prep does before g+1), that of g+2 is reset and that of g, the last
+// selection's, stays readable.
 __device__ __forceinline__ uint32_t *zbuf(const RunView &R, int64_t gen)
 {
-    return R.zbits + (gen & 1) * R.m;
+    return R.zbits + ((uint32_t)gen % 3u) * (uint32_t)R.m;
 }
 
 // Child objectives f (m values) of merged row `row` (>= K): the row takes

@@ -27,7 +27,7 @@ enum Buf {
     B_NVALID, B_STAMP, B_V0, B_V, B_V32, B_VN, B_GAMMA, B_ZBITS, B_RBITS, B_PMAX, B_PMASK,
     B_ASSOC, B_APD, B_KEY, B_SURV, B_TDONE, B_COUNTERS, B_VCHANGED, B_BCOUNT, B_FREECNT, B_PEN,
     B_NDONE, B_LQ, B_GPART, B_VEL,
-    B_GR, B_GCELL, B_GCNT, B_GSTART, B_GNUM, B_GVEC, B_GVH, B_LCNT, B_LSTART, B_GTOT,
+    B_GR, B_GCELL, B_GCNT, B_GSTART, B_GNUM, B_GVEC, B_GVH, B_LCNT, B_GTOT,
     B_LREC, B_LIDX, B_COUNT
 };
 
@@ -119,18 +119,19 @@ void make_layout(int problem, int m, int d, int64_t N, int64_t K, int op, Layout
     const size_t cells = (size_t)index_cells(m, L.gG);
     L.gcap = m == 3 ? (int64_t)grid_slot() * (int64_t)cells : 0;
     const size_t sz[] = {
-        (size_t)(K + N) * L.ld * 4, (size_t)2 * K * 4, (size_t)N * 4, (size_t)2 * K,
+        (size_t)(K + N) * L.ld * 4, (size_t)2 * K * 4,
+        turn_rule(K) ? (size_t)2 * M * 4 : (size_t)N * 4, (size_t)2 * K,
         (size_t)2 * M * m * 4, (size_t)M,
-        (size_t)P * 2 * 4, (size_t)K * 8, 4, (size_t)(K + N) * 4, (size_t)K * m * 8,
+        (size_t)P * 2 * 4, (size_t)K * 8, 8, (size_t)(K + N) * 4, (size_t)K * m * 8,
         (size_t)K * m * 8, (size_t)K * L.stride * 4, (size_t)K * 8, (size_t)K * 8,
-        (size_t)2 * m * 4, (size_t)2 * m * 4, (size_t)L.KC * M * 4, (size_t)L.KC * M * 4,
-        (size_t)M * 4, (size_t)M * 8, (size_t)K * 8, (size_t)K * 4, 8, 3 * 8, 4,
-        (size_t)((K + N + 255) / 256) * 4, 4, 8, 4,
+        (size_t)3 * m * 4, (size_t)4 * m * 4, (size_t)L.KC * M * 4, (size_t)L.KC * M * 4,
+        (size_t)M * 4, (size_t)M * 8, (size_t)K * (turn_rule(K) ? 16 : 8), (size_t)K * 4, 8, 3 * 8, 4,
+        (size_t)((K + N + 255) / 256) * 4, 8, 8, 4,
         problem == kPolicy ? (size_t)kLqFloats * 4 : 0,
         L.osplit > 1 ? (size_t)P * L.osplit * 2 * 8 : 8,
         swarm(op) ? (size_t)(K + N) * L.ld * 4 : 8,
         (size_t)m * 8, (size_t)K * 4, cells * 4, cells * 4, cells * 4, (size_t)K * 4,
-        (size_t)K * 32, cells * 4, cells * 4, 32, (size_t)L.gcap * 32, (size_t)L.gcap * 4};
+        (size_t)K * 32, cells * 4, 32, (size_t)L.gcap * 32, (size_t)L.gcap * 4};
     static_assert(sizeof(sz) / sizeof(sz[0]) == B_COUNT, "one size per buffer");
     size_t o = 0;
     for (int b = 0; b < B_COUNT; ++b) {
@@ -427,6 +428,7 @@ rvea_status create_run(int problem, int m, int d, int64_t N, int64_t K, uint64_t
     R.X = (float *)(w + L.off[B_X]);
     R.slot_rows = (int32_t *)(w + L.off[B_SLOT]);
     R.off_row = (int32_t *)(w + L.off[B_OFF]);
+    R.turn = turn_rule(K) ? 1 : 0;
     R.valids = (uint8_t *)(w + L.off[B_VALID]);
     R.Fms = (float *)(w + L.off[B_FM]);
     R.mvalid = (uint8_t *)(w + L.off[B_MVALID]);
@@ -448,7 +450,6 @@ rvea_status create_run(int problem, int m, int d, int64_t N, int64_t K, uint64_t
         R.gvec = (int32_t *)(w + L.off[B_GVEC]);
         R.gvh = (double *)(w + L.off[B_GVH]);
         R.lcnt = (int32_t *)(w + L.off[B_LCNT]);
-        R.lstart = (int32_t *)(w + L.off[B_LSTART]);
         R.gtot = (unsigned long long *)(w + L.off[B_GTOT]);
         R.lrec = (double *)(w + L.off[B_LREC]);
         R.lidx = (int32_t *)(w + L.off[B_LIDX]);
@@ -478,7 +479,7 @@ rvea_status create_run(int problem, int m, int d, int64_t N, int64_t K, uint64_t
     R.t_done = (int64_t *)(w + L.off[B_TDONE]);
     R.counters = (unsigned long long *)(w + L.off[B_COUNTERS]);
     R.vchanged = (int32_t *)(w + L.off[B_VCHANGED]);
-    hipError_t e = hipMemsetAsync(R.zbits, 0xff, (size_t)2 * m * 4, r->stream);
+    hipError_t e = hipMemsetAsync(R.zbits, 0xff, (size_t)3 * m * 4, r->stream);
     if (e == hipSuccess && problem == kPolicy) {
         float *lq = (float *)(w + L.off[B_LQ]);
         R.lq = lq;
@@ -555,7 +556,7 @@ rvea_status rvea_step(rvea_run r)
 {
     if (!r) return RVEA_EINVAL;
     if (r->phase != 0 || r->batch) return RVEA_ESTATE;
-    HIPCHK(r, launch_prepare(r->R, r->stream));
+    if (!r->R.turn) HIPCHK(r, launch_prepare(r->R, r->stream));
     rvea_status st = timed(r, 0, [&] { return launch_offspring(r->R, r->stream); }, "offspring");
     if (st != RVEA_OK) return st;
     if (r->R.problem == kPolicy) {
@@ -598,7 +599,7 @@ namespace {
 // enqueue one generation's kernels on stream s (graph capture or eager)
 hipError_t enqueue_generation(const RunView &R, hipStream_t s, bool adapt)
 {
-    hipError_t e = launch_prepare(R, s);
+    hipError_t e = R.turn ? hipSuccess : launch_prepare(R, s);
     if (e == hipSuccess) e = launch_offspring(R, s);
     if (e == hipSuccess && R.problem == kPolicy) e = launch_rollout(R, s, true);
     if (e == hipSuccess) e = launch_assoc(R, s);
@@ -753,6 +754,11 @@ namespace {
 int32_t *slot_rows_at(const RunView &R, int64_t p) { return R.slot_rows + (p & 1) * R.K; }
 uint8_t *valids_at(const RunView &R, int64_t p) { return R.valids + (p & 1) * R.K; }
 float *fm_at(const RunView &R, int64_t p) { return R.Fms + (p & 1) * R.M * R.m; }
+// the rows of the offspring made from population p
+int32_t *off_rows_at(const RunView &R, int64_t p)
+{
+    return R.off_row + (R.turn ? ((p + 1) & 1) * R.M : 0);
+}
 
 // completed generations as the device counts them (after a synchronize)
 rvea_status device_t(rvea_run r, int64_t *t)
@@ -835,10 +841,11 @@ rvea_status rvea_set_state(rvea_run r, const float *X, const float *F, const uin
     }
     HIPCHK(r, hipMemcpy(R.t_done, &t, 8, hipMemcpyHostToDevice));
     HIPCHK(r, hipMemset(R.stamp, 0xff, (size_t)(R.K + R.N) * 4));
-    HIPCHK(r, hipMemset(R.zbits, 0xff, (size_t)2 * R.m * 4));
+    HIPCHK(r, hipMemset(R.zbits, 0xff, (size_t)3 * R.m * 4));
     if (R.Vel) HIPCHK(r, hipMemset(R.Vel, 0, (size_t)(R.K + R.N) * R.ld * 4));
     HIPCHK(r, hipDeviceSynchronize());
     HIPCHK(r, launch_stamp(R, r->stream));
+    if (R.turn) HIPCHK(r, launch_prepare(R, r->stream));
     HIPCHK(r, hipStreamSynchronize(active_stream(r)));
     r->t = t;
     r->has_selection = false;
@@ -851,16 +858,17 @@ rvea_status rvea_get_offspring(rvea_run r, float *X, float *F, int32_t *parents)
     if (!offspring_readable(r)) return RVEA_ESTATE;
     const RunView &R = r->R;
     HIPCHK(r, hipStreamSynchronize(active_stream(r)));
+    int64_t td = 0;
+    rvea_status st = device_t(r, &td);
+    if (st != RVEA_OK) return st;
     if (X) {
         std::vector<int32_t> rows(R.N);
-        HIPCHK(r, hipMemcpy(rows.data(), R.off_row, R.N * 4, hipMemcpyDeviceToHost));
-        rvea_status st = copy_rows(r, rows, X);
+        HIPCHK(r, hipMemcpy(rows.data(), off_rows_at(R, offspring_pop(r, td)), R.N * 4,
+                            hipMemcpyDeviceToHost));
+        st = copy_rows(r, rows, X);
         if (st != RVEA_OK) return st;
     }
     if (F) {
-        int64_t td = 0;
-        rvea_status st = device_t(r, &td);
-        if (st != RVEA_OK) return st;
         HIPCHK(r, hipMemcpy(F, fm_at(R, offspring_pop(r, td)) + R.K * R.m,
                             (size_t)R.N * R.m * 4, hipMemcpyDeviceToHost));
     }
@@ -881,7 +889,7 @@ rvea_status rvea_get_selection(rvea_run r, float *zstar, int32_t *assoc, double 
         int64_t td = 0;  // the last selection's generation picks the buffer
         HIPCHK(r, hipMemcpy(&td, R.t_done, 8, hipMemcpyDeviceToHost));
         uint32_t zb[kMaxM];
-        HIPCHK(r, hipMemcpy(zb, R.zbits + (td & 1) * R.m, R.m * 4, hipMemcpyDeviceToHost));
+        HIPCHK(r, hipMemcpy(zb, R.zbits + (td % 3) * R.m, R.m * 4, hipMemcpyDeviceToHost));
         for (int k = 0; k < R.m; ++k) {
             const uint32_t e = zb[k];
             const uint32_t u = (e & 0x80000000u) ? (e & 0x7FFFFFFFu) : ~e;
@@ -909,7 +917,7 @@ rvea_status rvea_get_rows(rvea_run r, int offspring, const int64_t *idx, int64_t
     if (st0 != RVEA_OK) return st0;
     const int64_t pop = offspring ? offspring_pop(r, td) : td;
     std::vector<int32_t> map(lim);
-    HIPCHK(r, hipMemcpy(map.data(), offspring ? R.off_row : slot_rows_at(R, td), lim * 4,
+    HIPCHK(r, hipMemcpy(map.data(), offspring ? off_rows_at(R, pop) : slot_rows_at(R, td), lim * 4,
                         hipMemcpyDeviceToHost));
     for (int64_t q = 0; q < n; ++q) {
         const int64_t i = idx[q];
@@ -936,8 +944,9 @@ rvea_status rvea_get_velocities(rvea_run r, int offspring, float *Vel)
     if (st != RVEA_OK) return st;
     const int64_t n = offspring ? R.N : R.K;
     std::vector<int32_t> rows(n);
-    HIPCHK(r, hipMemcpy(rows.data(), offspring ? R.off_row : slot_rows_at(R, td), n * 4,
-                        hipMemcpyDeviceToHost));
+    HIPCHK(r, hipMemcpy(rows.data(), offspring ? off_rows_at(R, offspring_pop(r, td))
+                                               : slot_rows_at(R, td),
+                        n * 4, hipMemcpyDeviceToHost));
     st = copy_rows(r, rows, Vel, R.Vel);
     if (st != RVEA_OK) return st;
     if (!offspring) {
@@ -1117,7 +1126,7 @@ rvea_status rvea_autotune(rvea_run r, rvea_tuning *out)
     HIPCHK(r, hipMemcpy(saved, R.counters, sizeof saved, hipMemcpyDeviceToHost));
     // the next generation's offspring and ideal point give the association
     // its real input; nothing is committed, so the state is unchanged
-    HIPCHK(r, launch_prepare(R, r->stream));
+    if (!R.turn) HIPCHK(r, launch_prepare(R, r->stream));
     HIPCHK(r, launch_offspring(R, r->stream));
     if (R.problem == kPolicy) HIPCHK(r, launch_rollout(R, r->stream, true));
     EventPair ev(r);
@@ -1237,7 +1246,7 @@ rvea_status rvea_autotune(rvea_run r, rvea_tuning *out)
     R.gG = gG0;
     HIPCHK(r, hipMemcpy(R.counters, saved, sizeof saved, hipMemcpyHostToDevice));
     // the trial's preparation handed out free rows: the real one starts over
-    HIPCHK(r, hipMemsetAsync(R.freecnt, 0, 4, r->stream));
+    if (!R.turn) HIPCHK(r, hipMemsetAsync(R.freecnt, 0, 4, r->stream));
     HIPCHK(r, hipStreamSynchronize(r->stream));
     drop_graphs(r);            // captured with the old launch shapes
     r->has_selection = false;  // the trial overwrote the last selection's buffers

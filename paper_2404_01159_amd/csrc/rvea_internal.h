@@ -58,7 +58,10 @@ hipError_t launch_grid_build(const RunView &R, hipStream_t s, int force);
 hipError_t launch_grid_rebuild(const RunView &R, hipStream_t s);
 hipError_t launch_assoc_grid(const RunView &R, hipStream_t s);
 hipError_t launch_rerank(const RunView &R, hipStream_t s);
+// the new population (and, by turn_rule, the next generation's preparation)
 hipError_t launch_select_back(const RunView &R, hipStream_t s);
+bool turn_rule(int64_t K);
+int64_t newpop_blocks(const RunView &R);
 hipError_t launch_adapt(const RunView &R, hipStream_t s);
 hipError_t launch_init_gauss(const RunView &R, hipStream_t s);
 // objectives of the N initial slots (offspring = false) or of the offspring

@@ -1,0 +1,75 @@
+"""The kernel that writes the new population and prepares the next generation
+in one pass, against the oracle generation by generation, at the sizes where
+its work is cut: 1,024 slots (and 1,024 row-list entries) per workgroup,
+fewer individuals than vectors (rows to spare), an odd number of offspring, an
+adaptation every generation, and both sides of the rule that chooses it."""
+import numpy as np
+import pytest
+
+from parity import lockstep, new_stats
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def P():
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    import paper_2404_01159_amd as P
+
+    return P
+
+
+@pytest.fixture(scope="module")
+def O():
+    import oracle as O
+
+    O.lib()
+    return O
+
+
+# (problem, m, d, N, K): slots at the edges of one and two workgroups (any
+# count is a lattice of two objectives), list entries at 1,024 +- 1
+@pytest.mark.parametrize("shape", [(1, 2, 6, 1, 2), (2, 2, 5, 1023, 1023), (1, 2, 4, 1024, 1024),
+                                   (3, 2, 7, 1000, 1025), (1, 2, 5, 23, 1001), (2, 3, 9, 511, 528),
+                                   (1, 2, 4, 2047, 2049), (2, 8, 9, 33, 36)])
+def test_turn_matches_oracle(P, O, shape):
+    problem, m, d, N, K = shape
+    prm = P.default_params(t_max=6, fr=1 / 6)  # adapts after every generation
+    run = P.Run(problem, m, d, N, K, seed=K + N, params=prm)
+    stats = lockstep(O, run, prm, 4, new_stats())
+    run.close()
+    assert stats["generations"] == 4
+    assert stats["near_ties"] <= 1e-4 * stats["vectors"] + 1
+
+
+@pytest.mark.parametrize("K", [16383, 16384, 16385])
+def test_rule_edges_match_oracle(P, O, K):
+    prm = P.default_params(t_max=4, fr=0.5)
+    run = P.Run(1, 2, 4, K - 3, K, seed=K, params=prm)
+    stats = lockstep(O, run, prm, 3, new_stats())
+    run.close()
+    assert stats["near_ties"] <= 1e-4 * stats["vectors"] + 1
+
+
+def test_state_set_back_and_forward(P):
+    """A run set back to an earlier state (either parity of the generation)
+    repeats what it did, and its last offspring are not readable until then."""
+    prm = P.default_params(t_max=20, fr=0.2)
+    run = P.Run(2, 3, 14, 90, 105, seed=3, params=prm)
+    states = [run.get_state()]
+    for _ in range(7):
+        run.run(1)
+        states.append(run.get_state())
+    for t in (5, 2, 4, 0):
+        s = states[t]
+        run.set_state(s["X"], s["F"], s["valid"], s["V"], s["gamma"], t)
+        with pytest.raises(Exception):
+            run.get_offspring()
+        run.run(7 - t)
+        got = run.get_state()
+        for k in ("X", "F", "valid", "V", "gamma"):
+            assert np.array_equal(got[k], states[7][k], equal_nan=True), (t, k)
+    run.close()
