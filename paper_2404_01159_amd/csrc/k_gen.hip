@@ -397,23 +397,37 @@ __device__ __forceinline__ float dterm(int problem, float z)
     return dist_term(DK > 0 ? DK : problem, z);
 }
 
-// One segment of S lanes per parent pair.  NR > 0 compiles in the root index
+// One wavefront's mutation sites and ideal-point minima.
+template <int S>
+struct OffspringLds {
+    int32_t sites[64 / S][2][kMaxSites];
+    double mags[64 / S][2][kMaxSites];
+    float vals[64 / S][2][kMaxSites];  // mutated gene at each site
+    uint32_t zmin[kMaxM];
+};
+
+// orders one wavefront's LDS accesses (the wavefront's own are processed in
+// order; other wavefronts' LDS is not involved)
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// One wavefront, the bx-th: one segment of S lanes per parent pair.  NR > 0 compiles in the root index
 // n = eta + 1 = NR of both SBX and mutation; DK = 0 skips evaluation (the
 // policy problem has its own rollout kernel), DK > 0 fixes the distance term
 // and DK = -1 reads problem and indices from the run (the batched kernel).
 // Every variant takes the same arithmetic steps, so results do not depend on
 // which one ran.
-template <int S, int NR, int DK, int BS>
-__device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx)
+template <int S, int NR, int DK>
+__device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx, OffspringLds<S> &L)
 {
-    constexpr int SEGS = BS / S;
-    __shared__ int32_t sh_sites[SEGS][2][kMaxSites];
-    __shared__ double sh_mags[SEGS][2][kMaxSites];
-    __shared__ float sh_vals[SEGS][2][kMaxSites];  // mutated gene at each site
-    __shared__ uint32_t szmin[kMaxM];
-    if (threadIdx.x < kMaxM) szmin[threadIdx.x] = 0xffffffffu;
+    constexpr int SEGS = 64 / S;
+    const int wl = threadIdx.x & 63;  // lane of the wavefront
+    if (wl < kMaxM) L.zmin[wl] = 0xffffffffu;
 
-    const int seg = threadIdx.x / S, lane = threadIdx.x % S;
+    const int seg = wl / S, lane = wl % S;
     const int64_t P = (R.N + 1) / 2;
     // segment u of the grid: pair p, part sp of its genes (osplit parts)
     const int ns = R.osplit;
@@ -461,10 +475,10 @@ __device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx)
     if (pr > 0.0) {
         const double lq = log1p(-(pr > 1.0 ? 1.0 : pr));
         if (active)
-            draw_sites<S>(R, t, o1, o2, has2, lq, lane, sh_sites[seg][0], sh_mags[seg][0],
-                          sh_sites[seg][1], sh_mags[seg][1], &n1, &n2);
+            draw_sites<S>(R, t, o1, o2, has2, lq, lane, L.sites[seg][0], L.mags[seg][0],
+                          L.sites[seg][1], L.mags[seg][1], &n1, &n2);
     }
-    __syncthreads();
+    wave_sync();
     const bool evaluate = DK > 0 || (DK < 0 && R.problem != kPolicy);
     if (active) {
         bool nocross = false;
@@ -503,7 +517,7 @@ __device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx)
             const int idx = b0 + lane;
             const int c = idx < n1 ? 0 : 1;
             const int k = c ? idx - n1 : idx;
-            const int g = idx < nsites ? sh_sites[seg][c][k] : -1;
+            const int g = idx < nsites ? L.sites[seg][c][k] : -1;
             if (g >= 4 * qa && g < 4 * qb) {
                 const W4 w = draw(R, (uint32_t)(g >> 2), (uint32_t)p, t, TAG_SBX);
                 const int kk = g & 3;
@@ -514,8 +528,8 @@ __device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx)
                 if (((word >> 6) & 1u) || nocross) hB = 0.5;
                 const double hm = 0.5 * (xa_ + xb_), dd = xa_ - xb_;
                 const double x = dclip(fma(c == 0 ? hB : -hB, dd, hm), lb, ub);
-                const double mg = sh_mags[seg][c][k];
-                sh_vals[seg][c][k] =
+                const double mg = L.mags[seg][c][k];
+                L.vals[seg][c][k] =
                     (float)dclip(x + pm_delta<NR>(x, lb, ub, mg, R.eta_m, nroot_m), lb, ub);
             }
         }
@@ -523,8 +537,8 @@ __device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx)
         // mutation sites (ascending) seen through a cursor per child: this
         // lane's quads ascend, so the next site at or after the quad is
         // found by advancing past the other lanes' sites
-        const int32_t *st1 = sh_sites[seg][0], *st2 = sh_sites[seg][1];
-        const float *mv1 = sh_vals[seg][0], *mv2 = sh_vals[seg][1];
+        const int32_t *st1 = L.sites[seg][0], *st2 = L.sites[seg][1];
+        const float *mv1 = L.vals[seg][0], *mv2 = L.vals[seg][1];
         int p1 = 0, p2 = 0;
         int nx1 = n1 > 0 ? st1[0] : INT_MAX, nx2 = n2 > 0 ? st2[0] : INT_MAX;
 
@@ -645,7 +659,7 @@ __device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx)
                 }
 #pragma unroll
                 for (int k = 0; k < kMaxM; ++k)
-                    if (k < R.m) atomicMin(&szmin[k], ord_enc(f[k]));
+                    if (k < R.m) atomicMin(&L.zmin[k], ord_enc(f[k]));
             };
             float pos[kMaxM];
 #pragma unroll
@@ -654,16 +668,16 @@ __device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx)
             emit(pos, lane == 0 ? g1 : g2, R.K + (lane == 0 ? o1 : o2));
         }
     }
-    // the workgroup's share of the ideal point: one guarded atomic per
+    // the wavefront's share of the ideal point: one guarded atomic per
     // objective (values only decrease, so a stale read costs an atomic at most)
-    __syncthreads();
-    if (evaluate && threadIdx.x < R.m) {
-        const uint32_t e = szmin[threadIdx.x];
+    wave_sync();
+    if (evaluate && wl < R.m) {
+        const uint32_t e = L.zmin[wl];
         uint32_t *zb = zbuf(R, t);
         // a relaxed atomic read: unlike a volatile one it does not wait for
         // the wavefront's outstanding stores
-        if (e < __hip_atomic_load(&zb[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            atomicMin(&zb[threadIdx.x], e);
+        if (e < __hip_atomic_load(&zb[wl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMin(&zb[wl], e);
     }
     // the parents' slots (kept for the host): stored last, so that no wait
     // for an earlier load also waits for this store
@@ -680,29 +694,38 @@ __device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx)
 template <int S, int NR, int DK>
 __global__ __launch_bounds__(kOffBlock) void k_offspring(RunView R)
 {
-    offspring_body<S, NR, DK, kOffBlock>(R, blockIdx.x);
+    __shared__ OffspringLds<S> L;
+    offspring_body<S, NR, DK>(R, blockIdx.x, L);
 }
 
 // Objectives of the children of pairs split over segments (osplit > 1),
-// one lane per child: the parts' distance sums added in part order, the
-// position genes read back from the child's row; then, as in the offspring
-// kernel, the row's take-part flag, the non-finite count and the children's
-// share of the ideal point.
-__device__ __forceinline__ void offspring_finish_body(const RunView &R, int64_t bx)
+// kFinishLanes lanes per child (a row of 16 lanes): each adds every 16th of
+// the parts' distance sums, the 16 sums are paired by the segment sum, and the
+// first lane reads the position genes back from the child's row; then, as in
+// the offspring kernel, the row's take-part flag, the non-finite count and the
+// children's share of the ideal point.  One lane per child took 18.6 us at 100
+// children of 82 parts: a chain of that many loads and additions.
+constexpr int kFinishLanes = 16;
+__device__ __forceinline__ void offspring_finish_body(const RunView &R, int64_t tid)
 {
-    const int64_t o = bx * 256 + threadIdx.x;
+    const int64_t o = tid / kFinishLanes;
+    const int sub = (int)(tid % kFinishLanes);
     const int64_t P = (R.N + 1) / 2;
     const int64_t pop = *R.t_done;
     if (*nvalid_of(R, pop) == 0) return;  // no parent: the offspring kernel left empty children
     float *Fm = fm_of(R, pop);
-    const bool has = o < R.N;
+    double g = 0.0;
+    if (o < R.N) {
+        const int64_t p = o < P ? o : o - P;
+        const int ns = R.osplit;
+        const double *part = R.gpart + p * ns * 2 + (o < P ? 0 : 1);
+#pragma unroll 4
+        for (int k = sub; k < ns; k += kFinishLanes) g += part[2 * k];
+    }
+    g = seg_sum<kFinishLanes>(g);
+    const bool has = o < R.N && sub == 0;
     float f[kMaxM] = {};
     if (has) {
-        const int64_t p = o < P ? o : o - P;
-        const int c = o < P ? 0 : 1;
-        const int ns = R.osplit;
-        double g = 0.0;
-        for (int k = 0; k < ns; ++k) g += R.gpart[(p * ns + k) * 2 + c];
         const float *row = R.X + (int64_t)off_row_of(R, pop + 1)[o] * R.ld;
         float pos[kMaxM];
 #pragma unroll
@@ -718,7 +741,7 @@ __device__ __forceinline__ void offspring_finish_body(const RunView &R, int64_t 
 
 __global__ __launch_bounds__(256) void k_offspring_finish(RunView R)
 {
-    offspring_finish_body(R, blockIdx.x);
+    offspring_finish_body(R, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 // ----------------------------------------------------- batched (many runs)
@@ -735,13 +758,14 @@ __global__ __launch_bounds__(kOffBlock) void kb_offspring(const RunView *runs, c
                                                           int n)
 {
     const int s = find_span(sp, n, blockIdx.x);
-    offspring_body<S, NR, -1, kOffBlock>(runs[sp[s].run], blockIdx.x - sp[s].start);
+    __shared__ OffspringLds<S> L;
+    offspring_body<S, NR, -1>(runs[sp[s].run], blockIdx.x - sp[s].start, L);
 }
 __global__ __launch_bounds__(256) void kb_offspring_finish(const RunView *runs, const Span *sp,
                                                            int n)
 {
     const int s = find_span(sp, n, blockIdx.x);
-    offspring_finish_body(runs[sp[s].run], blockIdx.x - sp[s].start);
+    offspring_finish_body(runs[sp[s].run], (blockIdx.x - sp[s].start) * 256 + threadIdx.x);
 }
 
 // ------------------------------------------------------------- launchers
@@ -770,6 +794,11 @@ int offspring_segment(int d, int64_t N)
 {
     const int S = pick_segment(d);
     const int64_t P = (N + 1) / 2;
+    // few pairs of short rows: 16 lanes, though few of them have genes, draw
+    // eight mutation events of a child at once instead of two or four (105
+    // individuals x 12 genes: 13.1 -> 9.6 us), while the wavefronts are at most
+    // one for every second SIMD
+    if (S < 16 && P <= 2048) return 16;
     if (S == 64 && (P > kResidentOffspringWaves || (P > kResidentOffspringWaves / 4 && d < 2048)))
         return 32;
     return S;
@@ -886,6 +915,8 @@ void launch_offspring_as(const RunView &R, hipStream_t s)
     }
 }
 
+int64_t offspring_finish_blocks(const RunView &R) { return (R.N * kFinishLanes + 255) / 256; }
+
 hipError_t launch_offspring(const RunView &R, hipStream_t s)
 {
     if (R.op != OP_GA) return launch_operator(R, s);
@@ -902,7 +933,7 @@ hipError_t launch_offspring(const RunView &R, hipStream_t s)
         launch_offspring_as<0, -1>(R, s);
     }
     if (R.osplit > 1 && R.problem != kPolicy)
-        k_offspring_finish<<<(unsigned)((R.N + 255) / 256), 256, 0, s>>>(R);
+        k_offspring_finish<<<(unsigned)offspring_finish_blocks(R), 256, 0, s>>>(R);
     return hipGetLastError();
 }
 

@@ -210,7 +210,7 @@ int64_t batch_phase_blocks(int phase, const RunView &R)
         return ((R.N + 1) / 2 * R.osplit + (kOffBlock / S) - 1) / (kOffBlock / S);
     }
     case BP_OFFSPRING_FIN:  // only runs whose pairs are split over segments
-        return R.osplit > 1 ? (R.N + 255) / 256 : 0;
+        return R.osplit > 1 ? offspring_finish_blocks(R) : 0;
     case BP_ASSOC:
     case BP_GAMMA_ASSOC: return batch_phase_nbx(phase, R) * R.KC;
     case BP_RERANK: return (R.M + rerank_rows_per_wave() - 1) / rerank_rows_per_wave();

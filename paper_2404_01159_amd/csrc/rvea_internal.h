@@ -22,6 +22,7 @@ constexpr int kSegMask = 0xff, kDefaultIndices = 0x100;
 int pick_segment(int d);                 // lanes per individual (initialization)
 int offspring_segment(int d, int64_t N);  // lanes per parent pair
 int offspring_splits(int d, int64_t N);   // segments per parent pair
+int64_t offspring_finish_blocks(const RunView &R);
 int assoc_rows_per_block();
 int rerank_rows_per_wave();      // batched launch
 int default_rerank_rows(int64_t rows);  // single-run default for this many rows

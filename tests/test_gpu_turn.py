@@ -2,7 +2,8 @@
 in one pass, against the oracle generation by generation, at the sizes where
 its work is cut: 1,024 slots (and 1,024 row-list entries) per workgroup,
 fewer individuals than vectors (rows to spare), an odd number of offspring, an
-adaptation every generation, and both sides of the rule that chooses it."""
+adaptation every generation, and both sides of the rule that chooses it; and
+small populations' reproduction."""
 import numpy as np
 import pytest
 
@@ -72,4 +73,17 @@ def test_state_set_back_and_forward(P):
         got = run.get_state()
         for k in ("X", "F", "valid", "V", "gamma"):
             assert np.array_equal(got[k], states[7][k], equal_nan=True), (t, k)
+    run.close()
+
+
+# few pairs of long rows: the parts' distance sums of a child over 16 lanes,
+# part counts below, at and above 16; few pairs of short rows: 16 lanes a pair
+@pytest.mark.parametrize("shape", [(1, 3, 1024, 5, 6), (3, 2, 7681, 7, 8), (2, 3, 8192, 33, 36),
+                                   (1, 5, 8704, 14, 15), (2, 3, 3, 9, 10), (1, 2, 17, 301, 301),
+                                   (3, 4, 31, 4, 4)])
+def test_few_pairs_match_oracle(P, O, shape):
+    problem, m, d, N, K = shape
+    prm = P.default_params(t_max=6, fr=0.5)
+    run = P.Run(problem, m, d, N, K, seed=d, params=prm)
+    lockstep(O, run, prm, 3, new_stats())
     run.close()
