@@ -14,6 +14,7 @@
 #include "rvea.h"
 #include "rvea_dev.h"
 #include "rvea_internal.h"
+#include "rvea_transfer.h"
 
 using namespace rvea;
 
@@ -282,16 +283,21 @@ rvea_status timed(rvea_run r, int id, Fn fn, const char *what)
     return RVEA_OK;
 }
 
-rvea_status check_counters(rvea_run r)
+rvea_status counters_status(rvea_run r, const unsigned long long *c)
 {
-    unsigned long long c[3];
-    HIPCHK(r, hipMemcpy(c, r->R.counters, sizeof c, hipMemcpyDeviceToHost));
     if (c[2] != 0) {
         std::snprintf(r->err, sizeof r->err,
                       "a child drew more than %d mutation sites; lower p_m", kMaxSites);
         return RVEA_EUNSUPPORTED;
     }
     return RVEA_OK;
+}
+
+rvea_status check_counters(rvea_run r)
+{
+    unsigned long long c[3];
+    HIPCHK(r, hipMemcpy(c, r->R.counters, sizeof c, hipMemcpyDeviceToHost));
+    return counters_status(r, c);
 }
 
 }  // namespace
@@ -522,6 +528,7 @@ rvea_status create_run(int problem, int m, int d, int64_t N, int64_t K, uint64_t
         return RVEA_EDEVICE;
     }
     g_create_err[0] = 0;
+    staging_runs(1);
     *out = r;
     return RVEA_OK;
 }
@@ -785,27 +792,31 @@ rvea_status rvea_get_state(rvea_run r, float *X, float *F, uint8_t *valid, doubl
 {
     if (!r) return RVEA_EINVAL;
     const RunView &R = r->R;
-    HIPCHK(r, hipStreamSynchronize(active_stream(r)));
+    // everything in one pass over the stream: the kernels find the current
+    // population's buffers from the device's own generation counter
     int64_t td = 0;
-    rvea_status st0 = device_t(r, &td);
-    if (st0 != RVEA_OK) return st0;
-    std::vector<uint8_t> vh(R.K);
-    HIPCHK(r, hipMemcpy(vh.data(), valids_at(R, td), R.K, hipMemcpyDeviceToHost));
-    if (valid) std::memcpy(valid, vh.data(), R.K);
-    if (X) {
+    unsigned long long c[3] = {};
+    const size_t K = (size_t)R.K, m = (size_t)R.m;
+    std::vector<StateArray> arrays = {{R.t_done, 0, &td, 8}, {R.counters, 0, c, sizeof c}};
+    if (F) arrays.push_back({R.Fms, (size_t)R.M * m * 4, F, K * m * 4});
+    if (valid) arrays.push_back({R.valids, K, valid, K});
+    if (V) arrays.push_back({R.V, 0, V, K * m * 8});
+    if (V0) arrays.push_back({R.V0, 0, V0, K * m * 8});
+    if (gamma) arrays.push_back({R.gamma, 0, gamma, K * 8});
+    const bool long_rows = X && (size_t)R.d * 4 > kStageBytes;  // a row per chunk at most
+    HIPCHK(r, transfer_state(R, arrays, long_rows ? nullptr : X, true, active_stream(r)));
+    if (long_rows) {
+        std::vector<uint8_t> vh(R.K);
         std::vector<int32_t> rows(R.K);
+        HIPCHK(r, hipMemcpy(vh.data(), valids_at(R, td), R.K, hipMemcpyDeviceToHost));
         HIPCHK(r, hipMemcpy(rows.data(), slot_rows_at(R, td), R.K * 4, hipMemcpyDeviceToHost));
-        rvea_status st = copy_rows(r, rows, X);
+        const rvea_status st = copy_rows(r, rows, X);
         if (st != RVEA_OK) return st;
         for (int64_t j = 0; j < R.K; ++j)
             if (!vh[j]) std::memset(X + j * R.d, 0, (size_t)R.d * 4);
     }
-    if (F) HIPCHK(r, hipMemcpy(F, fm_at(R, td), (size_t)R.K * R.m * 4, hipMemcpyDeviceToHost));
-    if (V) HIPCHK(r, hipMemcpy(V, R.V, (size_t)R.K * R.m * 8, hipMemcpyDeviceToHost));
-    if (V0) HIPCHK(r, hipMemcpy(V0, R.V0, (size_t)R.K * R.m * 8, hipMemcpyDeviceToHost));
-    if (gamma) HIPCHK(r, hipMemcpy(gamma, R.gamma, (size_t)R.K * 8, hipMemcpyDeviceToHost));
     if (t) *t = td;
-    return check_counters(r);
+    return counters_status(r, c);
 }
 
 rvea_status rvea_set_state(rvea_run r, const float *X, const float *F, const uint8_t *valid,
@@ -814,39 +825,25 @@ rvea_status rvea_set_state(rvea_run r, const float *X, const float *F, const uin
     if (!r || !X || !F || !valid || t < 0) return RVEA_EINVAL;
     if (r->phase != 0 || r->batch) return RVEA_ESTATE;
     const RunView &R = r->R;
-    HIPCHK(r, hipStreamSynchronize(active_stream(r)));
-    HIPCHK(r, hipMemcpy2D(R.X, (size_t)R.ld * 4, X, (size_t)R.d * 4, (size_t)R.d * 4,
-                          (size_t)R.K, hipMemcpyHostToDevice));
-    std::vector<int32_t> rows(R.K);
-    std::vector<uint8_t> vv(R.K);
-    for (int64_t j = 0; j < R.K; ++j) {
-        rows[j] = (int32_t)j;
-        vv[j] = valid[j] ? 1 : 0;
-    }
-    HIPCHK(r, hipMemcpy(slot_rows_at(R, t), rows.data(), R.K * 4, hipMemcpyHostToDevice));
-    HIPCHK(r, hipMemcpy(valids_at(R, t), vv.data(), R.K, hipMemcpyHostToDevice));
-    HIPCHK(r, hipMemcpy(fm_at(R, t), F, (size_t)R.K * R.m * 4, hipMemcpyHostToDevice));
-    if (V) {
-        HIPCHK(r, hipMemcpy(R.V, V, (size_t)R.K * R.m * 8, hipMemcpyHostToDevice));
-        HIPCHK(r, launch_vec_aux(R, r->stream));
-    }
-    if (gamma)
-        HIPCHK(r, hipMemcpy(R.gamma, gamma, (size_t)R.K * 8, hipMemcpyHostToDevice));
-    else if (V)
-        HIPCHK(r, launch_gamma(R, r->stream, 1));
-    if (V && r->L.gG > 0) {  // a host-set V: the index unscaled and rebuilt
-        HIPCHK(r, hipStreamSynchronize(r->stream));
-        HIPCHK(r, hipMemcpy(R.gr, kUnitScale, (size_t)R.m * sizeof(double), hipMemcpyHostToDevice));
-        if (R.gG > 0) HIPCHK(r, launch_grid_build(R, r->stream, 1));
-    }
-    HIPCHK(r, hipMemcpy(R.t_done, &t, 8, hipMemcpyHostToDevice));
-    HIPCHK(r, hipMemset(R.stamp, 0xff, (size_t)(R.K + R.N) * 4));
-    HIPCHK(r, hipMemset(R.zbits, 0xff, (size_t)3 * R.m * 4));
-    if (R.Vel) HIPCHK(r, hipMemset(R.Vel, 0, (size_t)(R.K + R.N) * R.ld * 4));
-    HIPCHK(r, hipDeviceSynchronize());
+    const size_t K = (size_t)R.K, m = (size_t)R.m;
+    std::vector<StateArray> arrays = {{fm_at(R, t), 0, const_cast<float *>(F), K * m * 4},
+                                      {valids_at(R, t), 0, const_cast<uint8_t *>(valid), K}};
+    if (V) arrays.push_back({R.V, 0, const_cast<double *>(V), K * m * 8});
+    if (gamma) arrays.push_back({R.gamma, 0, const_cast<double *>(gamma), K * 8});
+    const bool long_rows = (size_t)R.d * 4 > kStageBytes;  // a row per chunk at most
+    HIPCHK(r, transfer_state(R, arrays, long_rows ? nullptr : const_cast<float *>(X), false, r->stream));
+    if (long_rows)
+        HIPCHK(r, hipMemcpy2D(R.X, (size_t)R.ld * 4, X, (size_t)R.d * 4, (size_t)R.d * 4,
+                              (size_t)R.K, hipMemcpyHostToDevice));
+    const bool build = V && r->L.gG > 0;  // a host-set V: the index unscaled and rebuilt
+    HIPCHK(r, launch_set_reset(R, r->stream, t, build ? 1 : 0));
+    if (V) HIPCHK(r, launch_vec_aux(R, r->stream));
+    if (V && !gamma) HIPCHK(r, launch_gamma(R, r->stream, 1));
+    if (build && R.gG > 0) HIPCHK(r, launch_grid_build(R, r->stream, 1));
+    if (R.Vel) HIPCHK(r, hipMemsetAsync(R.Vel, 0, (size_t)(R.K + R.N) * R.ld * 4, r->stream));
     HIPCHK(r, launch_stamp(R, r->stream));
     if (R.turn) HIPCHK(r, launch_prepare(R, r->stream));
-    HIPCHK(r, hipStreamSynchronize(active_stream(r)));
+    HIPCHK(r, hipStreamSynchronize(r->stream));
     r->t = t;
     r->has_selection = false;
     return RVEA_OK;
@@ -1280,6 +1277,7 @@ rvea_status rvea_destroy(rvea_run r)
     drop_graphs(r);
     if (r->cap_stream) (void)hipStreamDestroy(r->cap_stream);
     delete r;
+    staging_runs(-1);
     return RVEA_OK;
 }
 

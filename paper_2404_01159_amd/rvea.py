@@ -267,12 +267,12 @@ class Run:
 
     def get_state(self, genes=True):
         K, d, m = self.K, self.d, self.m
-        X = np.zeros((K, d), np.float32) if genes else None
-        F = np.zeros((K, m), np.float32)
-        valid = np.zeros(K, np.uint8)
-        V = np.zeros((K, m), np.float64)
-        V0 = np.zeros((K, m), np.float64)
-        g = np.zeros(K, np.float64)
+        X = np.empty((K, d), np.float32) if genes else None
+        F = np.empty((K, m), np.float32)
+        valid = np.empty(K, np.uint8)
+        V = np.empty((K, m), np.float64)
+        V0 = np.empty((K, m), np.float64)
+        g = np.empty(K, np.float64)
         t = C.c_int64(0)
         self._chk(lib.rvea_get_state(self._h, _p(X), _p(F), _p(valid), _p(V), _p(V0), _p(g),
                                      C.byref(t)), "rvea_get_state")

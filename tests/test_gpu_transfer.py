@@ -1,0 +1,89 @@
+"""State transfers in chunks over pinned staging buffers: sizes around the
+4 MiB chunk (one row per chunk, several rows, arrays over several chunks),
+byte arrays at odd offsets, empty slots, two runs and two threads at once."""
+import threading
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def P():
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    import paper_2404_01159_amd as P
+
+    return P
+
+
+def random_state(seed, K, d, m, frac=0.7):
+    r = np.random.default_rng(seed)
+    valid = (r.random(K) < frac).astype(np.uint8)
+    valid[0] = 1
+    X = r.random((K, d), np.float32)
+    X[valid == 0] = 0
+    F = r.random((K, m)).astype(np.float32)
+    return X, F, valid
+
+
+# rows of 3 genes, of exactly one chunk (1,048,576), one short and one over;
+# 300,000 slots: objectives and vectors over several chunks; odd slot counts
+@pytest.mark.parametrize("m,d,K", [(2, 3, 2), (2, 2, 7), (3, 33, 105), (2, 1048576, 3), (2, 1048575, 5),
+                                   (2, 1048577, 3), (3, 700, 1540), (2, 4, 300001), (5, 90, 1001)])
+@pytest.mark.parametrize("t", [0, 7])
+def test_set_then_get(P, m, d, K, t):
+    X, F, valid = random_state(d + K, K, d, m)
+    run = P.Run(1, m, d, K, K, seed=1)
+    V0 = run.get_state(genes=False)["V"]
+    run.set_state(X, F, 5 * valid, t=t)  # any non-zero mark counts
+    got = run.get_state()
+    assert got["t"] == t
+    assert np.array_equal(got["valid"], valid)
+    assert np.array_equal(got["X"], X)
+    assert np.array_equal(got["F"], F)
+    assert np.array_equal(got["V"], V0) and np.array_equal(got["V0"], V0)
+    assert np.all(np.isfinite(got["gamma"]))
+    run.close()
+
+
+def test_vectors_and_gamma_set_from_the_host(P):
+    run = P.Run(2, 5, 20, 126, 126, seed=2)
+    st = run.get_state()
+    V = st["V"] * np.linspace(0.5, 2.0, 5)
+    V /= np.linalg.norm(V, axis=1)[:, None]
+    g = np.linspace(0.1, 0.2, 126)
+    run.set_state(st["X"], st["F"], st["valid"], V, g, 3)
+    got = run.get_state()
+    assert np.array_equal(got["V"], V) and np.array_equal(got["gamma"], g)
+    assert np.array_equal(got["V0"], st["V0"])
+    run.set_state(st["X"], st["F"], st["valid"], V, None, 4)  # gamma from the vectors
+    assert not np.array_equal(run.get_state(genes=False)["gamma"], g)
+    run.close()
+
+
+def test_threads_share_the_staging_buffers(P):
+    shapes = [(3, 500, 2016), (2, 40, 4001), (3, 900, 1540), (2, 12, 64)]
+    bad = []
+
+    def work(k):
+        m, d, K = shapes[k]
+        run = P.Run(1, m, d, K, K, seed=k, stream=torch.cuda.Stream())
+        for i in range(5):
+            X, F, valid = random_state(10 * k + i, K, d, m)
+            run.set_state(X, F, valid, t=i)
+            got = run.get_state()
+            if not (np.array_equal(got["X"], X) and np.array_equal(got["F"], F)
+                    and np.array_equal(got["valid"], valid) and got["t"] == i):
+                bad.append((k, i))
+        run.close()
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
