@@ -218,6 +218,12 @@ struct W4 {
     uint32_t w[4];
 };
 
+// a ^ b ^ c in one instruction
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 __device__ __forceinline__ W4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                              uint32_t k0, uint32_t k1)
 {
@@ -232,8 +238,8 @@ __device__ __forceinline__ W4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c
     for (int r = 0; r < 10; ++r) {
         const uint64_t a = (uint64_t)c0 * 0xD2511F53u;
         const uint64_t b = (uint64_t)c2 * 0xCD9E8D57u;
-        const uint32_t x0 = (uint32_t)(b >> 32) ^ c1 ^ k0;
-        const uint32_t x2 = (uint32_t)(a >> 32) ^ c3 ^ k1;
+        const uint32_t x0 = xor3((uint32_t)(b >> 32), c1, k0);
+        const uint32_t x2 = xor3((uint32_t)(a >> 32), c3, k1);
         c1 = (uint32_t)b;
         c3 = (uint32_t)a;
         c0 = x0;
