@@ -737,18 +737,21 @@ __global__ __launch_bounds__(kOffBlock) void k_offspring(RunView R)
     offspring_body<S, NR, DK>(R, blockIdx.x, L);
 }
 
-// Objectives of the children of pairs split over segments (osplit > 1),
-// kFinishLanes lanes per child (a row of 16 lanes): each adds every 16th of
-// the parts' distance sums, the 16 sums are paired by the segment sum, and the
-// first lane reads the position genes back from the child's row; then, as in
-// the offspring kernel, the row's take-part flag, the non-finite count and the
-// children's share of the ideal point.  One lane per child took 18.6 us at 100
-// children of 82 parts: a chain of that many loads and additions.
-constexpr int kFinishLanes = 16;
+// Objectives of the children of pairs split over segments (osplit > 1): the
+// parts' distance sums added, the position genes read back from the child's
+// row; then, as in the offspring kernel, the row's take-part flag, the
+// non-finite count and the children's share of the ideal point.  A child of
+// 16 parts or more takes a row of 16 lanes, each adding every 16th part, their
+// sums paired by the segment sum (one lane took 18.6 us at 100 children of 82
+// parts, a chain of that many loads and additions; 7.0 so); a child of fewer
+// parts one lane (there the children are many, and 16 lanes for each made the
+// batched finish 18.2 us against 15.2).
+__host__ __device__ __forceinline__ int finish_lanes(const RunView &R) { return R.osplit >= 16 ? 16 : 1; }
 __device__ __forceinline__ void offspring_finish_body(const RunView &R, int64_t tid)
 {
-    const int64_t o = tid / kFinishLanes;
-    const int sub = (int)(tid % kFinishLanes);
+    const int fl = finish_lanes(R);  // uniform
+    const int64_t o = fl == 16 ? tid / 16 : tid;
+    const int sub = fl == 16 ? (int)(tid % 16) : 0;
     const int64_t P = (R.N + 1) / 2;
     const int64_t pop = *R.t_done;
     if (*nvalid_of(R, pop) == 0) return;  // no parent: the offspring kernel left empty children
@@ -759,9 +762,9 @@ __device__ __forceinline__ void offspring_finish_body(const RunView &R, int64_t 
         const int ns = R.osplit;
         const double *part = R.gpart + p * ns * 2 + (o < P ? 0 : 1);
 #pragma unroll 4
-        for (int k = sub; k < ns; k += kFinishLanes) g += part[2 * k];
+        for (int k = sub; k < ns; k += fl) g += part[2 * k];
     }
-    g = seg_sum<kFinishLanes>(g);
+    if (fl == 16) g = seg_sum<16>(g);
     const bool has = o < R.N && sub == 0;
     float f[kMaxM] = {};
     if (has) {
@@ -954,7 +957,7 @@ void launch_offspring_as(const RunView &R, hipStream_t s)
     }
 }
 
-int64_t offspring_finish_blocks(const RunView &R) { return (R.N * kFinishLanes + 255) / 256; }
+int64_t offspring_finish_blocks(const RunView &R) { return (R.N * finish_lanes(R) + 255) / 256; }
 
 hipError_t launch_offspring(const RunView &R, hipStream_t s)
 {
