@@ -43,14 +43,25 @@ __device__ __forceinline__ bf16x8 to_bf16(f32x4 lo, f32x4 hi)
     return __builtin_convertvector(v, bf16x8);
 }
 
-// the four low / high bfloat16 lanes of a pack, widened (exactly) to binary32
+// the four low / high bfloat16 lanes of a pack, widened (exactly) to binary32:
+// a value is the upper half of its binary32, so a shift or a mask of the packed
+// words (written as conversions, each lane was rounded to bfloat16 once more
+// before its shift)
+__device__ __forceinline__ f32x4 widen4(uint32_t a, uint32_t b)
+{
+    return f32x4{__uint_as_float(a << 16), __uint_as_float(a & 0xffff0000u),
+                 __uint_as_float(b << 16), __uint_as_float(b & 0xffff0000u)};
+}
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f32x4 lo4(bf16x8 v)
 {
-    return f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+    const u32x4 w = __builtin_bit_cast(u32x4, v);
+    return widen4(w[0], w[1]);
 }
 __device__ __forceinline__ f32x4 hi4(bf16x8 v)
 {
-    return f32x4{(float)v[4], (float)v[5], (float)v[6], (float)v[7]};
+    const u32x4 w = __builtin_bit_cast(u32x4, v);
+    return widen4(w[2], w[3]);
 }
 
 __device__ __forceinline__ f32x4 ld4(const float *p)
