@@ -334,10 +334,13 @@ __global__ __launch_bounds__(kBlock) void k_init(RunView R)
     float pos[kMaxM];
 #pragma unroll
     for (int k = 0; k < kMaxM - 1; ++k) pos[k] = __shfl(pv[k & 3], k >> 2, S);
+    pos[kMaxM - 1] = 0.f;
     if (lane == 0) {
         float f[kMaxM];
         finish_objectives(R.problem, R.m, R.d, pos, gsum, f);
-        for (int k = 0; k < R.m; ++k) R.Fms[i * R.m + k] = f[k];  // population 0
+#pragma unroll
+        for (int k = 0; k < kMaxM; ++k)
+            if (k < R.m) R.Fms[i * R.m + k] = f[k];  // population 0
         R.valids[i] = 1;
         R.slot_rows[i] = (int32_t)i;
     }

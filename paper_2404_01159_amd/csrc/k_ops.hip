@@ -274,7 +274,9 @@ __device__ __forceinline__ void operator_body(const RunView &R, int64_t bx)
         if (mine) {
             finish_objectives(R.problem, R.m, R.d, lane == 0 ? pos1 : pos2, lane == 0 ? g1 : g2,
                               f);
-            for (int k = 0; k < R.m; ++k) Fm[row * R.m + k] = f[k];
+#pragma unroll
+            for (int k = 0; k < kMaxM; ++k)
+                if (k < R.m) Fm[row * R.m + k] = f[k];
         }
         child_ideal(R, t, mine, row, f);
     }

@@ -430,12 +430,16 @@ __device__ __forceinline__ void child_ideal(const RunView &R, int64_t gen, bool 
 {
     bool ok = has;
     if (has) {
-        for (int k = 0; k < R.m; ++k) ok = ok && isfinite(f[k]);
+#pragma unroll
+        for (int k = 0; k < kMaxM; ++k)
+            if (k < R.m) ok = ok && isfinite(f[k]);
         if (!ok) atomicAdd(&R.counters[0], 1ull);
         R.mvalid[row] = ok ? 1 : 0;
     }
     uint32_t *zb = zbuf(R, gen);
-    for (int k = 0; k < R.m; ++k) {
+#pragma unroll
+    for (int k = 0; k < kMaxM; ++k) {
+        if (k >= R.m) break;  // uniform
         const uint32_t e = wave_min(ok ? ord_enc(f[k]) : 0xffffffffu);
         if ((threadIdx.x & 63) == 0 &&
             e < __hip_atomic_load(&zb[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
