@@ -37,15 +37,18 @@
 //          vector loses to the champion for every row direction in C, with
 //          a margin far above binary64 rounding
 // Lists longer than kSlot, cells whose box would pass kStage cells from
-// C, and cells with no vector within kNear cells are marked for a full scan
-// (correct for any vector set, counted as full rescans).  The same pass
-// gives Eq. 5's gamma of each vector whose nearest other vector provably lies
-// in its cell's staged neighbourhood (the nearest staged one is closer than
-// the neighbourhood's boundary); if any vector is left, it asks for the full
-// gamma pass.  Each cell's list
-// has a slot of kSlot records of its own; the cells' ranges of vector
-// positions are allocated by one atomic add per wavefront, so the order of
-// the vectors in memory varies from build to build (no result depends on it).
+// C, cells with no vector within kNear cells and cells near one with more
+// vectors than its kBucket places are marked for a full scan (correct for any
+// vector set, counted as full rescans).  The same pass gives Eq. 5's gamma of
+// the cell's vectors: from the staged neighbourhood where that provably holds
+// the nearest other vector (the nearest staged one is closer than the
+// neighbourhood's boundary), else by a scan of all vectors.  A cell's vectors
+// have kBucket places and its list kSlot records at fixed positions; the order
+// of a cell's vectors varies from build to build (no result depends on it).
+// After an adaptation the rebuild is one kernel, the adaptation having put each
+// vector into its cell; with ranges allocated to the cells, a fill and the full
+// gamma pass's two kernels behind it (which exited at once) it was five, about
+// 4.5 us each beside the cells' own time.
 //
 // Two objectives.  The index is a line: a direction x >= 0 maps to its share
 // u = (x1 / r1) / (x0 / r0 + x1 / r1) of the scaled simplex (u = j / H for
@@ -60,8 +63,8 @@
 // A walk past kLineWalk cells on a side, or any vector outside the quadrant
 // (which the bucket leaves out and flags), makes the row scan all vectors
 // (counted).  Eq. 5's gamma of each vector comes from the same walk, with
-// the vector as the row, itself and the vectors parallel to it skipped; a
-// walk past the limit leaves it to the full pass.
+// the vector as the row, itself and the vectors parallel to it skipped, or past
+// the limit from a scan of all vectors by its wavefront.
 #include <algorithm>
 
 #include "rvea_dev.h"
@@ -324,33 +327,27 @@ __device__ __forceinline__ double line_bound(double f0, double f1, double nrm, d
 }
 
 // ------------------------------------------------------------- build
-// vectors per cell (counts start at zero: the last build cleared them); a
-// rebuild after an adaptation skips this pass, the adaptation having
-// counted each vector as it wrote it (k_vectors.hip)
-__device__ __forceinline__ void grid_bucket_body(const RunView &R, int64_t bx, int gate)
+// vectors into the grid's cells, or counted into the line's (counts start at
+// zero); a rebuild after an adaptation skips this pass, the adaptation having
+// done it for each vector as it wrote it (k_vectors.hip)
+__device__ __forceinline__ void grid_bucket_body(const RunView &R, int64_t bx)
 {
-    if (!gate && *R.vchanged == 0) return;
     const int64_t j = bx * 256 + threadIdx.x;
-    if (j == 0) {
-        R.gtot[1] = 0;  // the full gamma pass not needed (yet)
-        R.gtot[2] = 0;  // no vector outside the line (yet)
-    }
+    if (j == 0 && R.m != 3) R.gtot[1] = 0;  // no vector outside the line (yet)
     if (j >= R.K) return;
-    int c;
     if (R.m == 3) {
-        c = cell_of(R.V[j * 3], R.V[j * 3 + 1], R.V[j * 3 + 2], R.gr, R.gG);
-        if (c < 0) c = 0;  // cannot happen for a nonzero vector >= 0
-    } else {
-        double u;
-        c = line_cell_of(R.V[j * 2], R.V[j * 2 + 1], R.gr, R.gG, u);
+        const int c = cell_of(R.V[j * 3], R.V[j * 3 + 1], R.V[j * 3 + 2], R.gr, R.gG);
+        bucket_vector(R, j, c < 0 ? 0 : c, R.V + j * 3, R.vn[j]);
+        return;
     }
+    double u;
+    const int c = line_cell_of(R.V[j * 2], R.V[j * 2 + 1], R.gr, R.gG, u);
     R.gcell[j] = c;
     if (c >= 0) atomicAdd(&R.gcnt[c], 1);
 }
 
-// each cell's range of positions (one atomic add per wavefront); the
-// counts become the fill cursors (grid: counting up from zero, cleared again
-// by the cells pass; line: counting down to zero)
+// line: each cell's range of positions (one atomic add per wavefront); the
+// counts become the fill cursors, counting down to zero
 __device__ __forceinline__ void grid_ranges_body(const RunView &R, int64_t bx, int gate)
 {
     if (!gate && *R.vchanged == 0) return;
@@ -361,34 +358,40 @@ __device__ __forceinline__ void grid_ranges_body(const RunView &R, int64_t bx, i
     if (c < cells) {
         R.gstart[c] = (int32_t)st;
         R.gnum[c] = n;
-        if (R.m == 3) R.gcnt[c] = 0;
     }
 }
 
-// vectors into their cells' ranges, with their unit directions (grid) or
-// (v, |v|) (line, whose build ends here: the range allocator cleared)
+// line: vectors into their cells' ranges, with (v, |v|); the range allocator
+// cleared
 __device__ __forceinline__ void grid_fill_body(const RunView &R, int64_t bx, int gate)
 {
     if (!gate && *R.vchanged == 0) return;
     const int64_t j = bx * 256 + threadIdx.x;
-    if (R.m != 3 && j == 0) R.gtot[0] = 0;
+    if (j == 0) R.gtot[0] = 0;
     if (j >= R.K) return;
     const int c = R.gcell[j];
     if (c < 0) {  // outside the line: every row scans all vectors
-        R.gtot[2] = 1;
+        R.gtot[1] = 1;
         return;
     }
-    const int64_t p = R.m == 3 ? R.gstart[c] + atomicAdd(&R.gcnt[c], 1)
-                               : R.gstart[c] + atomicSub(&R.gcnt[c], 1) - 1;
+    const int64_t p = R.gstart[c] + atomicSub(&R.gcnt[c], 1) - 1;
     R.gvec[p] = (int32_t)j;
-    if (R.m != 3) {
-        reinterpret_cast<double4 *>(R.gvh)[p] =
-            make_double4(R.V[j * 2], R.V[j * 2 + 1], R.vn[j], 0.0);
-        return;
-    }
-    const double inv = 1.0 / R.vn[j];
-    reinterpret_cast<double4 *>(R.gvh)[p] =
-        make_double4(R.V[j * 3] * inv, R.V[j * 3 + 1] * inv, R.V[j * 3 + 2] * inv, 0.0);
+    reinterpret_cast<double4 *>(R.gvh)[p] = make_double4(R.V[j * 2], R.V[j * 2 + 1], R.vn[j], 0.0);
+}
+
+// Eq. 5's gamma of vector id by the whole wavefront: the largest binary64
+// cosine to another vector that is not parallel to it, over all vectors (as the
+// full gamma pass computes it).
+// (Out of line: rare, and inlined it would keep the callers' registers; it takes
+// the arrays, not the run's view, which would have to be copied to memory.)
+template <int M>
+__device__ __attribute__((noinline)) void gamma_scan_call(const double *V, const double *vn,
+                                                          double *gamma, int64_t K, int32_t id,
+                                                          int lane);
+template <int M>
+__device__ __forceinline__ void gamma_scan(const RunView &R, int32_t id, int lane)
+{
+    gamma_scan_call<M>(R.V, R.vn, R.gamma, R.K, id, lane);
 }
 
 // Wavefront-wide minimum / best (largest value, lowest id on ties) over
@@ -448,6 +451,25 @@ __device__ __forceinline__ void wave_best(double &v, int32_t &j, int32_t &p)
     v = second ? v1 : v0;
     j = second ? j1 : j0;
     p = second ? p1 : p0;
+}
+
+template <int M>
+__device__ __attribute__((noinline)) void gamma_scan_call(const double *V, const double *vn,
+                                                          double *gamma, int64_t K, int32_t id,
+                                                          int lane)
+{
+    double vi[M], best = -INFINITY;
+    for (int k = 0; k < M; ++k) vi[k] = V[(int64_t)id * M + k];
+    const double vni = vn[id];
+    for (int64_t j = lane; j < K; j += 64) {
+        double s = vi[0] * V[j * M];
+        for (int k = 1; k < M; ++k) s = fma(vi[k], V[j * M + k], s);
+        const double cv = s / (vni * vn[j]);
+        if (j != id && cv < 1.0) best = fmax(best, cv);
+    }
+    best = -wave_fmin(-best);
+    if (lane == 0)
+        gamma[id] = best > -INFINITY ? acos(best < -1.0 ? -1.0 : best) : 1.5707963267948966;
 }
 
 constexpr int kNear = 3;  // the covering search looks at the (2 kNear + 1)^2 cells around
@@ -520,9 +542,8 @@ static int64_t grid_live_cells(int G) { return (int64_t)G + (int64_t)G * (G + 1)
 // radius (lane k tests radius k, at most kStage); the champions and the
 // list from the staged box vectors, written into the cell's slot at each
 // lane's prefix.
-// A neighbourhood over kStageCap vectors or a box over kStage marks the cell
-// for a full scan.  Also clears the cell's fill cursor and the range
-// allocator for the next build.
+// A neighbourhood over kStageCap vectors or with a cell over kBucket, or a box
+// over kStage marks the cell for a full scan.
 __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, int gate)
 {
     if (!gate && *R.vchanged == 0) return;
@@ -539,29 +560,29 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
     __shared__ CellGeo g;
     __shared__ Champs ch;
     __shared__ Stage st;
-    if (lane == 0) {
-        if (c == 0) R.gtot[0] = 0;
-        R.gcnt[c] = 0;
-    }
     // stage: each lane's cells of the neighbourhood, their vector counts
     // scanned over the wave, then the vectors
     int cnt[2] = {0, 0}, from[2] = {0, 0};
+    bool over = false;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const int t = lane + 64 * u;
         if (t < kStageW * kStageW) {
             const int i = ci - kStage + t / kStageW, jj = cj - kStage + t % kStageW;
             if (i >= 0 && i < G && jj >= 0 && jj < G) {
-                from[u] = R.gstart[i * G + jj];
-                cnt[u] = R.gnum[i * G + jj];
+                from[u] = (i * G + jj) * kBucket;
+                cnt[u] = R.gcnt[i * G + jj];
+                over = over || cnt[u] > kBucket;
             }
         }
     }
-    const int mine0 = cnt[0] + cnt[1];
+    const int own_cnt = __builtin_amdgcn_readlane(cnt[0], kStage * kStageW + kStage);
+    const bool crowded = __any(over);
+    const int mine0 = crowded ? 0 : cnt[0] + cnt[1];
     const int incl0 = wave_incl_scan(mine0);
     const int nst = __builtin_amdgcn_readlane(incl0, 63);
     cell_geo(R, c, g, lane);
-    bool full = nst > kStageCap;
+    bool full = crowded || nst > kStageCap;
     if (!full) {
         int q = incl0 - mine0;
 #pragma unroll
@@ -596,12 +617,21 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
     // holds that vector (the nearest staged one is closer than the
     // neighbourhood's boundary: every own vector lies within rho of u_c, so
     // its distance to that boundary is at least u_c's less rho); otherwise
-    // the full gamma pass is asked for
+    // by a scan of all vectors
+    if (full && own_cnt > 0) {  // uniform; own vectors past the bucket by their cell
+        if (own_cnt <= kBucket) {
+            for (int o = 0; o < own_cnt; ++o) gamma_scan<3>(R, R.gvec[(int64_t)c * kBucket + o], lane);
+        } else {
+            for (int64_t j0 = 0; j0 < R.K; j0 += 64) {
+                unsigned long long b = __ballot(j0 + lane < R.K && R.gcell[j0 + lane] == c);
+                for (; b; b &= b - 1) gamma_scan<3>(R, (int32_t)(j0 + __ffsll(b) - 1), lane);
+            }
+        }
+    }
     {
         const int own = kStage * kStageW + kStage;  // the centre cell's lane
         const int oq0 = __builtin_amdgcn_readlane(incl0 - mine0, own);
-        const int on = full ? 0 : __builtin_amdgcn_readlane(cnt[0], own);
-        bool need = full && __builtin_amdgcn_readlane(cnt[0], own) > 0;
+        const int on = full ? 0 : own_cnt;
         const float lo =
             __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bsm), kStage)) - g.rho -
             kSlack;
@@ -627,10 +657,9 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
             if (dmin < INFINITY && lo > dmin + 2.0f * kSlack) {
                 if (lane == 0) R.gamma[id] = acos(gb < -1.0 ? -1.0 : gb);
             } else {
-                need = true;
+                gamma_scan<3>(R, id, lane);
             }
         }
-        if (need && lane == 0) R.gtot[1] = 1;
     }
     // b: the best covering vector among the cells within kNear
     float best = INFINITY;
@@ -882,7 +911,7 @@ __device__ __forceinline__ void assoc_line_body(const RunView &R, int64_t bx)
     int64_t bj = R.K;
     double u;
     const int c = line_cell_of(f0, f1, r, G, u);
-    bool full = c < 0 || R.gtot[2] != 0;
+    bool full = c < 0 || R.gtot[1] != 0;
     if (!full) {
         const double4 *rec = reinterpret_cast<const double4 *>(R.gvh);
         // scan one cell's vectors into (best, bj)
@@ -948,22 +977,19 @@ __device__ __forceinline__ void assoc_line_body(const RunView &R, int64_t bx)
 // of the association with the vector as the row, skipping itself and the
 // vectors exactly parallel to it (binary64 cosine 1 or more), as the full
 // gamma pass does; the largest cosine's angle (pi/2 without another
-// vector).  A vector outside the line or a walk past kLineWalk cells on a
-// side asks for the full gamma pass instead.
+// vector).  A vector outside the line, or with a walk past kLineWalk cells on a
+// side, is scanned against all vectors by the whole wavefront instead.
 __device__ __forceinline__ void line_gamma_body(const RunView &R, int64_t bx, int gate)
 {
     if (!gate && *R.vchanged == 0) return;
     const int64_t i = bx * 256 + threadIdx.x;
-    if (i >= R.K) return;
-    const double f0 = R.V[i * 2], f1 = R.V[i * 2 + 1], nrm = R.vn[i];
+    const bool in = i < R.K;
+    const double f0 = in ? R.V[i * 2] : 1.0, f1 = in ? R.V[i * 2 + 1] : 0.0, nrm = in ? R.vn[i] : 1.0;
     const int G = R.gG;
     const double *r = R.gr;
     double u;
     const int c = line_cell_of(f0, f1, r, G, u);
-    if (c < 0 || R.gtot[2] != 0) {
-        R.gtot[1] = 1;
-        return;
-    }
+    bool full = in && (c < 0 || R.gtot[1] != 0);
     const double4 *rec = reinterpret_cast<const double4 *>(R.gvh);
     double best = -INFINITY;
     auto scan = [&](int cc) {
@@ -978,34 +1004,35 @@ __device__ __forceinline__ void line_gamma_body(const RunView &R, int64_t bx, in
             best = fmax(best, cv);
         }
     };
-    scan(c);
+    const bool walk = in && !full;
+    if (walk) scan(c);
     int lo = c, hi = c, steps = 0;
-    bool full = false;
-    while (lo > 0 && !full) {
+    while (walk && lo > 0 && !full) {
         if (lo < c && line_bound(f0, f1, nrm, (double)lo / G + kLineEps, r) + kLineTau < best)
             break;
         scan(--lo);
         full = ++steps > kLineWalk;
     }
     steps = 0;
-    while (hi < G - 1 && !full) {
+    while (walk && hi < G - 1 && !full) {
         if (hi > c && line_bound(f0, f1, nrm, (double)(hi + 1) / G - kLineEps, r) + kLineTau < best)
             break;
         scan(++hi);
         full = ++steps > kLineWalk;
     }
-    if (full) {
-        R.gtot[1] = 1;
-        return;
-    }
-    R.gamma[i] = best > -INFINITY ? acos(best < -1.0 ? -1.0 : best) : 1.5707963267948966;
+    // the wavefront's lanes again together: the vectors left, one by one
+    const int lane = threadIdx.x & 63;
+    for (unsigned long long b = __ballot(full); b; b &= b - 1)
+        gamma_scan<2>(R, (int32_t)(i - lane + __ffsll(b) - 1), lane);
+    if (in && !full) R.gamma[i] = best > -INFINITY ? acos(best < -1.0 ? -1.0 : best) : 1.5707963267948966;
 }
 
 // ------------------------------------------------------------- kernels
-__global__ __launch_bounds__(256) void k_grid_bucket(RunView R, int gate)
+__global__ __launch_bounds__(256) void k_grid_clear(RunView R)
 {
-    grid_bucket_body(R, blockIdx.x, gate);
+    clear_counts(R, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
 }
+__global__ __launch_bounds__(256) void k_grid_bucket(RunView R) { grid_bucket_body(R, blockIdx.x); }
 __global__ __launch_bounds__(256) void k_grid_ranges(RunView R, int gate)
 {
     grid_ranges_body(R, blockIdx.x, gate);
@@ -1061,33 +1088,31 @@ __global__ __launch_bounds__(256) void kb_line_gamma(const RunView *runs, const 
 }
 
 // ------------------------------------------------------------- launchers
-hipError_t launch_grid_build(const RunView &R, hipStream_t s, int force)
+static hipError_t launch_grid_rest(const RunView &R, hipStream_t s, int gate)
+{
+    const unsigned vb = (unsigned)((R.K + 255) / 256);
+    if (R.m == 3) {
+        k_grid_cells<<<(unsigned)grid_live_cells(R.gG), 64, 0, s>>>(R, gate);
+    } else {
+        k_grid_ranges<<<(unsigned)((R.gG + 255) / 256), 256, 0, s>>>(R, gate);
+        k_grid_fill<<<vb, 256, 0, s>>>(R, gate);
+        k_line_gamma<<<vb, 256, 0, s>>>(R, gate);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_grid_build(const RunView &R, hipStream_t s)
 {
     if (R.gG <= 0) return hipSuccess;
     const unsigned vb = (unsigned)((R.K + 255) / 256);
-    const int64_t cells = index_cells(R.m, R.gG);
-    k_grid_bucket<<<vb, 256, 0, s>>>(R, force);
-    k_grid_ranges<<<(unsigned)((cells + 255) / 256), 256, 0, s>>>(R, force);
-    k_grid_fill<<<vb, 256, 0, s>>>(R, force);
-    if (R.m == 3)
-        k_grid_cells<<<(unsigned)grid_live_cells(R.gG), 64, 0, s>>>(R, force);
-    else
-        k_line_gamma<<<vb, 256, 0, s>>>(R, force);
-    return hipGetLastError();
+    if (R.m == 3) k_grid_clear<<<vb, 256, 0, s>>>(R);
+    k_grid_bucket<<<vb, 256, 0, s>>>(R);
+    return launch_grid_rest(R, s, 1);
 }
 
 hipError_t launch_grid_rebuild(const RunView &R, hipStream_t s)
 {
-    if (R.gG <= 0) return hipSuccess;
-    const unsigned vb = (unsigned)((R.K + 255) / 256);
-    const int64_t cells = index_cells(R.m, R.gG);
-    k_grid_ranges<<<(unsigned)((cells + 255) / 256), 256, 0, s>>>(R, 0);
-    k_grid_fill<<<vb, 256, 0, s>>>(R, 0);
-    if (R.m == 3)
-        k_grid_cells<<<(unsigned)grid_live_cells(R.gG), 64, 0, s>>>(R, 0);
-    else
-        k_line_gamma<<<vb, 256, 0, s>>>(R, 0);
-    return hipGetLastError();
+    return R.gG <= 0 ? hipSuccess : launch_grid_rest(R, s, 0);
 }
 
 hipError_t launch_assoc_grid(const RunView &R, hipStream_t s)
@@ -1131,8 +1156,8 @@ int64_t grid_phase_blocks(int phase, const RunView &R)
     const int64_t cells = index_cells(R.m, R.gG);
     switch (phase) {
     case BP_ASSOC: return ((R.m == 3 ? R.M * kGridRowLanes : R.M) + 255) / 256;
-    case BP_GRID_FILL: return (R.K + 255) / 256;
-    case BP_GRID_RANGES: return (cells + 255) / 256;
+    case BP_GRID_FILL: return R.m == 3 ? 0 : (R.K + 255) / 256;
+    case BP_GRID_RANGES: return R.m == 3 ? 0 : (cells + 255) / 256;
     case BP_GRID_CELLS: return R.m == 3 ? grid_live_cells(R.gG) : (R.K + 255) / 256;
     }
     return 0;

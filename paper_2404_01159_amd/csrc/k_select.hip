@@ -84,9 +84,8 @@ __device__ __forceinline__ float dotf(const float *f, const float4 *v)
 template <int MD, int RR, bool GAMMA>
 __device__ __forceinline__ void assoc_body(const RunView &R, int64_t bx, int c, int gate)
 {
-    // gamma pass, uniform exits: gate 1 always runs; gate 0 runs when the
-    // vectors changed; gate 2 also needs the index to have asked for it
-    if (GAMMA && gate != 1 && (*R.vchanged == 0 || (gate == 2 && R.gtot[1] == 0))) return;
+    // gamma pass, uniform exit: gate 1 always runs, gate 0 when the vectors changed
+    if (GAMMA && gate != 1 && *R.vchanged == 0) return;
     constexpr int NV4 = MD <= 4 ? 1 : 2;  // float4 per vector
     __shared__ float4 sv[1024 * NV4];
     const int64_t j0 = (int64_t)c * R.CS;
@@ -256,9 +255,8 @@ __device__ __forceinline__ void rerank_body(const RunView &R, int64_t bx, int ga
 {
     constexpr int kLanes = 64 / kRows;  // lanes per row in phase 1
     constexpr int kWaveItems = 12 * kRows < kItems ? kItems : 12 * kRows;  // tiles per wave
-    // gamma pass, uniform exits: gate 1 always runs; gate 0 runs when the
-    // vectors changed; gate 2 also needs the index to have asked for it
-    if (GAMMA && gate != 1 && (*R.vchanged == 0 || (gate == 2 && R.gtot[1] == 0))) return;
+    // gamma pass, uniform exit: gate 1 always runs, gate 0 when the vectors changed
+    if (GAMMA && gate != 1 && *R.vchanged == 0) return;
     __shared__ double s_f[kRows][MD];
     __shared__ double s_nrm[kRows];
     __shared__ int s_state[kRows];  // 0 inactive, 1 items, 2 zero row, 3 full scan
@@ -778,6 +776,7 @@ __device__ __forceinline__ void turn_body(const RunView &R, int64_t bx)
         }
     }
     const bool ext = g % R.period == 0;  // an adaptation follows: extremes needed
+    if (ext) clear_counts(R, bx * kTurnBlock + threadIdx.x, nb * kTurnBlock);
     if (slots) {
 #pragma unroll
         for (int k = 0; k < kMaxM; ++k) {
@@ -885,6 +884,7 @@ __device__ __forceinline__ void newpop_body(const RunView &R, int64_t bx)
     // generation (g a multiple of the period): other generations skip the
     // reductions (uniform branch)
     const bool ext = g % R.period == 0;
+    if (ext) clear_counts(R, j, (R.K + 255) / 256 * 256);
 #pragma unroll
     for (int k = 0; k < kMaxM; ++k) {
         if (k >= R.m) break;
@@ -948,15 +948,14 @@ __global__ __launch_bounds__(256) void kb_assoc(const RunView *runs, const Span 
     const int64_t local = blockIdx.x - sp[s].start;
     const int64_t nbx = sp[s].nbx;
     const RunView &R = runs[sp[s].run];
-    // an indexed run's gamma pass also needs its index build to have asked
-    assoc_body<MD, RR, GAMMA>(R, local % nbx, (int)(local / nbx), R.gG > 0 ? 2 : 0);
+    assoc_body<MD, RR, GAMMA>(R, local % nbx, (int)(local / nbx), 0);
 }
 template <int MD, bool GAMMA>
 __global__ __launch_bounds__(64) void kb_rerank(const RunView *runs, const Span *sp, int n)
 {
     const int s = find_span(sp, n, blockIdx.x);
     const RunView &R = runs[sp[s].run];
-    rerank_body<MD, GAMMA, kBatchRows>(R, blockIdx.x - sp[s].start, R.gG > 0 ? 2 : 0);
+    rerank_body<MD, GAMMA, kBatchRows>(R, blockIdx.x - sp[s].start, 0);
 }
 // the batched gamma passes, U blocks per workgroup (U = kSkipBlocks when
 // the launch has blocks enough to fill the device U times over: most

@@ -120,25 +120,22 @@ __device__ __forceinline__ void adapt_v_body(const RunView &R, int64_t bx, bool 
     write_aux(R, j, v);
     if (R.gG > 0) {
         // the index rebuild's first step for this vector: its cell under the
-        // new scaling (each thread forms the scaling as thread 0 stores it),
-        // counted (the counts start at zero: the last build cleared them)
+        // new scaling (each thread forms the scaling as thread 0 stores it);
+        // the counts start at zero (grid: cleared with the new population,
+        // line: by the last build)
         double gr[kMaxM];
         double mx = r[0];
         for (int k = 1; k < R.m; ++k) mx = fmax(mx, r[k]);
         for (int k = 0; k < R.m; ++k) gr[k] = fmax(r[k] / mx, 1e-6);
-        int c;
         if (R.m == 3) {
-            c = cell_of(v[0], v[1], v[2], gr, R.gG);
-            if (c < 0) c = 0;  // cannot happen for a nonzero vector >= 0
+            const int c = cell_of(v[0], v[1], v[2], gr, R.gG);
+            bucket_vector(R, j, c < 0 ? 0 : c, v, R.vn[j]);  // c < 0: not for a nonzero vector >= 0
         } else {
             double u;
-            c = line_cell_of(v[0], v[1], gr, R.gG, u);
-        }
-        R.gcell[j] = c;
-        if (c >= 0) atomicAdd(&R.gcnt[c], 1);
-        if (j == 0) {
-            R.gtot[1] = 0;  // as the bucket pass sets them
-            R.gtot[2] = 0;
+            const int c = line_cell_of(v[0], v[1], gr, R.gG, u);
+            R.gcell[j] = c;
+            if (c >= 0) atomicAdd(&R.gcnt[c], 1);
+            if (j == 0) R.gtot[1] = 0;  // as the bucket pass sets it
         }
     }
 }
@@ -200,6 +197,7 @@ int64_t batch_phase_nbx(int phase, const RunView &R)
 int64_t batch_phase_blocks(int phase, const RunView &R)
 {
     if (phase >= BP_GRID_RANGES && phase <= BP_GRID_CELLS) return grid_phase_blocks(phase, R);
+    if (batch_phase_gamma(phase) && R.gG > 0) return 0;  // the index build gives gamma
     if (phase == BP_ASSOC && R.gG > 0) return grid_phase_blocks(phase, R);
     if (phase == BP_RERANK && R.gG > 0) return 0;  // the indexed association ranks in full
     switch (phase) {
@@ -239,15 +237,8 @@ hipError_t launch_adapt(const RunView &R, hipStream_t s)
     k_adapt_v<<<blocks(R.K, 256), 256, 0, s>>>(R);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // with the index, its build computes gamma where it can prove the nearest
-    // vector is among a vector's neighbours, and the full pass runs only when
-    // some vector is left
-    if (R.gG > 0) {
-        e = launch_grid_rebuild(R, s);  // the adaptation counted the vectors
-        if (e != hipSuccess) return e;
-        return launch_gamma(R, s, 2);
-    }
-    return launch_gamma(R, s, 0);
+    // with the index, its build gives gamma too
+    return R.gG > 0 ? launch_grid_rebuild(R, s) : launch_gamma(R, s, 0);
 }
 
 }  // namespace rvea

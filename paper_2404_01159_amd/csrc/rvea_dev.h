@@ -68,17 +68,15 @@ struct RunView {
     int64_t gcap;       // list records: a slot of equal size per cell (grid only)
     double *gr;         // m: the scaling r the cells' coordinates divide by
     int32_t *gcell;     // K: cell of each vector (-1: outside the line)
-    int32_t *gcnt;      // cells: vectors per cell, then fill cursors (build)
-    int32_t *gstart;    // cells: first position of each cell's vectors
-    int32_t *gnum;      // cells: vectors of each cell
-    int32_t *gvec;      // K: vector ids by cell
-    double *gvh;        // K x 4: by cell, their unit directions (grid) or
-                        // (v, |v|) (line)
+    int32_t *gcnt;      // cells: vectors per cell (line: then fill cursors)
+    int32_t *gstart;    // cells: first position of each cell's vectors (line only)
+    int32_t *gnum;      // cells: vectors of each cell (line only)
+    int32_t *gvec;      // vector ids by cell: kBucket places per cell (grid), K (line)
+    double *gvh;        // x 4: by cell, their unit directions (grid) or (v, |v|) (line)
     int32_t *lcnt;      // cells: candidate-list length (-1: full scan; grid only)
-    unsigned long long *gtot;  // 4: the allocator of the cells' vector ranges (build),
-                               // 1 when the build left some vector's gamma,
-                               // 1 when some vector is outside the
-                               // line (every row then scans all vectors), spare
+    unsigned long long *gtot;  // line only: the allocator of the cells' vector
+                               // ranges (build), 1 when some vector is outside
+                               // the line (every row then scans all vectors)
     double *lrec;       // gcap x 4: (v, |v|) of the list entries
     int32_t *lidx;      // gcap: vector id of each record
     int32_t *vs;        // K x 2: valid slots, ascending, each with its physical row
@@ -206,11 +204,16 @@ __device__ __forceinline__ void span_blocks(const RunView *runs, const Span *sp,
     }
 }
 
-// the gamma pass of a run runs after its vectors changed, and, with an
-// index, only when the index build left some vector's gamma
-__device__ __forceinline__ bool gamma_open(const RunView &R)
+// the gamma pass of a run (one without an index: its build gives gamma) runs
+// after its vectors changed
+__device__ __forceinline__ bool gamma_open(const RunView &R) { return *R.vchanged != 0; }
+
+// Before an adaptation: the grid's counts cleared, for the vectors that it will
+// put into their cells (the threads of the kernel that writes the new population).
+__device__ __forceinline__ void clear_counts(const RunView &R, int64_t tid, int64_t threads)
 {
-    return *R.vchanged != 0 && (R.gG == 0 || R.gtot[1] != 0);
+    if (R.m != 3 || R.gG == 0) return;
+    for (int64_t c = tid; c < (int64_t)R.gG * R.gG; c += threads) R.gcnt[c] = 0;
 }
 
 // ---------------------------------------------------------------- Philox

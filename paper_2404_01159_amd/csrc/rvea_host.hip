@@ -13,6 +13,7 @@
 
 #include "rvea.h"
 #include "rvea_dev.h"
+#include "rvea_index.h"
 #include "rvea_internal.h"
 #include "rvea_transfer.h"
 
@@ -118,6 +119,7 @@ void make_layout(int problem, int m, int d, int64_t N, int64_t K, int op, Layout
     // line of G = K cells, no lists
     L.gG = grid_side(m, K);
     const size_t cells = (size_t)index_cells(m, L.gG);
+    const size_t places = m == 3 ? cells * kBucket : (size_t)K;  // of the vectors, by cell
     L.gcap = m == 3 ? (int64_t)grid_slot() * (int64_t)cells : 0;
     const size_t sz[] = {
         (size_t)(K + N) * L.ld * 4, (size_t)2 * K * 4,
@@ -131,8 +133,8 @@ void make_layout(int problem, int m, int d, int64_t N, int64_t K, int op, Layout
         problem == kPolicy ? (size_t)kLqFloats * 4 : 0,
         L.osplit > 1 ? (size_t)P * L.osplit * 2 * 8 : 8,
         swarm(op) ? (size_t)(K + N) * L.ld * 4 : 8,
-        (size_t)m * 8, (size_t)K * 4, cells * 4, cells * 4, cells * 4, (size_t)K * 4,
-        (size_t)K * 32, cells * 4, 32, (size_t)L.gcap * 32, (size_t)L.gcap * 4};
+        (size_t)m * 8, (size_t)K * 4, cells * 4, m == 3 ? 0 : cells * 4, m == 3 ? 0 : cells * 4,
+        places * 4, places * 32, m == 3 ? cells * 4 : 0, 32, (size_t)L.gcap * 32, (size_t)L.gcap * 4};
     static_assert(sizeof(sz) / sizeof(sz[0]) == B_COUNT, "one size per buffer");
     size_t o = 0;
     for (int b = 0; b < B_COUNT; ++b) {
@@ -518,8 +520,8 @@ rvea_status create_run(int problem, int m, int d, int64_t N, int64_t K, uint64_t
         if (e == hipSuccess) e = hipMemsetAsync(R.gtot, 0, 32, r->stream);
     }
     if (e == hipSuccess) e = launch_lattice(R, r->stream, r->H);
-    if (e == hipSuccess) e = launch_gamma(R, r->stream, 1);
-    if (e == hipSuccess) e = launch_grid_build(R, r->stream, 1);
+    if (e == hipSuccess)  // the index's build gives gamma too
+        e = R.gG > 0 ? launch_grid_build(R, r->stream) : launch_gamma(R, r->stream, 1);
     if (e == hipSuccess) e = launch_init(R, r->stream);
     if (e != hipSuccess) {
         std::snprintf(g_create_err, sizeof g_create_err, "initialization: %s (%d)",
@@ -838,8 +840,8 @@ rvea_status rvea_set_state(rvea_run r, const float *X, const float *F, const uin
     const bool build = V && r->L.gG > 0;  // a host-set V: the index unscaled and rebuilt
     HIPCHK(r, launch_set_reset(R, r->stream, t, build ? 1 : 0));
     if (V) HIPCHK(r, launch_vec_aux(R, r->stream));
-    if (V && !gamma) HIPCHK(r, launch_gamma(R, r->stream, 1));
-    if (build && R.gG > 0) HIPCHK(r, launch_grid_build(R, r->stream, 1));
+    if (V && !gamma && R.gG == 0) HIPCHK(r, launch_gamma(R, r->stream, 1));
+    if (build && R.gG > 0) HIPCHK(r, launch_grid_build(R, r->stream));
     if (R.Vel) HIPCHK(r, hipMemsetAsync(R.Vel, 0, (size_t)(R.K + R.N) * R.ld * 4, r->stream));
     HIPCHK(r, launch_stamp(R, r->stream));
     if (R.turn) HIPCHK(r, launch_prepare(R, r->stream));
@@ -1006,7 +1008,7 @@ rvea_status rvea_set_index(rvea_run r, int enable)
     HIPCHK(r, hipStreamSynchronize(r->stream));
     r->R.gG = G;
     // V may have changed while the index was off
-    if (G > 0) HIPCHK(r, launch_grid_build(r->R, r->stream, 1));
+    if (G > 0) HIPCHK(r, launch_grid_build(r->R, r->stream));
     drop_graphs(r);  // they hold the old launch sequence
     return RVEA_OK;
 }

@@ -7,6 +7,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "rvea_dev.h"
+
 namespace rvea {
 
 // cell of a direction x >= 0 (x != 0); q pulled onto the simplex if rounding
@@ -26,6 +28,26 @@ __device__ __forceinline__ int cell_of(double x0, double x1, double x2, const do
     ci = ci < 0 ? 0 : (ci > G - 1 ? G - 1 : ci);
     cj = cj < 0 ? 0 : (cj > G - 1 ? G - 1 : cj);
     return ci * G + cj;
+}
+
+// Vectors that a grid cell holds (two on average; a cell with more leaves the
+// cells around it to full scans).  Fixed places, cell c's from c * kBucket on,
+// let the pass that writes a vector put it there at once: with ranges sized to
+// the cells a rebuild needed two kernels more.
+constexpr int kBucket = 16;
+
+// Vector j = v (norm vn) into cell c of the grid: counted, and its id and unit
+// direction at the next place (counts start at zero).
+__device__ __forceinline__ void bucket_vector(const RunView &R, int64_t j, int c, const double *v,
+                                              double vn)
+{
+    R.gcell[j] = c;
+    const int k = atomicAdd(&R.gcnt[c], 1);
+    if (k >= kBucket) return;
+    const int64_t p = (int64_t)c * kBucket + k;
+    const double inv = 1.0 / vn;
+    R.gvec[p] = (int32_t)j;
+    reinterpret_cast<double4 *>(R.gvh)[p] = make_double4(v[0] * inv, v[1] * inv, v[2] * inv, 0.0);
 }
 
 // share u of a direction x on the scaled simplex and its cell; -1 unless

@@ -263,3 +263,44 @@ def test_index_crowded_vectors_fall_back_to_full_scans(P):
     assert stats["near_ties"] <= max(1, 1e-4 * stats["vectors"]), stats
     a.close()
     b.close()
+
+
+def gamma_brute(V):
+    """Eq. 5's gamma in binary64: the angle to the nearest vector not parallel."""
+    g = np.empty(len(V))
+    n = np.sqrt((V * V).sum(1))
+    for i in range(len(V)):
+        c = (V @ V[i]) / (n * n[i])
+        c[i] = -2.0
+        c[c >= 1.0] = -2.0
+        g[i] = np.arccos(np.clip(c.max(), -1, 1)) if c.max() > -2.0 else np.pi / 2
+    return g
+
+
+# vectors in one cell of the index: as many as its places, one more, far more
+# (the cells around it scan all vectors, and so do its vectors for gamma)
+@pytest.mark.parametrize("m,H", [(3, 30), (2, 495)])
+@pytest.mark.parametrize("crowd", [15, 16, 17, 90])
+def test_crowded_cell(P, m, H, crowd):
+    K = (H + 1) * (H + 2) // 2 if m == 3 else H + 1
+    runs = []
+    for on in (True, False):
+        run = P.Run(1, m, 20, K, K, seed=11)
+        run.set_index(on)
+        st = run.get_state()
+        V = st["V"].copy()
+        r = np.random.default_rng(crowd)
+        V[:crowd] = V[K // 2] + 1e-4 * r.random((crowd, m))
+        V /= np.linalg.norm(V, axis=1)[:, None]
+        run.set_state(st["X"], st["F"], st["valid"], V)
+        run.run(3)
+        runs.append((run.get_state(), run.get_selection(), V))
+        run.close()
+    (a, sa, V), (b, sb, _) = runs
+    for k in ("F", "valid", "gamma", "X"):
+        assert np.array_equal(a[k], b[k], equal_nan=True), k
+    for k in ("assoc", "apd", "surv"):
+        assert np.array_equal(sa[k], sb[k]), k
+    # acos near 1 turns the cosine's rounding (2^-52) into sqrt(2 * 2^-52)/angle
+    want = gamma_brute(V)
+    assert np.all(np.abs(a["gamma"] - want) <= 4 * 2.0 ** -52 / np.maximum(want, 1e-8))
