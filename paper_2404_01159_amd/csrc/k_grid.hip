@@ -24,20 +24,19 @@
 //   b      an upper bound of the distance from any point of C to its nearest
 //          vector: min over the vectors k of the cells around C of the largest
 //          distance from a vertex to v_k (again attained at a vertex)
-//   box    the smallest square of cells around C whose boundary (clipped to
-//          the simplex) is farther than b + rho from u_c: that ball around
+//   box    the (2 kStage + 1)^2 cells around C: its boundary (clipped to the
+//          simplex) must be farther than b + rho from u_c: that ball around
 //          u_c is convex in q, so it lies inside the box
-//   P      the vectors in the box whose distance to the cell is at most b
-//          (the least over its edges, each the distance to a great-circle
-//          arc; the cell's own vectors always): any vector that is the
-//          nearest for some row direction in C is within b of it
-//   list   P without the vectors that a champion (the vector of largest
-//          cosine at a vertex or at u_c) beats at every vertex by more than
-//          1e-12: the cosine difference is linear on the cone, so such a
-//          vector loses to the champion for every row direction in C, with
-//          a margin far above binary64 rounding
-// Lists longer than kSlot, cells whose box would pass kStage cells from
-// C, cells with no vector within kNear cells and cells near one with more
+//   P      the vectors within b + rho of u_c: a vector that is the nearest
+//          for some row direction in C is within b of it, so it is among them
+//   list   P without the vectors that a champion (a vector near a vertex or
+//          u_c) beats at every vertex by more than 1e-12: the cosine
+//          difference is linear on the cone, so such a vector loses to the
+//          champion for every row direction in C, with a margin far above
+//          binary64 rounding (any vector may serve as a champion, so they are
+//          found from binary32 chords)
+// Lists longer than kSlot, cells whose ball passes the box, cells with no
+// vector in the box and cells near one with more
 // vectors than its kBucket places are marked for a full scan (correct for any
 // vector set, counted as full rescans).  The same pass gives Eq. 5's gamma of
 // the cell's vectors: from the staged neighbourhood where that provably holds
@@ -86,7 +85,6 @@ __device__ __forceinline__ double dot3(const D3 &a, const D3 &b)
 {
     return a.x * b.x + a.y * b.y + a.z * b.z;
 }
-__device__ __forceinline__ D3 sub3(const D3 &a, const D3 &b) { return d3(a.x - b.x, a.y - b.y, a.z - b.z); }
 __device__ __forceinline__ D3 unit3(const D3 &a)
 {
     const double inv = 1.0 / sqrt(dot3(a, a));
@@ -165,17 +163,13 @@ __device__ __forceinline__ D3 lift(double q1, double q2, const double *r)
 // [a, a+h] x [b, b+h] clipped to q1 + q2 <= 1 as five vertices in order
 // (with corner sums s0 <= s1 = s3 <= s2: the whole square when s2 <= 1, a
 // pentagon when only the far corner is cut, a triangle (or a point) when
-// s1 > 1; fewer distinct vertices repeat the last, which adds only
-// zero-length edges), their unit directions in binary64 (champions and
-// domination) and binary32 (the geometric tests), the unit normals of the
-// edges' planes, u_c and rho.
+// s1 > 1; fewer distinct vertices repeat the last) and their mean u_c after
+// them: unit directions in binary64 (domination) and binary32 (the geometric
+// tests), and rho.
 constexpr int kNv = 5;
 struct CellGeo {
-    double X[kNv][3];
-    float Xf[kNv][3], Nf[kNv][3];
-    int nok[kNv];
-    double uc[3];
-    float ucf[3];
+    double X[kNv + 1][3];
+    float Xf[kNv + 1][3];
     float rho;
 };
 
@@ -207,8 +201,8 @@ __device__ __forceinline__ void cell_vertex(int G, int c, int v, double &px, dou
 }
 
 // the geometry of a live cell, by the workgroup: lanes 0..4 the vertices,
-// lane 5 u_c; then lanes 0..4 the edge normals and rho (g.rho as the bits
-// of a non-negative float, combined by an LDS max)
+// lane 5 u_c; then lanes 0..4 rho (as the bits of a non-negative float,
+// combined by an LDS max)
 __device__ void cell_geo(const RunView &R, int c, CellGeo &g, int lane)
 {
     if (lane <= kNv) {
@@ -227,77 +221,19 @@ __device__ void cell_geo(const RunView &R, int c, CellGeo &g, int lane)
         }
         const D3 X = unit3(lift(px, py, R.gr));
         const F3 Xf = f3of(X);
-        double *dst = lane < kNv ? g.X[lane] : g.uc;
-        float *dsf = lane < kNv ? g.Xf[lane] : g.ucf;
-        dst[0] = X.x;
-        dst[1] = X.y;
-        dst[2] = X.z;
-        dsf[0] = Xf.x;
-        dsf[1] = Xf.y;
-        dsf[2] = Xf.z;
+        g.X[lane][0] = X.x;
+        g.X[lane][1] = X.y;
+        g.X[lane][2] = X.z;
+        g.Xf[lane][0] = Xf.x;
+        g.Xf[lane][1] = Xf.y;
+        g.Xf[lane][2] = Xf.z;
     }
     if (lane == 0) g.rho = 0.0f;
     __syncthreads();
-    if (lane < kNv) {
-        const F3 p = ld3(g.Xf[lane]), q = ld3(g.Xf[(lane + 1) % kNv]);
-        const F3 n = fcross(p, q);
-        const float nn = fsqrt(fdot(n, n));
-        g.nok[lane] = nn > 1e-30f;
-        const float inv = g.nok[lane] ? __builtin_amdgcn_rcpf(nn) : 0.0f;
-        g.Nf[lane][0] = n.x * inv;
-        g.Nf[lane][1] = n.y * inv;
-        g.Nf[lane][2] = n.z * inv;
+    if (lane < kNv)
         atomicMax(reinterpret_cast<unsigned int *>(&g.rho),
-                  __float_as_uint(fchord(ld3(g.ucf), p)));
-    }
+                  __float_as_uint(fchord(ld3(g.Xf[kNv]), ld3(g.Xf[lane]))));
     __syncthreads();
-}
-
-// least distance from unit v to the cell (v outside it: the least over the
-// polygon's edges, each an arc of a great circle)
-__device__ float cell_dist(const CellGeo &g, const F3 &v)
-{
-    float d = INFINITY;
-    for (int e = 0; e < kNv; ++e)
-        d = fminf(d, farc_chord(v, ld3(g.Xf[e]), ld3(g.Xf[(e + 1) % kNv]), ld3(g.Nf[e]),
-                                g.nok[e] != 0));
-    return d;
-}
-
-__device__ __forceinline__ D3 gvh_at(const RunView &R, int64_t p)
-{
-    const double4 v = reinterpret_cast<const double4 *>(R.gvh)[p];
-    return d3(v.x, v.y, v.z);
-}
-
-// a vector of the box belongs to P (cell c's own vectors always do); b
-// already holds its slack
-__device__ __forceinline__ bool in_p(const CellGeo &g, const D3 &v, bool own, float b)
-{
-    if (own) return true;
-    const F3 vf = f3of(v);
-    // a lower bound of the distance first
-    if (fchord(ld3(g.ucf), vf) - g.rho - 2.0f * kSlack > b) return false;
-    return cell_dist(g, vf) - kSlack <= b;
-}
-
-// the champions of a cell (LDS): unit directions and vector ids (-1: none)
-struct Champs {
-    double v[kChamps][3];
-    int32_t j[kChamps];
-};
-
-// some champion beats v at every vertex by more than the margin
-__device__ __forceinline__ bool dominated(const CellGeo &g, const Champs &ch, const D3 &v, int32_t j)
-{
-    for (int d = 0; d < kChamps; ++d) {
-        if (ch.j[d] < 0 || ch.j[d] == j) continue;
-        const D3 w = sub3(ld3(ch.v[d]), v);
-        bool all = true;
-        for (int e = 0; e < kNv; ++e) all = all && dot3(ld3(g.X[e]), w) > kDomMargin;
-        if (all) return true;
-    }
-    return false;
 }
 
 // first position of a range of n items allocated by the whole wavefront
@@ -412,47 +348,6 @@ __device__ __forceinline__ double wave_fmin(double v)
                                       __builtin_amdgcn_readlane(__double2loint(v), 32));
     return fmin(a, b);
 }
-__device__ __forceinline__ int wave_imin(int v)
-{
-    v = min(v, partner32<0>(v));
-    v = min(v, partner32<1>(v));
-    v = min(v, partner32<2>(v));
-    v = min(v, partner32<3>(v));
-    v = min(v, partner32<4>(v));
-    RVEA_ASSERT_FULL_WAVE();
-    return min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 32));
-}
-template <int L>
-__device__ __forceinline__ void best_step(double &v, int32_t &j, int32_t &p)
-{
-    const double ov = partner32<L>(v);
-    const int32_t oj = partner32<L>((int)j), op = partner32<L>((int)p);
-    if (ov > v || (ov == v && oj < j)) {
-        v = ov;
-        j = oj;
-        p = op;
-    }
-}
-__device__ __forceinline__ void wave_best(double &v, int32_t &j, int32_t &p)
-{
-    best_step<0>(v, j, p);
-    best_step<1>(v, j, p);
-    best_step<2>(v, j, p);
-    best_step<3>(v, j, p);
-    best_step<4>(v, j, p);
-    RVEA_ASSERT_FULL_WAVE();
-    const double v0 = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 0),
-                                       __builtin_amdgcn_readlane(__double2loint(v), 0));
-    const double v1 = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 32),
-                                       __builtin_amdgcn_readlane(__double2loint(v), 32));
-    const int32_t j0 = __builtin_amdgcn_readlane(j, 0), j1 = __builtin_amdgcn_readlane(j, 32);
-    const int32_t p0 = __builtin_amdgcn_readlane(p, 0), p1 = __builtin_amdgcn_readlane(p, 32);
-    const bool second = v1 > v0 || (v1 == v0 && j1 < j0);
-    v = second ? v1 : v0;
-    j = second ? j1 : j0;
-    p = second ? p1 : p0;
-}
-
 template <int M>
 __device__ __attribute__((noinline)) void gamma_scan_call(const double *V, const double *vn,
                                                           double *gamma, int64_t K, int32_t id,
@@ -472,59 +367,36 @@ __device__ __attribute__((noinline)) void gamma_scan_call(const double *V, const
         gamma[id] = best > -INFINITY ? acos(best < -1.0 ? -1.0 : best) : 1.5707963267948966;
 }
 
-constexpr int kNear = 3;  // the covering search looks at the (2 kNear + 1)^2 cells around
-
 // The vectors of the (2 kStage + 1)^2 cells around a cell, staged in LDS by
-// its workgroup: unit direction, id, raw vector and norm (the list record),
-// and the cell offset.  kStageCap entries at most.
+// its workgroup: the list record (v, |v|) and the id.  kStageCap entries at
+// most, kStageLane per lane.
 constexpr int kStage = 4;
 constexpr int kStageW = 2 * kStage + 1;
-constexpr int kStageCap = 192;
+constexpr int kStageLane = 3, kStageCap = 64 * kStageLane;
 struct Stage {
-    double vh[kStageCap][3];
-    double rec[kStageCap][4];
+    double4 rec[kStageCap];
     int32_t j[kStageCap];
-    int8_t di[kStageCap], dj[kStageCap];
-    int n;
 };
 
-// least distance from unit u to the boundary of the box of cells of radius
-// k around (ci, cj), clipped to the simplex (sides on the grid's edge, where
-// the simplex ends, do not count): the sides are exact grid lines in
+// distance from unit u to side `side` (0..3) of the box of cells of radius
+// kStage around (ci, cj), clipped to the simplex; a side on the grid's edge,
+// where the simplex ends, does not count.  The sides are exact grid lines in
 // binary64 (their ends on the simplex's edge), lifted in binary32, so the
 // callers compare it with their slack
-__device__ float box_side_min(const RunView &R, int ci, int cj, int k, const F3 &u)
+__device__ float box_side(const RunView &R, int ci, int cj, int side, const F3 &u)
 {
     const int G = R.gG;
-    const int i0 = max(0, ci - k), i1 = min(G - 1, ci + k);
-    const int j0 = max(0, cj - k), j1 = min(G - 1, cj + k);
+    const int i0 = max(0, ci - kStage), i1 = min(G - 1, ci + kStage);
+    const int j0 = max(0, cj - kStage), j1 = min(G - 1, cj + kStage);
     const double h = 1.0 / G;
-    float lo = INFINITY;
-    if (i0 > 0) {
-        const double x = i0 * h, ya = j0 * h, yb = fmin((j1 + 1) * h, 1.0 - x);
-        if (yb >= ya)
-            lo = fminf(lo, farc_chord_of(u, flift((float)x, (float)ya, R.gr),
-                                         flift((float)x, (float)yb, R.gr)));
-    }
-    if (i1 < G - 1) {
-        const double x = (i1 + 1) * h, ya = j0 * h, yb = fmin((j1 + 1) * h, 1.0 - x);
-        if (yb >= ya)
-            lo = fminf(lo, farc_chord_of(u, flift((float)x, (float)ya, R.gr),
-                                         flift((float)x, (float)yb, R.gr)));
-    }
-    if (j0 > 0) {
-        const double y = j0 * h, xa = i0 * h, xb = fmin((i1 + 1) * h, 1.0 - y);
-        if (xb >= xa)
-            lo = fminf(lo, farc_chord_of(u, flift((float)xa, (float)y, R.gr),
-                                         flift((float)xb, (float)y, R.gr)));
-    }
-    if (j1 < G - 1) {
-        const double y = (j1 + 1) * h, xa = i0 * h, xb = fmin((i1 + 1) * h, 1.0 - y);
-        if (xb >= xa)
-            lo = fminf(lo, farc_chord_of(u, flift((float)xa, (float)y, R.gr),
-                                         flift((float)xb, (float)y, R.gr)));
-    }
-    return lo;
+    const bool first = side < 2, low = (side & 1) == 0;  // a line of q1 or q2; the lower one
+    const int line = low ? (first ? i0 : j0) : (first ? i1 + 1 : j1 + 1);
+    const double at = line * h, from = (first ? j0 : i0) * h;
+    const double to = fmin(((first ? j1 : i1) + 1) * h, 1.0 - at);
+    if (!(low ? line > 0 : line < G) || to < from) return INFINITY;
+    const F3 a = first ? flift((float)at, (float)from, R.gr) : flift((float)from, (float)at, R.gr);
+    const F3 b = first ? flift((float)at, (float)to, R.gr) : flift((float)to, (float)at, R.gr);
+    return farc_chord_of(u, a, b);
 }
 
 // The cells a row or a vector can land in: ci + cj <= G (cell_of clamps q
@@ -538,12 +410,16 @@ __device__ __forceinline__ int64_t tri_start(int G, int ci)
 static int64_t grid_live_cells(int G) { return (int64_t)G + (int64_t)G * (G + 1) / 2 - 1; }
 
 // One wavefront per cell (the simplex's cells only, in row order): the
-// neighbourhood staged in LDS; b from the cells within kNear; the box
-// radius (lane k tests radius k, at most kStage); the champions and the
-// list from the staged box vectors, written into the cell's slot at each
-// lane's prefix.
-// A neighbourhood over kStageCap vectors or with a cell over kBucket, or a box
-// over kStage marks the cell for a full scan.
+// neighbourhood staged in LDS; each lane's three entries in binary32 registers
+// with their squared chords to the five vertices and u_c, which serve b, P and
+// the champions; the list from P, written into the cell's slot at each lane's
+// prefix.
+// A neighbourhood over kStageCap vectors or with a cell over kBucket, or a ball
+// of radius b + rho that leaves it, marks the cell for a full scan.
+// Bound by vector instructions at four wavefronts per SIMD: with exact distances
+// to the cell's edges, the smallest of five boxes, binary64 champions and the
+// vertex products formed per (entry, champion), it took 56 us at 10,011 vectors
+// and 432 at 100,128; 26 and 162 so, with lists of the same length.
 __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, int gate)
 {
     if (!gate && *R.vchanged == 0) return;
@@ -558,7 +434,7 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
     const int cj = (int)(bx - tri_start(G, ci));
     const int c = ci * G + cj;
     __shared__ CellGeo g;
-    __shared__ Champs ch;
+    __shared__ double champ[kChamps][kNv];  // products of the champions and the vertices
     __shared__ Stage st;
     // stage: each lane's cells of the neighbourhood, their vector counts
     // scanned over the wave, then the vectors
@@ -576,7 +452,8 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
             }
         }
     }
-    const int own_cnt = __builtin_amdgcn_readlane(cnt[0], kStage * kStageW + kStage);
+    constexpr int own = kStage * kStageW + kStage;  // the centre cell's lane
+    const int own_cnt = __builtin_amdgcn_readlane(cnt[0], own);
     const bool crowded = __any(over);
     const int mine0 = crowded ? 0 : cnt[0] + cnt[1];
     const int incl0 = wave_incl_scan(mine0);
@@ -587,30 +464,33 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
         int q = incl0 - mine0;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const int t = lane + 64 * u;
             for (int k = 0; k < cnt[u]; ++k, ++q) {
                 const int p = from[u] + k;
-                const int32_t j = R.gvec[p];
-                const D3 v = gvh_at(R, p);
-                st.vh[q][0] = v.x;
-                st.vh[q][1] = v.y;
-                st.vh[q][2] = v.z;
-                st.j[q] = j;
-                st.di[q] = (int8_t)(t / kStageW - kStage);
-                st.dj[q] = (int8_t)(t % kStageW - kStage);
-                st.rec[q][0] = R.V[(int64_t)j * 3];
-                st.rec[q][1] = R.V[(int64_t)j * 3 + 1];
-                st.rec[q][2] = R.V[(int64_t)j * 3 + 2];
-                st.rec[q][3] = R.vn[j];
+                st.j[q] = R.gvec[p];
+                st.rec[q] = reinterpret_cast<const double4 *>(R.gvh)[p];
             }
         }
     }
     __syncthreads();
-    // the least distance from u_c to the boundary of the box of cells of
-    // radius k, on lane k <= kStage: for the box test below and, at radius
-    // kStage, for the own vectors' gamma
-    float bsm = INFINITY;
-    if (!full && lane <= kStage) bsm = box_side_min(R, ci, cj, lane, ld3(g.ucf));
+    const F3 uc = ld3(g.Xf[kNv]);
+    const float rho = g.rho;
+    // the least distance from u_c to the box's boundary, a side per lane
+    float bsm = lane < 4 && !full ? box_side(R, ci, cj, lane, uc) : INFINITY;
+    bsm = __uint_as_float(wave_min(__float_as_uint(bsm)));  // not negative: ordered as bits
+    // this lane's entries: unit directions, squared chords to the vertices and
+    // u_c (infinite without an entry)
+    F3 vf[kStageLane];
+    float c2[kStageLane][kNv + 1];
+#pragma unroll
+    for (int u = 0; u < kStageLane; ++u) {
+        const int q = lane + 64 * u;
+        const bool has = !full && q < nst;
+        const double4 r = st.rec[has ? q : 0];
+        const float inv = __builtin_amdgcn_rcpf((float)r.w);
+        vf[u] = f3((float)r.x * inv, (float)r.y * inv, (float)r.z * inv);
+#pragma unroll
+        for (int e = 0; e <= kNv; ++e) c2[u][e] = has ? fchord2(ld3(g.Xf[e]), vf[u]) : INFINITY;
+    }
     // Eq. 5's gamma of the cell's own vectors: the largest binary64 cosine
     // to another vector that is not parallel to it (cosine below 1, as the
     // full pass computes it), kept when the staged neighbourhood provably
@@ -629,108 +509,110 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
         }
     }
     {
-        const int own = kStage * kStageW + kStage;  // the centre cell's lane
         const int oq0 = __builtin_amdgcn_readlane(incl0 - mine0, own);
         const int on = full ? 0 : own_cnt;
-        const float lo =
-            __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bsm), kStage)) - g.rho -
-            kSlack;
+        const float lo = bsm - rho - kSlack;
+        double gmine = 0.0;  // own vector oq0 + lane: its largest cosine
+        bool gok = false;
         for (int o = oq0; o < oq0 + on; ++o) {  // uniform
-            const int32_t id = st.j[o];
-            const double vi[3] = {st.rec[o][0], st.rec[o][1], st.rec[o][2]};
-            const double vni = st.rec[o][3];
-            const F3 ui = f3(st.vh[o][0], st.vh[o][1], st.vh[o][2]);
+            const double4 v = st.rec[o];
+            const float inv = __builtin_amdgcn_rcpf((float)v.w);
+            const F3 ui = f3((float)v.x * inv, (float)v.y * inv, (float)v.z * inv);
             double gb = -INFINITY;
-            float dmin = INFINITY;
-            for (int q = lane; q < nst; q += 64) {
-                if (st.j[q] == id) continue;
-                double sd = vi[0] * st.rec[q][0];
-                sd = fma(vi[1], st.rec[q][1], sd);
-                sd = fma(vi[2], st.rec[q][2], sd);
-                const double cv = sd / (vni * st.rec[q][3]);
+            float dmin = INFINITY;  // squared
+#pragma unroll
+            for (int u = 0; u < kStageLane; ++u) {
+                const int q = lane + 64 * u;
+                if (q >= nst || q == o) continue;
+                const double4 w = st.rec[q];
+                double sd = v.x * w.x;
+                sd = fma(v.y, w.y, sd);
+                sd = fma(v.z, w.z, sd);
+                const double cv = sd / (v.w * w.w);
                 if (cv >= 1.0) continue;
                 gb = fmax(gb, cv);
-                dmin = fminf(dmin, fchord2(ui, f3(st.vh[q][0], st.vh[q][1], st.vh[q][2])));
+                dmin = fminf(dmin, fchord2(ui, vf[u]));
             }
             gb = -wave_fmin(-gb);
-            dmin = fsqrt((float)wave_fmin((double)dmin));  // the squared minimum's root
-            if (dmin < INFINITY && lo > dmin + 2.0f * kSlack) {
-                if (lane == 0) R.gamma[id] = acos(gb < -1.0 ? -1.0 : gb);
-            } else {
-                gamma_scan<3>(R, id, lane);
+            dmin = fsqrt(__uint_as_float(wave_min(__float_as_uint(dmin))));
+            const bool ok = dmin < INFINITY && lo > dmin + 2.0f * kSlack;
+            if (!ok) gamma_scan<3>(R, st.j[o], lane);
+            if (lane == o - oq0) {
+                gmine = gb;
+                gok = ok;
             }
         }
+        if (gok) R.gamma[st.j[oq0 + lane]] = acos(gmine < -1.0 ? -1.0 : gmine);
     }
-    // b: the best covering vector among the cells within kNear
-    float best = INFINITY;
-    if (!full) {
-        for (int q = lane; q < nst; q += 64) {
-            if (abs(st.di[q]) > kNear || abs(st.dj[q]) > kNear) continue;
-            const F3 v = f3(st.vh[q][0], st.vh[q][1], st.vh[q][2]);
-            float cov = 0.0f;
-            for (int e = 0; e < kNv; ++e) cov = fmaxf(cov, fchord2(ld3(g.Xf[e]), v));
-            best = fminf(best, cov);  // squared
-        }
-    }
-    best = fsqrt((float)wave_fmin((double)best));
-    full = full || !(best < INFINITY);
-    const float b = best + kSlack;
-    int kc = 0x7fffffff;
-    if (!full) {  // lane k: does the box of radius k hold the ball of radius b + rho?
-        const int k = lane;
-        const bool ok = k <= kStage && bsm > b + g.rho + 2.0f * kSlack;
-        kc = wave_imin(ok ? k : 0x7fffffff);
-        full = kc == 0x7fffffff;
-    }
-    if (!full) {
-        // members of P among this lane's staged entries (q = lane + 64 u),
-        // and the champions: largest cosine at each vertex and at u_c
-        uint32_t mem = 0;
-        double bv[kChamps];
-        int32_t bj[kChamps], bq[kChamps];
+    // b: the vector that covers the cell best
+    float cover = INFINITY;
 #pragma unroll
-        for (int d = 0; d < kChamps; ++d) {
-            bv[d] = -INFINITY;
-            bj[d] = 0x7fffffff;
-            bq[d] = -1;
-        }
-        for (int u = 0; lane + 64 * u < nst; ++u) {
-            const int q = lane + 64 * u;
-            if (abs(st.di[q]) > kc || abs(st.dj[q]) > kc) continue;
-            const D3 v = ld3(st.vh[q]);
-            if (!in_p(g, v, st.di[q] == 0 && st.dj[q] == 0, b)) continue;
-            mem |= 1u << u;
-            const int32_t j = st.j[q];
+    for (int u = 0; u < kStageLane; ++u) {
+        float far = c2[u][0];
+#pragma unroll
+        for (int e = 1; e < kNv; ++e) far = fmaxf(far, c2[u][e]);
+        cover = fminf(cover, far);
+    }
+    cover = fsqrt(__uint_as_float(wave_min(__float_as_uint(cover))));
+    const float ball = cover + kSlack + rho + 2.0f * kSlack;  // b + rho and the comparisons' slack
+    full = full || !(cover < INFINITY) || !(bsm > ball);
+    if (!full) {
+        // P, and the champions: for each vertex and u_c the entry of P with the
+        // least squared chord, its last 8 bits replaced by the entry's number
+        const float lim = ball * ball * 1.000002f;
+        uint32_t key[kChamps];
+#pragma unroll
+        for (int d = 0; d < kChamps; ++d) key[d] = 0xffffffffu;
+#pragma unroll
+        for (int u = 0; u < kStageLane; ++u) {
+            const bool in = c2[u][kNv] <= lim;
 #pragma unroll
             for (int d = 0; d < kChamps; ++d) {
-                const double cv = dot3(d < kNv ? ld3(g.X[d]) : ld3(g.uc), v);
-                if (cv > bv[d] || (cv == bv[d] && j < bj[d])) {
-                    bv[d] = cv;
-                    bj[d] = j;
-                    bq[d] = q;
-                }
+                const uint32_t k = (__float_as_uint(c2[u][d]) & ~0xffu) | (uint32_t)(lane + 64 * u);
+                key[d] = in ? min(key[d], k) : key[d];
             }
         }
+        int mine_d = -1;  // the champion of this lane's (champion, vertex) pair
 #pragma unroll
-        for (int d = 0; d < kChamps; ++d) wave_best(bv[d], bj[d], bq[d]);
-        if (lane < kChamps) {
-            int32_t q = -1;
-#pragma unroll
-            for (int d = 0; d < kChamps; ++d) q = lane == d ? bq[d] : q;
-            ch.j[lane] = q < 0 ? -1 : st.j[q];
-            ch.v[lane][0] = q < 0 ? 0.0 : st.vh[q][0];
-            ch.v[lane][1] = q < 0 ? 0.0 : st.vh[q][1];
-            ch.v[lane][2] = q < 0 ? 0.0 : st.vh[q][2];
+        for (int d = 0; d < kChamps; ++d) {
+            const uint32_t k = wave_min(key[d]);
+            if (lane / kNv == d && k != 0xffffffffu) mine_d = (int)(k & 0xffu);
+        }
+        if (lane < kChamps * kNv) {
+            double p = -INFINITY;
+            if (mine_d >= 0) {
+                const double4 r = st.rec[mine_d];
+                const double inv = 1.0 / r.w;
+                p = dot3(ld3(g.X[lane % kNv]), d3(r.x * inv, r.y * inv, r.z * inv));
+            }
+            champ[lane / kNv][lane % kNv] = p;
         }
         __syncthreads();
-        // the list: members no champion beats on the whole cell
+        // the list: members that no champion beats at every vertex (a champion
+        // does not beat itself)
         uint32_t keep = 0;
         int mine = 0;
-        for (int u = 0; lane + 64 * u < nst; ++u) {
-            const int q = lane + 64 * u;
-            if (((mem >> u) & 1u) && !dominated(g, ch, ld3(st.vh[q]), st.j[q])) {
-                keep |= 1u << u;
-                ++mine;
+#pragma unroll
+        for (int u = 0; u < kStageLane; ++u) {
+            if (c2[u][kNv] <= lim) {
+                const double4 r = st.rec[lane + 64 * u];
+                const double inv = 1.0 / r.w;
+                const D3 v = d3(r.x * inv, r.y * inv, r.z * inv);
+                double x[kNv];
+#pragma unroll
+                for (int e = 0; e < kNv; ++e) x[e] = dot3(ld3(g.X[e]), v) + kDomMargin;
+                bool beaten = false;
+#pragma unroll
+                for (int d = 0; d < kChamps; ++d) {
+                    bool all = true;
+#pragma unroll
+                    for (int e = 0; e < kNv; ++e) all = all && champ[d][e] > x[e];
+                    beaten = beaten || all;
+                }
+                if (!beaten) {
+                    keep |= 1u << u;
+                    ++mine;
+                }
             }
         }
         const int incl = wave_incl_scan(mine);
@@ -740,11 +622,11 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
         const int64_t base = (int64_t)c * kSlot;
         if (!full) {
             int64_t o = base + incl - mine;
-            for (int u = 0; lane + 64 * u < nst; ++u) {
+#pragma unroll
+            for (int u = 0; u < kStageLane; ++u) {
                 if (!((keep >> u) & 1u)) continue;
                 const int q = lane + 64 * u;
-                reinterpret_cast<double4 *>(R.lrec)[o] =
-                    make_double4(st.rec[q][0], st.rec[q][1], st.rec[q][2], st.rec[q][3]);
+                reinterpret_cast<double4 *>(R.lrec)[o] = st.rec[q];
                 R.lidx[o] = st.j[q];
                 ++o;
             }

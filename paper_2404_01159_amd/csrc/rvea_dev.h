@@ -72,7 +72,7 @@ struct RunView {
     int32_t *gstart;    // cells: first position of each cell's vectors (line only)
     int32_t *gnum;      // cells: vectors of each cell (line only)
     int32_t *gvec;      // vector ids by cell: kBucket places per cell (grid), K (line)
-    double *gvh;        // x 4: by cell, their unit directions (grid) or (v, |v|) (line)
+    double *gvh;        // x 4: (v, |v|) of each
     int32_t *lcnt;      // cells: candidate-list length (-1: full scan; grid only)
     unsigned long long *gtot;  // line only: the allocator of the cells' vector
                                // ranges (build), 1 when some vector is outside

@@ -36,8 +36,8 @@ __device__ __forceinline__ int cell_of(double x0, double x1, double x2, const do
 // the cells a rebuild needed two kernels more.
 constexpr int kBucket = 16;
 
-// Vector j = v (norm vn) into cell c of the grid: counted, and its id and unit
-// direction at the next place (counts start at zero).
+// Vector j = v (norm vn) into cell c of the grid: counted, and its id and (v,
+// |v|) at the next place (counts start at zero).
 __device__ __forceinline__ void bucket_vector(const RunView &R, int64_t j, int c, const double *v,
                                               double vn)
 {
@@ -45,9 +45,8 @@ __device__ __forceinline__ void bucket_vector(const RunView &R, int64_t j, int c
     const int k = atomicAdd(&R.gcnt[c], 1);
     if (k >= kBucket) return;
     const int64_t p = (int64_t)c * kBucket + k;
-    const double inv = 1.0 / vn;
     R.gvec[p] = (int32_t)j;
-    reinterpret_cast<double4 *>(R.gvh)[p] = make_double4(v[0] * inv, v[1] * inv, v[2] * inv, 0.0);
+    reinterpret_cast<double4 *>(R.gvh)[p] = make_double4(v[0], v[1], v[2], vn);
 }
 
 // share u of a direction x on the scaled simplex and its cell; -1 unless
