@@ -673,22 +673,25 @@ __device__ __forceinline__ void next_resets(const RunView &R, int64_t g)
 // k_newpop and the next generation's k_prep in one pass (RunView::turn), one
 // kernel boundary (about 4.5 us) fewer per generation.  Nothing here waits for
 // another workgroup:
-//   - new slots (the first ceil(K/1024) workgroups): slot j <- its survivor as
+//   - new slots (the first ceil(K/512) workgroups): slot j <- its survivor as
 //     in newpop_body; its place in the ascending list of valid slots counts
 //     the earlier workgroups' survivors straight from their keys (final since
-//     the association), up to 15 eight-byte loads per thread at the largest K
+//     the association), up to 31 eight-byte loads per thread at the largest K
 //     taken here;
 //   - free rows: the old slots' rows (same workgroups) and the rows that were
-//     handed out or spare in this generation (ceil((K+N)/1024) workgroups more)
+//     handed out or spare in this generation (ceil((K+N)/512) workgroups more)
 //     of individuals that no key names.  A merged row lives exactly if its
 //     vector's key holds its index, so no pass over stamped rows is needed.
 // The buffers that this kernel reads and the ones it writes alternate by
 // generation parity (keys, row lists, counts).  Bound by its chain of memory
 // round trips (counter; keys and rows; the survivors' values; one returned
-// atomic), so loads are issued unconditionally where an index is at hand, and
-// workgroups are as large as they can be: fewer earlier keys per thread, fewer
-// atomics on the one counter.
-constexpr int kTurnBlock = 1024, kTurnWaves = kTurnBlock / 64;
+// atomic), so loads are issued unconditionally where an index is at hand.
+// Larger workgroups read fewer earlier keys per thread and add less often to
+// the one counter, smaller ones spread the scattered reads over more CUs: 20
+// generations of 2,048 x 100 took 467, 455 and 459 us with 1,024, 512 and 256
+// threads, of 10,011 x 500 782, 781 and 796.  Two kernels in its place took 5.6 +
+// 4.9 us at 10,011 vectors and 4.0 + 3.8 at 36; it takes 8.1 and 4.8.
+constexpr int kTurnBlock = 512, kTurnWaves = kTurnBlock / 64;
 __device__ __forceinline__ void turn_body(const RunView &R, int64_t bx)
 {
     __shared__ uint32_t smin[kTurnWaves][kMaxM], smax[kTurnWaves][kMaxM];
@@ -1093,8 +1096,8 @@ int64_t newpop_blocks(const RunView &R)
 }
 
 // Runs whose k_newpop also prepares the next generation.  Each workgroup reads
-// all earlier keys, so the reads grow with K^2: at 16,384 vectors up to 15
-// loads a thread, at 100,128 they would be 39 MB per generation.
+// all earlier keys, so the reads grow with K^2: at 16,384 vectors up to 31
+// loads a thread, at 100,128 they would be 78 MB per generation.
 bool turn_rule(int64_t K) { return K <= 16384; }
 
 int assoc_rows_per_block() { return 256 * 4; }

@@ -1,6 +1,6 @@
 """The kernel that writes the new population and prepares the next generation
 in one pass, against the oracle generation by generation, at the sizes where
-its work is cut: 1,024 slots (and 1,024 row-list entries) per workgroup,
+its work is cut: 512 slots (and 512 row-list entries) per workgroup,
 fewer individuals than vectors (rows to spare), an odd number of offspring, an
 adaptation every generation, and both sides of the rule that chooses it; and
 small populations' reproduction."""
@@ -31,9 +31,9 @@ def O():
     return O
 
 
-# (problem, m, d, N, K): slots at the edges of one and two workgroups (any
-# count is a lattice of two objectives), list entries at 1,024 +- 1
-@pytest.mark.parametrize("shape", [(1, 2, 6, 1, 2), (2, 2, 5, 1023, 1023), (1, 2, 4, 1024, 1024),
+# (problem, m, d, N, K): slots at the edges of one to four workgroups (any
+# count is a lattice of two objectives), list entries at multiples of 512 +- 1
+@pytest.mark.parametrize("shape", [(1, 2, 6, 1, 2), (1, 2, 5, 511, 512), (2, 2, 4, 512, 513), (2, 2, 5, 1023, 1023), (1, 2, 4, 1024, 1024),
                                    (3, 2, 7, 1000, 1025), (1, 2, 5, 23, 1001), (2, 3, 9, 511, 528),
                                    (1, 2, 4, 2047, 2049), (2, 8, 9, 33, 36)])
 def test_turn_matches_oracle(P, O, shape):
