@@ -94,6 +94,32 @@ rvea_status check_args(int problem, int m, int d, int64_t N, int64_t K, const rv
     return RVEA_OK;
 }
 
+// Default shape of a full-scan pass of `rows` rows over K vectors: rows per lane,
+// and the chunk length that gives about kScanGroups workgroups (two per CU, so
+// that no CU runs three), within the tile and [CS0, 1024].  More chunks fill the
+// device no better, and every chunk leaves a maximum and a tile mask per row for
+// the re-rank to read: at 3,876 vectors of five objectives four rows per lane and
+// 122 chunks took 13.2 + 16.2 us, one row and 16 chunks 11.0 + 7.8; at 8 objectives
+// and 6,435 vectors 58.7 and 37.2 us together, at 84 vectors 10.7 and 9.7.  More
+// rows per lane share a vector's read once one row per lane gives more
+// workgroups than that by itself.
+constexpr int64_t kScanGroups = 512;
+struct ScanShape {
+    int rr, cs, kc;
+};
+ScanShape scan_shape(int64_t rows, int64_t K, int CS0)
+{
+    ScanShape s;
+    s.rr = rows <= 16384 ? 1 : rows <= 32768 ? 2 : 4;
+    const int64_t nbi = (rows + 256 * s.rr - 1) / (256 * s.rr);
+    const int64_t kc = std::max<int64_t>(1, kScanGroups / nbi);
+    int64_t cs = ((K + kc - 1) / kc + kTile - 1) / kTile * kTile;
+    cs = std::min<int64_t>(std::max<int64_t>(cs, CS0), 32 * kTile);
+    s.cs = (int)cs;
+    s.kc = (int)((K + cs - 1) / cs);
+    return s;
+}
+
 bool swarm(int op) { return op == OP_PSO || op == OP_CSO; }
 
 void make_layout(int problem, int m, int d, int64_t N, int64_t K, int op, Layout &L)
@@ -425,13 +451,14 @@ rvea_status create_run(int problem, int m, int d, int64_t N, int64_t K, uint64_t
     R.p_m = p.p_m;
     R.lb = p.lb;
     R.ub = p.ub;
-    R.KC = L.KC;
-    R.CS = L.CS;
-    R.rr = 4;
+    const ScanShape scan = scan_shape(K + N, K, L.CS), gscan = scan_shape(K, K, L.CS);
+    R.KC = scan.kc;
+    R.CS = scan.cs;
+    R.rr = scan.rr;
     R.rk = default_rerank_rows(K + N);
-    R.gKC = L.KC;
-    R.gCS = L.CS;
-    R.grr = 4;
+    R.gKC = gscan.kc;
+    R.gCS = gscan.cs;
+    R.grr = gscan.rr;
     char *w = (char *)workspace;
     R.X = (float *)(w + L.off[B_X]);
     R.slot_rows = (int32_t *)(w + L.off[B_SLOT]);
@@ -1162,9 +1189,10 @@ rvea_status rvea_autotune(rvea_run r, rvea_tuning *out)
     // the gamma pass, batches, and runs without an index)
     const int gG0 = R.gG;
     R.gG = 0;
-    std::vector<Cand> cands;
+    std::vector<Cand> cands = {{R.rr, R.CS, 0.f}};  // the current shape first
     for (int rr : {4, 2, 1})
-        for (int cs : chunk_candidates(R.M, R.K, rr, CS0, KC0, cus)) cands.push_back({rr, cs, 0.f});
+        for (int cs : chunk_candidates(R.M, R.K, rr, CS0, KC0, cus))
+            if (rr != R.rr || cs != R.CS) cands.push_back({rr, cs, 0.f});
     const int saved_rr = R.rr, saved_cs = R.CS, saved_kc = R.KC;
     double def_ms = -1.0;
     for (auto &c : cands) {
@@ -1221,7 +1249,10 @@ rvea_status rvea_autotune(rvea_run r, rvea_tuning *out)
     int g_rr = grr0, g_cs = gcs0;
     int ncand = (int)cands.size() + 3;
     for (int rr : {4, 2, 1}) {
-        for (int cs : chunk_candidates(R.K, R.K, rr, CS0, KC0, cus)) {
+        std::vector<int> lengths = chunk_candidates(R.K, R.K, rr, CS0, KC0, cus);
+        if (rr == grr0 && std::find(lengths.begin(), lengths.end(), gcs0) == lengths.end())
+            lengths.push_back(gcs0);  // the current shape
+        for (int cs : lengths) {
             const int kc = (int)((R.K + cs - 1) / cs);
             {  // timed as one launch of both passes
                 R.grr = rr;
@@ -1304,30 +1335,36 @@ rvea_status rebuild_plan(rvea_batch b)
 {
     BHIPCHK(b, hipStreamSynchronize(b->stream));
     const int n = (int)b->runs.size();
-    std::vector<RunView> views(n), gviews(n), wide(n);
-    int64_t wide_blocks = 0;
+    // Vector chunks of the full-scan launches: one length for the runs of a
+    // launch (an objective count), so that a launch of all their (row, vector)
+    // pairs has about kBatchGroups workgroups of 1,024 rows, within the tile, the
+    // 32 tiles that a chunk may have and the chunks that the run's buffers hold.
+    // A few runs need the chunks for parallelism; many fill the device without,
+    // and fewer chunks cut the per-chunk maxima written and the re-rank's walk
+    // over them (the exact argmax does not depend on the chunking).  The gamma
+    // passes (rows = vectors) have their own lengths.
+    constexpr int64_t kBatchGroups = 1024;
+    std::vector<RunView> views(n), gviews(n);
+    int64_t pairs[kMaxM + 1] = {}, gpairs[kMaxM + 1] = {};
     for (int i = 0; i < n; ++i) {
-        views[i] = b->runs[i]->R;
-        // the gamma passes (rows = vectors) keep the run's own chunking, as
-        // alone: their few rows need the chunks for parallelism
-        gviews[i] = views[i];
-        gviews[i].KC = gviews[i].gKC;
-        gviews[i].CS = gviews[i].gCS;
-        // a batch whose runs fill the device by themselves needs no vector
-        // chunks for occupancy: chunks of up to 32 tiles (never more chunks
-        // than the run's buffers hold) cut the per-chunk maxima written and
-        // re-read and the re-rank's walk over them (the exact argmax does not
-        // depend on the chunking)
-        RunView &v = wide[i];
-        v = views[i];
-        const int64_t cs = std::min<int64_t>(32 * kTile, (v.K + kTile - 1) / kTile * kTile);
-        if (cs > v.CS) {
+        const RunView &v = b->runs[i]->R;
+        if (v.gG > 0) continue;
+        pairs[v.m] += v.M * v.K;
+        gpairs[v.m] += v.K * v.K;
+    }
+    for (int i = 0; i < n; ++i) {
+        const Layout &L = b->runs[i]->L;
+        views[i] = gviews[i] = b->runs[i]->R;
+        auto chunk = [&](RunView &v, int64_t all) {
+            int64_t cs = all / (kBatchGroups * assoc_rows_per_block());
+            cs = std::min<int64_t>(std::min<int64_t>(cs, v.K), 32 * kTile);
+            cs = std::max<int64_t>((cs + kTile - 1) / kTile * kTile, L.CS);
             v.CS = (int)cs;
             v.KC = (int)((v.K + cs - 1) / cs);
-        }
-        if (v.gG <= 0) wide_blocks += batch_phase_blocks(BP_ASSOC, v);
+        };
+        chunk(views[i], pairs[views[i].m]);
+        chunk(gviews[i], gpairs[gviews[i].m]);
     }
-    if (wide_blocks >= kFillBlocks) views = wide;
     std::vector<Span> spans;
     b->plan.clear();
     for (int phase = 0; phase < BP_COUNT; ++phase) {
