@@ -219,10 +219,15 @@ struct rvea_batch_s {
     };
     std::vector<Launch> plan;
     bool dirty = true;
-    int64_t version = 0, graph_version = -1, last_step_version = -1;
+    int64_t version = 0;
     hipStream_t cap_stream = nullptr;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
+    // captured generations: without and with the phases of an adaptation, each
+    // captured when a membership comes to its second such generation
+    struct Captured {
+        int64_t version = -1, seen = -1;  // memberships captured, and come to once
+        hipGraph_t graph = nullptr;
+        hipGraphExec_t exec = nullptr;
+    } captured[2];
     bool use_graphs = true;
     char err[512] = "";
 };
@@ -1399,9 +1404,14 @@ rvea_status rebuild_plan(rvea_batch b)
     return RVEA_OK;
 }
 
-hipError_t enqueue_batch_generation(rvea_batch b, hipStream_t s)
+// The phases from BP_ADAPT on do nothing unless some run adapts (each run's
+// adaptation is decided on the device): a generation in which none does leaves
+// them out.  Their launches, up to nine, cost 4.7 us each even so, 45 of 390 us
+// a generation at sixteen served runs.
+hipError_t enqueue_batch_generation(rvea_batch b, hipStream_t s, bool adapt)
 {
     for (const auto &L : b->plan) {
+        if (!adapt && L.phase >= BP_ADAPT) continue;
         hipError_t e = launch_batch(L.phase, L.cls, batch_phase_gamma(L.phase) ? b->d_gruns : b->d_runs,
                                     b->d_spans + L.span_off, L.n, L.blocks, s);
         if (e != hipSuccess) return e;
@@ -1473,31 +1483,34 @@ rvea_status rvea_batch_step(rvea_batch b)
         if (st != RVEA_OK) return st;
     }
     if (b->runs.empty()) return RVEA_OK;
-    const bool stable = b->last_step_version == b->version;
-    b->last_step_version = b->version;
-    if (b->use_graphs && (stable || b->graph_version == b->version)) {
-        if (b->graph_version != b->version) {
-            if (b->gexec) {
-                BHIPCHK(b, hipGraphExecDestroy(b->gexec));
-                BHIPCHK(b, hipGraphDestroy(b->graph));
-                b->gexec = nullptr;
-                b->graph = nullptr;
+    bool adapt = false;  // some run's generation is a multiple of its period
+    for (rvea_run r : b->runs) adapt = adapt || (r->t + 1) % r->R.period == 0;
+    rvea_batch_s::Captured &cap = b->captured[adapt ? 1 : 0];
+    const bool again = cap.seen == b->version;
+    cap.seen = b->version;
+    if (b->use_graphs && again) {
+        if (cap.version != b->version) {
+            if (cap.exec) {
+                BHIPCHK(b, hipGraphExecDestroy(cap.exec));
+                BHIPCHK(b, hipGraphDestroy(cap.graph));
+                cap.exec = nullptr;
+                cap.graph = nullptr;
             }
             if (!b->cap_stream)
                 BHIPCHK(b, hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
             BHIPCHK(b, hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
-            hipError_t e = enqueue_batch_generation(b, b->cap_stream);
+            hipError_t e = enqueue_batch_generation(b, b->cap_stream, adapt);
             hipGraph_t g = nullptr;
             hipError_t e2 = hipStreamEndCapture(b->cap_stream, &g);
             if (e != hipSuccess) return bfail(b, e, "batch capture");
             if (e2 != hipSuccess) return bfail(b, e2, "hipStreamEndCapture");
-            b->graph = g;
-            BHIPCHK(b, hipGraphInstantiate(&b->gexec, g, nullptr, nullptr, 0));
-            b->graph_version = b->version;
+            cap.graph = g;
+            BHIPCHK(b, hipGraphInstantiate(&cap.exec, g, nullptr, nullptr, 0));
+            cap.version = b->version;
         }
-        BHIPCHK(b, hipGraphLaunch(b->gexec, b->stream));
+        BHIPCHK(b, hipGraphLaunch(cap.exec, b->stream));
     } else {
-        BHIPCHK(b, enqueue_batch_generation(b, b->stream));
+        BHIPCHK(b, enqueue_batch_generation(b, b->stream, adapt));
     }
     for (rvea_run r : b->runs) {
         r->t += 1;
@@ -1532,8 +1545,10 @@ rvea_status rvea_batch_destroy(rvea_batch b)
     if (!b) return RVEA_EINVAL;
     (void)hipStreamSynchronize(b->stream);
     for (rvea_run r : b->runs) r->batch = nullptr;
-    if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
-    if (b->graph) (void)hipGraphDestroy(b->graph);
+    for (auto &cap : b->captured) {
+        if (cap.exec) (void)hipGraphExecDestroy(cap.exec);
+        if (cap.graph) (void)hipGraphDestroy(cap.graph);
+    }
     if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
     delete b;
     return RVEA_OK;

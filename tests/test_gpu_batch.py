@@ -235,3 +235,38 @@ def test_batch_with_general_distribution_indices(P, O):
         assert same(a, b) is None, same(a, b)
     assert stats["straddles"] <= max(2, 1e-6 * stats["genes"]), stats
     assert stats["near_ties"] <= max(1, 1e-4 * stats["vectors"]), stats
+
+
+def test_batch_of_different_periods_equals_alone(P):
+    """Runs that adapt every generation, every third, every seventh and never,
+    joined at different generations: steps with and without an adaptation
+    alternate, eager and as graphs, and every run ends as it does alone."""
+    shapes = [(1, 3, 20, 105, 1.0 / 3), (2, 2, 15, 60, 1.0 / 40), (3, 5, 12, 126, 7.0 / 40), (1, 3, 9, 36, 1.0)]
+
+    def make(k):
+        problem, m, d, K, fr = shapes[k]
+        return P.Run(problem, m, d, K, K, seed=40 + k, params=P.default_params(t_max=40, fr=fr))
+
+    alone = []
+    for k in range(len(shapes)):
+        r = make(k)
+        r.run(23 - 2 * k)
+        alone.append(r.get_state())
+        r.close()
+    for graphs in (True, False):
+        batch = P.Batch(4)
+        batch.set_graphs(graphs)
+        runs = []
+        for k in range(len(shapes)):
+            runs.append(make(k))
+            batch.admit(runs[-1])
+            batch.step(2 if k < 3 else 17)
+        for r, want in zip(runs, alone):
+            got = r.get_state()
+            assert got["t"] == want["t"]
+            for key in ("X", "F", "valid", "V", "gamma"):
+                assert np.array_equal(got[key], want[key], equal_nan=True), (graphs, key)
+        for r in list(runs):
+            batch.retire(r)
+            r.close()
+        batch.close()
