@@ -234,7 +234,7 @@ __device__ __forceinline__ double pm_delta(double x, double lb, double ub, doubl
     if (mm == 0.5) return 0.0;
     const double span = ub - lb;
     const bool lo = mm < 0.5;
-    const double dd = lo ? (x - lb) / span : (ub - x) / span;
+    const double dd = (lo ? x - lb : ub - x) / span;
     const double base = lo ? 2.0 * mm + (1.0 - 2.0 * mm) * ipow(1.0 - dd, n)
                            : 2.0 * (1.0 - mm) + 2.0 * (mm - 0.5) * ipow(1.0 - dd, n);
     if (base > 0.0 && base < 1e-30) return pm_delta_pow(x, lb, ub, mm, xi);  // below float range
@@ -362,14 +362,17 @@ __global__ void k_init_empty(RunView R)
 // Mutation sites of child o: events e = 0,1,... with counter (e, o, t,
 // TAG_MUT); U = 1 - u53(w0,w1) in (0,1], gap = floor(log U / log(1-p)),
 // site_e = site_{e-1} + 1 + gap while it stays below d; M_mut = u53(w2,w3).
-// Both children of a pair are drawn at once, S/2 lanes each per round.
+// Both children of a pair are drawn at once, S/2 lanes each per round.  rlq is
+// 1 / log(1-p); prefix sums by DPP and counts by ballots (shuffles through LDS, a
+// dozen a round, were half of the 2.5 us that the sites took a wavefront).
 template <int S>
 __device__ void draw_sites(const RunView &R, uint32_t t, int64_t o1, int64_t o2, bool has2,
-                           double lq, int lane, int32_t *s1, double *m1, int32_t *s2, double *m2,
+                           double rlq, int lane, int32_t *s1, double *m1, int32_t *s2, double *m2,
                            int *n1, int *n2)
 {
     constexpr int H2 = S / 2;
     const int c = lane / H2, hl = lane % H2;
+    const int first = (threadIdx.x & 63) - hl;  // the child's first lane in the wavefront
     const int64_t o = c ? o2 : o1;
     int32_t *sites = c ? s2 : s1;
     double *mags = c ? m2 : m1;
@@ -385,19 +388,13 @@ __device__ void draw_sites(const RunView &R, uint32_t t, int64_t o1, int64_t o2,
         if (!done) {
             const W4 w = draw(R, e, (uint32_t)o, t, TAG_MUT);
             const double U = 1.0 - unif53(w.w[0], w.w[1]);
-            double q = log(U) / lq;
+            double q = log(U) * rlq;
             if (!(q >= 0.0)) q = 0.0;
             const double gap = floor(q);
             step = gap >= (double)R.d ? R.d + 1 : 1 + (int)gap;
             mag = unif53(w.w[2], w.w[3]);
         }
-        int incl = step;
-#pragma unroll
-        for (int off = 1; off < H2; off <<= 1) {
-            const int y = __shfl_up(incl, off, H2);
-            if (hl >= off) incl += y;
-        }
-        const int pos = cur + incl;
+        const int pos = cur + group_incl_scan<H2>(step, hl);
         if (!done && pos < R.d) {
             const int idx = round * H2 + hl;
             if (idx < kMaxSites) {
@@ -408,11 +405,9 @@ __device__ void draw_sites(const RunView &R, uint32_t t, int64_t o1, int64_t o2,
             }
         }
         const int last = __shfl(pos, H2 - 1, H2);
-        int mine = (!done && pos < R.d) ? 1 : 0;
-#pragma unroll
-        for (int off = H2 / 2; off > 0; off >>= 1) mine += __shfl_xor(mine, off, H2);
+        const unsigned long long hits = __ballot(!done && pos < R.d) >> first;
         if (!done) {
-            count += mine;
+            count += __popc((uint32_t)hits & (uint32_t)((1ull << H2) - 1));
             cur = last;
             if (last >= R.d) done = true;
         }
@@ -481,12 +476,13 @@ __device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx, Off
     const int64_t p = ns == 1 ? u : u / ns;
     const int sp = ns == 1 ? 0 : (int)(u - p * ns);
     const bool active = p < P;
-    const int64_t pop = *R.t_done;  // the parents' population
+    int32_t nvalid;
+    const int64_t pop = count_and_nvalid(R, nvalid);  // the parents' population
     const uint32_t t = (uint32_t)(pop + 1);
     float *Fm = fm_of(R, pop);
     const int64_t o1 = p, o2 = p + P;
     const bool has2 = o2 < R.N;
-    const uint32_t nv = (uint32_t)*nvalid_of(R, pop);
+    const uint32_t nv = (uint32_t)nvalid;
     if (nv == 0) {  // no parent left (every row was non-finite): offspring are empty
         if (active && lane == 0 && sp == 0) {
             for (int k = 0; k < R.m; ++k) {
@@ -519,9 +515,9 @@ __device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx, Off
     int n1 = 0, n2 = 0;
     const double pr = R.p_m / (double)R.d;
     if (pr > 0.0) {
-        const double lq = log1p(-(pr > 1.0 ? 1.0 : pr));
+        const double rlq = 1.0 / log1p(-(pr > 1.0 ? 1.0 : pr));
         if (active)
-            draw_sites<S>(R, t, o1, o2, has2, lq, lane, L.sites[seg][0], L.mags[seg][0],
+            draw_sites<S>(R, t, o1, o2, has2, rlq, lane, L.sites[seg][0], L.mags[seg][0],
                           L.sites[seg][1], L.mags[seg][1], &n1, &n2);
     }
     wave_sync();
@@ -756,8 +752,9 @@ __device__ __forceinline__ void offspring_finish_body(const RunView &R, int64_t 
     const int64_t o = fl == 16 ? tid / 16 : tid;
     const int sub = fl == 16 ? (int)(tid % 16) : 0;
     const int64_t P = (R.N + 1) / 2;
-    const int64_t pop = *R.t_done;
-    if (*nvalid_of(R, pop) == 0) return;  // no parent: the offspring kernel left empty children
+    int32_t nv;
+    const int64_t pop = count_and_nvalid(R, nv);
+    if (nv == 0) return;  // no parent: the offspring kernel left empty children
     float *Fm = fm_of(R, pop);
     double g = 0.0;
     if (o < R.N) {

@@ -101,12 +101,13 @@ __device__ __forceinline__ void operator_body(const RunView &R, int64_t bx)
     const int64_t units = OP == OP_CSO ? P : R.N;
     const int64_t u = bx * SEGS + seg;
     const bool active = u < units;
-    const int64_t pop = *R.t_done;  // the parents' population
+    int32_t nvalid;
+    const int64_t pop = count_and_nvalid(R, nvalid);  // the parents' population
     const uint32_t t = (uint32_t)(pop + 1);
     float *Fm = fm_of(R, pop);
     const int64_t o1 = u, o2 = u + P;  // CSO: the loser's child and the winner's copy
     const bool has2 = OP == OP_CSO && o2 < R.N;
-    const uint32_t nv = (uint32_t)*nvalid_of(R, pop);
+    const uint32_t nv = (uint32_t)nvalid;
     const int32_t *orow = off_row_of(R, t);
     if (nv == 0) {  // no member left: the offspring are empty, as for the genetic operators
         if (active && lane == 0) {

@@ -711,7 +711,8 @@ __device__ __forceinline__ void turn_body(const RunView &R, int64_t bx)
         ka = R.key[j];
         kb = R.key[R.K + j];
     }
-    const int64_t g = *R.t_done + 1;
+    int32_t nv0;  // individuals of the parents' population
+    const int64_t g = count_and_nvalid(R, nv0) + 1;
     const unsigned long long *key = key_of(R, g);
     const int32_t *rows = off_row_of(R, g);
     if (bx == 0) next_resets(R, g);
@@ -747,7 +748,6 @@ __device__ __forceinline__ void turn_body(const RunView &R, int64_t bx)
         fr = vold && (kk == ~0ull || (int64_t)(kk & mask) != j);
     } else if (j < R.M) {  // the generation's row list (unset beyond its M - nvalid rows)
         rowold = rows[j];
-        const int32_t nv0 = *nvalid_of(R, g - 1);
         // spare rows (j >= N) have no vector
         fr = j < R.M - nv0 && (kk == ~0ull || (int64_t)(kk & mask) != R.K + j);
     }

@@ -129,6 +129,15 @@ __device__ __forceinline__ int32_t *nvalid_of(const RunView &R, int64_t p)
 {
     return R.nvalid + (p & 1);
 }
+// the generation counter p and the individuals of population p, in one memory
+// round trip (both parities' counts load beside the counter)
+__device__ __forceinline__ int64_t count_and_nvalid(const RunView &R, int32_t &nv)
+{
+    const int2 n = *reinterpret_cast<const int2 *>(R.nvalid);
+    const int64_t p = *R.t_done;
+    nv = (p & 1) ? n.y : n.x;
+    return p;
+}
 
 // buffers of generation gen: its offspring's rows, its keys, the extremes of
 // its survivors
@@ -375,6 +384,28 @@ __device__ __forceinline__ int wave_incl_scan(int v)
     v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);  // row_shr:8
     v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return v;
+}
+
+// Inclusive prefix sum over groups of H adjacent lanes (H = 2 .. 32, aligned),
+// every lane of a group active or none: DPP shifts within each row of 16 lanes
+// (a lane without a source in its group adds 0), and for 32 the first row's last
+// lane added to the second.
+template <int H>
+__device__ __forceinline__ int group_incl_scan(int v, int hl)
+{
+    int y = __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);  // row_shr:1
+    v += H >= 16 || hl >= 1 ? y : 0;
+    if constexpr (H >= 4) {
+        y = __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+        v += H >= 16 || hl >= 2 ? y : 0;
+    }
+    if constexpr (H >= 8) {
+        y = __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+        v += H >= 16 || hl >= 4 ? y : 0;
+    }
+    if constexpr (H >= 16) v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    if constexpr (H == 32) v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
     return v;
 }
 

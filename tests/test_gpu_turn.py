@@ -87,3 +87,18 @@ def test_few_pairs_match_oracle(P, O, shape):
     run = P.Run(problem, m, d, N, K, seed=d, params=prm)
     lockstep(O, run, prm, 3, new_stats())
     run.close()
+
+
+# every segment width of the reproduction kernel (4, 8, 16, 32 and 64 lanes a
+# pair): the mutation sites' prefix sums and counts over 2 to 32 lanes a child,
+# up to four sites a child expected
+@pytest.mark.parametrize("shape", [(1, 2, 12, 4200, 4200), (2, 2, 25, 4199, 4200), (3, 2, 60, 4101, 4200),
+                                   (1, 3, 100, 251, 253), (2, 3, 300, 989, 990)])
+@pytest.mark.parametrize("p_m", [1.0, 4.0])
+def test_segment_widths_match_oracle(P, O, shape, p_m):
+    problem, m, d, N, K = shape
+    prm = P.default_params(t_max=6, fr=0.5, p_m=p_m)
+    run = P.Run(problem, m, d, N, K, seed=d, params=prm)
+    stats = lockstep(O, run, prm, 2, new_stats())
+    run.close()
+    assert stats["straddles"] <= 1e-6 * stats["genes"] + 1
