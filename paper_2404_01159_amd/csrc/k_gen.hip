@@ -651,8 +651,14 @@ __device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx, Off
                     pv2[k] = y2[k];
                 }
             }
-            *reinterpret_cast<float4 *>(c1row + g0) = make_float4(y1[0], y1[1], y1[2], y1[3]);
-            if (has2) *reinterpret_cast<float4 *>(c2row + g0) = make_float4(y2[0], y2[1], y2[2], y2[3]);
+            if (evaluate) {  // uniform
+                st4_stream(c1row + g0, y1);
+                if (has2) st4_stream(c2row + g0, y2);
+            } else {
+                *reinterpret_cast<float4 *>(c1row + g0) = make_float4(y1[0], y1[1], y1[2], y1[3]);
+                if (has2)
+                    *reinterpret_cast<float4 *>(c2row + g0) = make_float4(y2[0], y2[1], y2[2], y2[3]);
+            }
         }
         g1 = seg_sum<S>(g1);
         g2 = seg_sum<S>(g2);

@@ -481,6 +481,20 @@ __device__ __forceinline__ void child_ideal(const RunView &R, int64_t gen, bool 
     }
 }
 
+// Four genes of a child, written past the caches' ordinary allocation
+// (nontemporal).  For genetic children that are evaluated on the fly: nothing
+// reads them before the next generation's random mating, and the rows that the
+// kernel still reads stay cached instead.  Ordinary stores there: ten generations
+// of 100,128 x 5,000 9.9 ms, twenty of 10,011 x 500 774 us, sixteen served runs
+// 3.63 ms; so: 9.4 ms, 753 us, 3.42 ms.  Policies are read by their rollouts right
+// after (1217 -> 1225 us), and the swarm's children and velocities lost by it too
+// (347 -> 357 us at 5,000 x 700).
+__device__ __forceinline__ void st4_stream(float *p, const float (&y)[4])
+{
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store((f4{y[0], y[1], y[2], y[3]}), reinterpret_cast<f4 *>(p));
+}
+
 // x clipped to [lo, hi] (lo <= hi, x not NaN): one binary64 max and min
 __device__ __forceinline__ double dclip(double x, double lo, double hi)
 {
