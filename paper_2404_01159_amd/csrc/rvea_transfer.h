@@ -38,8 +38,10 @@ struct StateArray {
     size_t bytes;
 };
 // Copies the arrays, and the slots' gene rows if X is given, between the host
-// and the workspace on stream s; returns when the copies are done.
-hipError_t transfer_state(const RunView &R, const std::vector<StateArray> &arrays, float *X, bool out,
+// and the workspace on stream s; returns when the copies are done.  Refused on
+// a capturing stream, before anything is enqueued, and for rows longer than a
+// chunk.
+hipError_t transfer_state(const RunView &R, const StateArray *arrays, int n_arrays, float *X, bool out,
                           hipStream_t s);
 // the rest of a host-set state at generation t
 hipError_t launch_set_reset(const RunView &R, hipStream_t s, int64_t t, int unscale);

@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <vector>
 
 #include "rvea_dev.h"
@@ -76,7 +77,12 @@ void staging_give(const Staging &s)
 {
     if (!s.p) return;
     std::lock_guard<std::mutex> lock(g_mu);
-    g_idle.push_back(s);
+    try {
+        g_idle.push_back(s);
+    } catch (const std::bad_alloc &) {  // no place in the list: not kept
+        (void)hipHostFree(s.p);
+        return;
+    }
     trim(g_runs > 0 ? kIdleBytes : kIdleNoRuns);
 }
 
@@ -196,18 +202,16 @@ void host_copy(const RunView &R, const Chunk &c, uint8_t *stage, bool out)
     if (c.parts.n == 0) move(c.x, stage, (size_t)c.rows * R.d * 4);
 }
 
-}  // namespace
-
-hipError_t transfer_state(const RunView &R, const std::vector<StateArray> &arrays, float *X, bool out,
-                          hipStream_t s)
+// arrays packed into chunks (a large one over several), then the rows
+void plan_chunks(const RunView &R, const StateArray *arrays, int n_arrays, float *X,
+                 std::vector<Chunk> *chunks)
 {
-    // arrays packed into chunks (a large one over several), then the rows
-    std::vector<Chunk> chunks;
-    for (const StateArray &a : arrays) {
+    for (int k = 0; k < n_arrays; ++k) {
+        const StateArray &a = arrays[k];
         for (size_t o = 0; o < a.bytes;) {
-            if (chunks.empty() || chunks.back().parts.n == kMaxParts || chunks.back().bytes >= kStageBytes)
-                chunks.push_back(Chunk{});
-            Chunk &c = chunks.back();
+            if (chunks->empty() || chunks->back().parts.n == kMaxParts || chunks->back().bytes >= kStageBytes)
+                chunks->push_back(Chunk{});
+            Chunk &c = chunks->back();
             const size_t n = std::min(a.bytes - o, kStageBytes - c.bytes);
             c.user[c.parts.n] = (uint8_t *)a.host + o;
             c.parts.part[c.parts.n++] = Part{(uint8_t *)a.dev + o, a.stride, c.bytes, n};
@@ -215,18 +219,35 @@ hipError_t transfer_state(const RunView &R, const std::vector<StateArray> &array
             o += n;
         }
     }
-    if (X) {
-        const int64_t rowb = (int64_t)R.d * 4;
-        const int64_t per = std::min<int64_t>(65535, (int64_t)kStageBytes / rowb);
-        if (per < 1) return hipErrorInvalidValue;  // the caller copies rows this long itself
-        for (int64_t r = 0; r < R.K; r += per) {
-            Chunk c{};
-            c.r0 = r;
-            c.rows = std::min(per, R.K - r);
-            c.x = (uint8_t *)(X + r * R.d);
-            c.bytes = (size_t)(c.rows * rowb);
-            chunks.push_back(c);
-        }
+    if (!X) return;
+    const int64_t rowb = (int64_t)R.d * 4;  // at most one chunk: longer rows are the caller's
+    const int64_t per = std::min<int64_t>(65535, (int64_t)kStageBytes / rowb);
+    for (int64_t r = 0; r < R.K; r += per) {
+        Chunk c{};
+        c.r0 = r;
+        c.rows = std::min(per, R.K - r);
+        c.x = (uint8_t *)(X + r * R.d);
+        c.bytes = (size_t)(c.rows * rowb);
+        chunks->push_back(c);
+    }
+}
+
+}  // namespace
+
+hipError_t transfer_state(const RunView &R, const StateArray *arrays, int n_arrays, float *X, bool out,
+                          hipStream_t s)
+{
+    // nothing may be captured here: the staging buffers serve this call only
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const hipError_t ec = hipStreamIsCapturing(s, &cap);
+    if (ec != hipSuccess) return ec;
+    if (X && (size_t)R.d * 4 > kStageBytes) return hipErrorInvalidValue;
+    if (cap != hipStreamCaptureStatusNone) return hipErrorStreamCaptureUnsupported;
+    std::vector<Chunk> chunks;
+    try {
+        plan_chunks(R, arrays, n_arrays, X, &chunks);
+    } catch (const std::bad_alloc &) {
+        return hipErrorOutOfMemory;
     }
     // two buffers in turn: a chunk's kernel is enqueued before the host copies
     // the chunk before it, and a buffer is taken again once its event is done

@@ -87,3 +87,42 @@ def test_threads_share_the_staging_buffers(P):
     for t in threads:
         t.join()
     assert not bad
+
+
+# a host-set gamma is kept although the index build computes one (cells, line)
+@pytest.mark.parametrize("m,K", [(2, 64), (3, 105), (3, 2016)])
+def test_gamma_set_from_the_host_with_an_index(P, m, K):
+    run = P.Run(2, m, 20, K, K, seed=2)
+    st = run.get_state()
+    g = np.linspace(0.1, 0.2, K)
+    run.set_state(st["X"], st["F"], st["valid"], st["V"], g, 3)
+    assert np.array_equal(run.get_state(genes=False)["gamma"], g)
+    run.set_index(False)
+    run.set_index(True)
+    assert np.array_equal(run.get_state(genes=False)["gamma"], g)
+    run.set_state(st["X"], st["F"], st["valid"], st["V"], None, 3)  # from the vectors
+    assert np.array_equal(run.get_state(genes=False)["gamma"], st["gamma"])
+    run.close()
+
+
+def test_refused_on_a_capturing_stream(P):
+    """An accessor on a stream under capture fails and leaves the capture alone."""
+    s = torch.cuda.Stream()
+    run = P.Run(1, 3, 12, 105, 105, seed=2, stream=s)
+    before = run.get_state()
+    x = torch.zeros(8, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        x += 1
+        with pytest.raises(RuntimeError):
+            run.get_state()
+        with pytest.raises(RuntimeError):
+            run.set_state(before["X"], before["F"], before["valid"], t=5)
+    g.replay()
+    torch.cuda.synchronize()
+    assert x.tolist() == [1.0] * 8
+    after = run.get_state()
+    for k in ("X", "F", "valid", "V", "gamma", "t"):
+        assert np.array_equal(after[k], before[k]), k
+    run.close()
