@@ -792,32 +792,8 @@ __global__ __launch_bounds__(256) void k_offspring_finish(RunView R)
     offspring_finish_body(R, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
-// ----------------------------------------------------- batched (many runs)
-__global__ __launch_bounds__(256) void kb_prep(const RunView *runs, const Span *sp, int n)
-{
-    const int s = find_span(sp, n, blockIdx.x);
-    prep_body(runs[sp[s].run], blockIdx.x - sp[s].start);
-}
-// batched: one-wavefront workgroups as above; NR = 21 when every run of the
-// launch has the default distribution indices (the same arithmetic as the
-// general variant, so results do not depend on the batch's make-up)
-template <int S, int NR>
-__global__ __launch_bounds__(kOffBlock) void kb_offspring(const RunView *runs, const Span *sp,
-                                                          int n)
-{
-    const int s = find_span(sp, n, blockIdx.x);
-    __shared__ OffspringLds<S> L;
-    offspring_body<S, NR, -1>(runs[sp[s].run], blockIdx.x - sp[s].start, L);
-}
-__global__ __launch_bounds__(256) void kb_offspring_finish(const RunView *runs, const Span *sp,
-                                                           int n)
-{
-    const int s = find_span(sp, n, blockIdx.x);
-    offspring_finish_body(runs[sp[s].run], (blockIdx.x - sp[s].start) * 256 + threadIdx.x);
-}
-
-// ------------------------------------------------------------- launchers
-int pick_segment(int d)
+// --------------------------------------------------------- segment lengths
+__host__ __device__ int pick_segment(int d)
 {
     const int Q = (d + 3) / 4;
     int S = 4;
@@ -838,7 +814,7 @@ int pick_segment(int d)
 // batched.
 constexpr int64_t kResidentOffspringWaves = 4096;
 
-int offspring_segment(int d, int64_t N)
+__host__ __device__ int offspring_segment(int d, int64_t N)
 {
     const int S = pick_segment(d);
     const int64_t P = (N + 1) / 2;
@@ -852,6 +828,49 @@ int offspring_segment(int d, int64_t N)
     return S;
 }
 
+// ----------------------------------------------------- batched (many runs)
+__global__ __launch_bounds__(256) void kb_prep(const RunView *runs, const Span *sp, int n)
+{
+    const int s = find_span(sp, n, blockIdx.x);
+    prep_body(runs[sp[s].run], blockIdx.x - sp[s].start);
+}
+// batched: one-wavefront workgroups as above; NR = 21 when every run of the
+// launch has the default distribution indices (the same arithmetic as the
+// general variant, so results do not depend on the batch's make-up)
+template <int S, int NR>
+__global__ __launch_bounds__(kOffBlock) void kb_offspring(const RunView *runs, const Span *sp,
+                                                          int n)
+{
+    const int s = find_span(sp, n, blockIdx.x);
+    __shared__ OffspringLds<S> L;
+    offspring_body<S, NR, -1>(runs[sp[s].run], blockIdx.x - sp[s].start, L);
+}
+// the runs of 32 and of 64 lanes in one launch: apart, the launch of the fewer
+// left part of the device idle (sixteen served runs: 114.8 and 23.7 us apart,
+// 129.7 together)
+template <int NR>
+__global__ __launch_bounds__(kOffBlock) void kb_offspring_wide(const RunView *runs, const Span *sp,
+                                                               int n)
+{
+    const int s = find_span(sp, n, blockIdx.x);
+    const RunView &R = runs[sp[s].run];
+    const int64_t bx = blockIdx.x - sp[s].start;
+    if (offspring_segment(R.d, R.N) == 32) {  // uniform
+        __shared__ OffspringLds<32> L;
+        offspring_body<32, NR, -1>(R, bx, L);
+    } else {
+        __shared__ OffspringLds<64> L;
+        offspring_body<64, NR, -1>(R, bx, L);
+    }
+}
+__global__ __launch_bounds__(256) void kb_offspring_finish(const RunView *runs, const Span *sp,
+                                                           int n)
+{
+    const int s = find_span(sp, n, blockIdx.x);
+    offspring_finish_body(runs[sp[s].run], (blockIdx.x - sp[s].start) * 256 + threadIdx.x);
+}
+
+// ------------------------------------------------------------- launchers
 // Few pairs of long rows (fewer pairs than the resident wavefronts, rows of
 // at least two 64-lane passes): each pair's genes are split into contiguous
 // parts, one 64-lane segment each, enough to fill the resident wavefronts,
@@ -900,8 +919,7 @@ hipError_t launch_batch_gen(int phase, int cls, const RunView *runs, const Span 
     case 4: kb_offspring<4, NRV><<<g, kOffBlock, 0, s>>>(runs, sp, n); break;                \
     case 8: kb_offspring<8, NRV><<<g, kOffBlock, 0, s>>>(runs, sp, n); break;                \
     case 16: kb_offspring<16, NRV><<<g, kOffBlock, 0, s>>>(runs, sp, n); break;              \
-    case 32: kb_offspring<32, NRV><<<g, kOffBlock, 0, s>>>(runs, sp, n); break;              \
-    default: kb_offspring<64, NRV><<<g, kOffBlock, 0, s>>>(runs, sp, n); break;              \
+    default: kb_offspring_wide<NRV><<<g, kOffBlock, 0, s>>>(runs, sp, n); break;             \
     }
         if (cls & kDefaultIndices)
             RVEA_KBOFF(21)

@@ -981,15 +981,16 @@ __global__ __launch_bounds__(64) void kb_grid_cells(const RunView *runs, const S
     const int s = find_span(sp, n, blockIdx.x);
     grid_cells_body(runs[sp[s].run], blockIdx.x - sp[s].start, 0);
 }
-__global__ __launch_bounds__(256) void kb_assoc_grid(const RunView *runs, const Span *sp, int n)
+// the indexed associations, m = 2 and 3 in one launch: neither fills the
+// device for long (sixteen served runs: 9.3 and 9.6 us apart, 12.1 together)
+__global__ __launch_bounds__(256) void kb_assoc_index(const RunView *runs, const Span *sp, int n)
 {
     const int s = find_span(sp, n, blockIdx.x);
-    assoc_grid_body(runs[sp[s].run], blockIdx.x - sp[s].start);
-}
-__global__ __launch_bounds__(256) void kb_assoc_line(const RunView *runs, const Span *sp, int n)
-{
-    const int s = find_span(sp, n, blockIdx.x);
-    assoc_line_body(runs[sp[s].run], blockIdx.x - sp[s].start);
+    const RunView &R = runs[sp[s].run];
+    if (R.m == 3)
+        assoc_grid_body(R, blockIdx.x - sp[s].start);
+    else
+        assoc_line_body(R, blockIdx.x - sp[s].start);
 }
 __global__ __launch_bounds__(256) void kb_line_gamma(const RunView *runs, const Span *sp, int n)
 {
@@ -1040,12 +1041,7 @@ hipError_t launch_batch_grid(int phase, int cls, const RunView *runs, const Span
 {
     const dim3 g((unsigned)blocks);
     switch (phase) {
-    case BP_ASSOC:
-        if (cls == (kIndexedClass | 3))
-            kb_assoc_grid<<<g, 256, 0, s>>>(runs, sp, n);
-        else
-            kb_assoc_line<<<g, 256, 0, s>>>(runs, sp, n);
-        break;
+    case BP_ASSOC: kb_assoc_index<<<g, 256, 0, s>>>(runs, sp, n); break;
     case BP_GRID_RANGES: kb_grid_ranges<<<g, 256, 0, s>>>(runs, sp, n); break;
     case BP_GRID_FILL: kb_grid_fill<<<g, 256, 0, s>>>(runs, sp, n); break;
     case BP_GRID_CELLS:  // class: the objective count (3: cells, 2: the line's gamma)

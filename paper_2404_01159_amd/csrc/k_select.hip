@@ -81,13 +81,14 @@ __device__ __forceinline__ float dotf(const float *f, const float4 *v)
 // GAMMA = false: rows are the merged objective rows f' = F - z*.
 // GAMMA = true:  rows are the reference vectors themselves (Eq. 5), with the
 // pair (j, j) excluded.
+constexpr int kTileVectors = 1024;  // vectors of a workgroup's LDS copy, at most
+constexpr int vector_quads(int m) { return m <= 4 ? 1 : 2; }  // float4s of a binary32 vector
 template <int MD, int RR, bool GAMMA>
-__device__ __forceinline__ void assoc_body(const RunView &R, int64_t bx, int c, int gate)
+__device__ __forceinline__ void assoc_body(const RunView &R, int64_t bx, int c, int gate, float4 *sv)
 {
     // gamma pass, uniform exit: gate 1 always runs, gate 0 when the vectors changed
     if (GAMMA && gate != 1 && *R.vchanged == 0) return;
-    constexpr int NV4 = MD <= 4 ? 1 : 2;  // float4 per vector
-    __shared__ float4 sv[1024 * NV4];
+    constexpr int NV4 = vector_quads(MD);
     const int64_t j0 = (int64_t)c * R.CS;
     const int64_t left = R.K - j0;
     const int nvec = (int)(left < R.CS ? left : R.CS);
@@ -247,33 +248,48 @@ constexpr int kCache = 4;    // candidate chunks per lane kept in registers
 constexpr int kBatchRows = 8;  // rows per wave of the batched launch
 constexpr int kCand = 64;      // candidate vectors per wave after the binary32 prefilter
 
+// One wave's scratch of the re-rank, given by the kernel: a launch over several
+// objective counts holds one for all of them.
+template <int MD, int kRows>
+struct RerankLds {
+    static constexpr int kWaveItems = 12 * kRows < kItems ? kItems : 12 * kRows;  // tiles per wave
+    double s_f[kRows][MD];
+    double s_nrm[kRows];
+    int s_state[kRows];  // 0 inactive, 1 items, 2 zero row, 3 full scan
+    int s_cnt[kRows], s_off[kRows];
+    int s_item[kWaveItems];  // row << 27 | first vector of the tile
+    double s_best[kWaveItems];
+    double s_gam[kWaveItems];  // gamma of the item's best vector (selection)
+    int s_bj[kWaveItems];
+    unsigned char s_dup[kWaveItems];
+    // selection rows: the row's binary32 f' and threshold, and the candidate
+    // vectors that pass the binary32 prefilter (row << 27 | vector), their
+    // count per row and their binary64 cosines
+    float s_f32[kRows][MD];
+    float s_thr[kRows];
+    int s_rc[kRows];
+    int s_cand[kCand];
+    double s_cos[kCand];
+    double s_rb[kRows], s_rg[kRows];
+    int s_rj[kRows], s_full[kRows];
+};
 // kRows rows per wave (4, 8 or 16): fewer rows give more waves to hide the
 // phases' memory latency on small populations, more rows less per-row
 // overhead on large ones.
 template <int MD, bool GAMMA, int kRows>
-__device__ __forceinline__ void rerank_body(const RunView &R, int64_t bx, int gate)
+__device__ __forceinline__ void rerank_body(const RunView &R, int64_t bx, int gate, RerankLds<MD, kRows> &L)
 {
     constexpr int kLanes = 64 / kRows;  // lanes per row in phase 1
-    constexpr int kWaveItems = 12 * kRows < kItems ? kItems : 12 * kRows;  // tiles per wave
     // gamma pass, uniform exit: gate 1 always runs, gate 0 when the vectors changed
     if (GAMMA && gate != 1 && *R.vchanged == 0) return;
-    __shared__ double s_f[kRows][MD];
-    __shared__ double s_nrm[kRows];
-    __shared__ int s_state[kRows];  // 0 inactive, 1 items, 2 zero row, 3 full scan
-    __shared__ int s_cnt[kRows], s_off[kRows];
-    __shared__ int s_item[kWaveItems];  // row << 27 | first vector of the tile
-    __shared__ double s_best[kWaveItems];
-    __shared__ double s_gam[kWaveItems];  // gamma of the item's best vector (selection)
-    __shared__ int s_bj[kWaveItems];
-    __shared__ unsigned char s_dup[kWaveItems];
-    // selection rows: the row's binary32 f' and threshold, and the candidate
-    // vectors that pass the binary32 prefilter (row << 27 | vector), their
-    // count per row and their binary64 cosines
-    __shared__ float s_f32[kRows][MD];
-    __shared__ float s_thr[kRows];
-    __shared__ int s_rc[kRows];
-    __shared__ int s_cand[kCand];
-    __shared__ double s_cos[kCand];
+    constexpr int kWaveItems = RerankLds<MD, kRows>::kWaveItems;
+    auto &s_f = L.s_f; auto &s_nrm = L.s_nrm; auto &s_state = L.s_state;
+    auto &s_cnt = L.s_cnt; auto &s_off = L.s_off; auto &s_item = L.s_item;
+    auto &s_best = L.s_best; auto &s_gam = L.s_gam; auto &s_bj = L.s_bj;
+    auto &s_dup = L.s_dup; auto &s_f32 = L.s_f32; auto &s_thr = L.s_thr;
+    auto &s_rc = L.s_rc; auto &s_cand = L.s_cand; auto &s_cos = L.s_cos;
+    auto &s_rb = L.s_rb; auto &s_rg = L.s_rg; auto &s_rj = L.s_rj;
+    auto &s_full = L.s_full;
 
     const int t = threadIdx.x;
     const int r = t / kLanes, sub = t % kLanes;
@@ -425,8 +441,6 @@ __device__ __forceinline__ void rerank_body(const RunView &R, int64_t bx, int ga
     }
     __syncthreads();
 
-    __shared__ double s_rb[kRows], s_rg[kRows];
-    __shared__ int s_rj[kRows], s_full[kRows];
     const int rounds = (total * kTile + 63) / 64;
 
     // ---- phase 2, selection rows: the candidate tiles' vectors are scored
@@ -931,34 +945,63 @@ __device__ __forceinline__ void newpop_body(const RunView &R, int64_t bx)
 template <int MD, int RR, bool GAMMA>
 __global__ __launch_bounds__(256) void k_assoc(RunView R, int gate)
 {
-    assoc_body<MD, RR, GAMMA>(R, blockIdx.x, blockIdx.y, gate);
+    __shared__ float4 sv[kTileVectors * vector_quads(MD)];
+    assoc_body<MD, RR, GAMMA>(R, blockIdx.x, blockIdx.y, gate, sv);
 }
 template <int MD, bool GAMMA, int ROWS>
 __global__ __launch_bounds__(64) void k_rerank(RunView R, int gate)
 {
-    rerank_body<MD, GAMMA, ROWS>(R, blockIdx.x, gate);
+    __shared__ RerankLds<MD, ROWS> L;
+    rerank_body<MD, GAMMA, ROWS>(R, blockIdx.x, gate, L);
 }
 __global__ __launch_bounds__(256) void k_newpop(RunView R) { newpop_body(R, blockIdx.x); }
 __global__ __launch_bounds__(kTurnBlock) void k_turn(RunView R) { turn_body(R, blockIdx.x); }
 
+#define RVEA_M_DISPATCH(MVAL, CALL)                                                          \
+    switch (MVAL) {                                                                          \
+    case 2: CALL(2); break;                                                                  \
+    case 3: CALL(3); break;                                                                  \
+    case 4: CALL(4); break;                                                                  \
+    case 5: CALL(5); break;                                                                  \
+    case 6: CALL(6); break;                                                                  \
+    case 7: CALL(7); break;                                                                  \
+    default: CALL(8); break;                                                                 \
+    }
+
 // ----------------------------------------------------- batched (many runs)
 // blockIdx.x is decoded into (run, local block) through the span table; for
 // the association, local = chunk * row_blocks + row_block.
-template <int MD, int RR, bool GAMMA>
+// The objective counts of one vector width (float4s, QUADS) in one launch: a
+// launch each left the device part idle at its end (m = 5 and 8 of sixteen
+// served runs: 34.4 and 22.6 us, 41.2 together, though m = 5 then has the
+// registers of m = 7, four waves per SIMD instead of five).
+template <int QUADS, int RR>
 __global__ __launch_bounds__(256) void kb_assoc(const RunView *runs, const Span *sp, int n)
 {
     const int s = find_span(sp, n, blockIdx.x);
     const int64_t local = blockIdx.x - sp[s].start;
     const int64_t nbx = sp[s].nbx;
     const RunView &R = runs[sp[s].run];
-    assoc_body<MD, RR, GAMMA>(R, local % nbx, (int)(local / nbx), 0);
+    __shared__ float4 sv[kTileVectors * QUADS];
+#define RVEA_BA(MV)                                                                          \
+    if constexpr (vector_quads(MV) == QUADS)                                                  \
+    assoc_body<MV, RR, false>(R, local % nbx, (int)(local / nbx), 0, sv)
+    RVEA_M_DISPATCH(R.m, RVEA_BA);  // uniform
+#undef RVEA_BA
 }
-template <int MD, bool GAMMA>
+// every objective count in one launch: the registers allow eight waves per SIMD
+// for each (m = 5 and 8 of sixteen served runs: 18.1 and 20.8 us apart, 22.2
+// together; with scratch of its own for each count, 28 KB of LDS, 48.6)
 __global__ __launch_bounds__(64) void kb_rerank(const RunView *runs, const Span *sp, int n)
 {
     const int s = find_span(sp, n, blockIdx.x);
     const RunView &R = runs[sp[s].run];
-    rerank_body<MD, GAMMA, kBatchRows>(R, blockIdx.x - sp[s].start, 0);
+    const int64_t bx = blockIdx.x - sp[s].start;
+    __shared__ alignas(16) unsigned char buf[sizeof(RerankLds<kMaxM, kBatchRows>)];  // the largest
+#define RVEA_BR(MV) \
+    rerank_body<MV, false, kBatchRows>(R, bx, 0, *reinterpret_cast<RerankLds<MV, kBatchRows> *>(buf))
+    RVEA_M_DISPATCH(R.m, RVEA_BR);  // uniform
+#undef RVEA_BR
 }
 // the batched gamma passes, U blocks per workgroup (U = kSkipBlocks when
 // the launch has blocks enough to fill the device U times over: most
@@ -969,7 +1012,8 @@ __global__ __launch_bounds__(256) void kb_gamma_assoc(const RunView *runs, const
                                                       int64_t total)
 {
     span_blocks<U>(runs, sp, n, total, gamma_open, [](const RunView &R, int64_t local, int nbx) {
-        assoc_body<MD, RR, true>(R, local % nbx, (int)(local / nbx), 1);
+        __shared__ float4 sv[kTileVectors * vector_quads(MD)];
+        assoc_body<MD, RR, true>(R, local % nbx, (int)(local / nbx), 1, sv);
     });
 }
 // (with U > 1 the re-rank body is called, not inlined: inlined U times it
@@ -977,17 +1021,20 @@ __global__ __launch_bounds__(256) void kb_gamma_assoc(const RunView *runs, const
 template <int MD>
 __device__ __attribute__((noinline)) void gamma_rerank_call(const RunView &R, int64_t local)
 {
-    rerank_body<MD, true, kBatchRows>(R, local, 1);
+    __shared__ RerankLds<MD, kBatchRows> L;
+    rerank_body<MD, true, kBatchRows>(R, local, 1, L);
 }
 template <int MD, int U>
 __global__ __launch_bounds__(64) void kb_gamma_rerank(const RunView *runs, const Span *sp, int n,
                                                       int64_t total)
 {
     span_blocks<U>(runs, sp, n, total, gamma_open, [](const RunView &R, int64_t local, int) {
-        if constexpr (U == 1)
-            rerank_body<MD, true, kBatchRows>(R, local, 1);
-        else
+        if constexpr (U == 1) {
+            __shared__ RerankLds<MD, kBatchRows> L;
+            rerank_body<MD, true, kBatchRows>(R, local, 1, L);
+        } else {
             gamma_rerank_call<MD>(R, local);
+        }
     });
 }
 __global__ __launch_bounds__(256) void kb_newpop(const RunView *runs, const Span *sp, int n)
@@ -1003,17 +1050,6 @@ __global__ __launch_bounds__(kTurnBlock) void kb_turn(const RunView *runs, const
 
 // ------------------------------------------------------------- launchers
 static unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
-
-#define RVEA_M_DISPATCH(MVAL, CALL)                                                          \
-    switch (MVAL) {                                                                          \
-    case 2: CALL(2); break;                                                                  \
-    case 3: CALL(3); break;                                                                  \
-    case 4: CALL(4); break;                                                                  \
-    case 5: CALL(5); break;                                                                  \
-    case 6: CALL(6); break;                                                                  \
-    case 7: CALL(7); break;                                                                  \
-    default: CALL(8); break;                                                                 \
-    }
 
 // association launch with R.rr rows per lane (1, 2 or 4) and R.KC chunks
 template <bool GAMMA>
@@ -1122,15 +1158,12 @@ hipError_t launch_batch_select(int phase, int cls, const RunView *runs, const Sp
             kb_newpop<<<g, 256, 0, s>>>(runs, sp, n);
         break;
     case BP_ASSOC:
-#define RVEA_BA(MV) kb_assoc<MV, RR, false><<<g, 256, 0, s>>>(runs, sp, n)
-        RVEA_M_DISPATCH(cls, RVEA_BA);
-#undef RVEA_BA
+        if (cls == 1)  // float4s of a vector
+            kb_assoc<1, RR><<<g, 256, 0, s>>>(runs, sp, n);
+        else
+            kb_assoc<2, RR><<<g, 256, 0, s>>>(runs, sp, n);
         break;
-    case BP_RERANK:
-#define RVEA_BR(MV) kb_rerank<MV, false><<<g, 64, 0, s>>>(runs, sp, n)
-        RVEA_M_DISPATCH(cls, RVEA_BR);
-#undef RVEA_BR
-        break;
+    case BP_RERANK: kb_rerank<<<g, 64, 0, s>>>(runs, sp, n); break;
     case BP_GAMMA_ASSOC:
     case BP_GAMMA_RERANK: {
         const bool wide = blocks >= (int64_t)kSkipBlocks * kFillBlocks;

@@ -8,6 +8,8 @@
 //               |V0_j o r| with r the survivors' per-objective range; left
 //               unchanged if some range is not positive and finite
 //   k_vec_aux   float copy of V (padded rows) and row norms
+#include <algorithm>
+
 #include "rvea_dev.h"
 #include "rvea_index.h"
 #include "rvea_internal.h"
@@ -177,14 +179,14 @@ int batch_phase_class(int phase, const RunView &R)
 {
     if (phase == BP_OFFSPRING && R.op != OP_GA) return operator_class(R);
     if (phase == BP_OFFSPRING)
-        return offspring_segment(R.d, R.N) |
+        return std::min(offspring_segment(R.d, R.N), 32) |  // 32 and 64 lanes: one launch
                (R.eta_c == 20.0 && R.eta_m == 20.0 ? kDefaultIndices : 0);
-    if (phase == BP_ASSOC && R.gG > 0) return kIndexedClass | R.m;
+    if (phase == BP_ASSOC && R.gG > 0) return kIndexedClass;
+    if (phase == BP_RERANK) return 0;
     if (phase == BP_NEWPOP) return R.turn;
     if (phase == BP_GRID_CELLS) return R.m;  // the grid's cells, or the line's gamma
-    if (phase == BP_ASSOC || phase == BP_RERANK || phase == BP_GAMMA_ASSOC ||
-        phase == BP_GAMMA_RERANK)
-        return R.m;
+    if (phase == BP_ASSOC) return R.m <= 4 ? 1 : 2;  // float4s of a vector
+    if (phase == BP_GAMMA_ASSOC || phase == BP_GAMMA_RERANK) return R.m;
     return 0;
 }
 

@@ -1360,7 +1360,7 @@ rvea_status rebuild_plan(rvea_batch b)
     BHIPCHK(b, hipStreamSynchronize(b->stream));
     const int n = (int)b->runs.size();
     // Vector chunks of the full-scan launches: one length for the runs of a
-    // launch (an objective count), so that a launch of all their (row, vector)
+    // launch (a vector width), so that a launch of all their (row, vector)
     // pairs has about kBatchGroups workgroups of 1,024 rows, within the tile, the
     // 32 tiles that a chunk may have and the chunks that the run's buffers hold.
     // A few runs need the chunks for parallelism; many fill the device without,
@@ -1369,11 +1369,11 @@ rvea_status rebuild_plan(rvea_batch b)
     // passes (rows = vectors) have their own lengths.
     constexpr int64_t kBatchGroups = 1024;
     std::vector<RunView> views(n), gviews(n);
-    int64_t pairs[kMaxM + 1] = {}, gpairs[kMaxM + 1] = {};
+    int64_t pairs[3] = {}, gpairs[kMaxM + 1] = {};
     for (int i = 0; i < n; ++i) {
         const RunView &v = b->runs[i]->R;
         if (v.gG > 0) continue;
-        pairs[v.m] += v.M * v.K;
+        pairs[v.m <= 4 ? 1 : 2] += v.M * v.K;
         gpairs[v.m] += v.K * v.K;
     }
     for (int i = 0; i < n; ++i) {
@@ -1386,7 +1386,7 @@ rvea_status rebuild_plan(rvea_batch b)
             v.CS = (int)cs;
             v.KC = (int)((v.K + cs - 1) / cs);
         };
-        chunk(views[i], pairs[views[i].m]);
+        chunk(views[i], pairs[views[i].m <= 4 ? 1 : 2]);
         chunk(gviews[i], gpairs[gviews[i].m]);
     }
     std::vector<Span> spans;

@@ -19,8 +19,8 @@ constexpr int kOffBlock = 64;  // threads per workgroup of the offspring kernels
 // kDefaultIndices when the run has the default distribution indices
 constexpr int kSegMask = 0xff, kDefaultIndices = 0x100;
 
-int pick_segment(int d);                 // lanes per individual (initialization)
-int offspring_segment(int d, int64_t N);  // lanes per parent pair
+__host__ __device__ int pick_segment(int d);                 // lanes per individual (initialization)
+__host__ __device__ int offspring_segment(int d, int64_t N);  // lanes per parent pair
 int offspring_splits(int d, int64_t N);   // segments per parent pair
 int64_t offspring_finish_blocks(const RunView &R);
 int assoc_rows_per_block();
@@ -80,8 +80,8 @@ enum BatchPhase {
 // blocks; kFillBlocks workgroups fill the device several times over
 constexpr int kSkipBlocks = 8;
 constexpr int64_t kFillBlocks = 2048;
-// class of the indexed association launches (runs with an index of V), with
-// the objective count; the full-scan association classes are the counts alone
+// class of the indexed association launch (runs with an index of V); the
+// full-scan association classes are the objective counts
 constexpr int kIndexedClass = 0x100;
 // the gamma passes run over a view with the gamma pass's own vector chunks
 inline bool batch_phase_gamma(int phase)

@@ -270,3 +270,35 @@ def test_batch_of_different_periods_equals_alone(P):
             batch.retire(r)
             r.close()
         batch.close()
+
+
+# one launch for several classes of runs: every objective count scanned in full
+# (vectors of one and of two float4s), both indices, 32 and 64 lanes per pair
+@pytest.mark.parametrize("eta", [20.0, 15.5])
+@pytest.mark.parametrize("index", [True, False])
+def test_runs_that_share_launches_equal_alone(P, index, eta):
+    shapes = [(2, 300, 200, 200), (2, 300, 2200, 2201), (3, 512, 2210, 2211), (3, 270, 105, 105),
+              (4, 60, 165, 165), (5, 300, 2380, 2380), (6, 2100, 70, 252), (7, 41, 84, 84), (8, 17, 120, 120)]
+
+    def made():
+        runs = [P.Run(1 + i % 3, m, d, N, K, seed=i, params=P.default_params(t_max=30, eta_m=eta))
+                for i, (m, d, N, K) in enumerate(shapes)]
+        if not index:
+            for r in runs:
+                if r.m <= 3:
+                    r.set_index(False)
+        return runs
+
+    alone, mixed = made(), made()
+    batch = P.Batch(16)
+    for r in mixed:
+        batch.admit(r)
+    for _ in range(7):
+        batch.step()
+    for r in mixed:
+        batch.retire(r)
+    for a, b in zip(alone, mixed):
+        a.run(7)
+        assert same(a, b) is None, (a.m, a.d, same(a, b))
+        a.close()
+        b.close()
