@@ -346,18 +346,6 @@ __global__ __launch_bounds__(kBlock) void k_init(RunView R)
     }
 }
 
-// empty slots N..K-1 and the generation counter
-__global__ void k_init_empty(RunView R)
-{
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x + R.N;
-    if (j < R.K) {
-        R.valids[j] = 0;  // population 0
-        R.slot_rows[j] = (int32_t)j;
-        for (int k = 0; k < R.m; ++k) R.Fms[j * R.m + k] = __int_as_float(0x7fc00000);
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *R.t_done = 0;
-}
-
 // --------------------------------------------------------------- offspring
 // Mutation sites of child o: events e = 0,1,... with counter (e, o, t,
 // TAG_MUT); U = 1 - u53(w0,w1) in (0,1], gap = floor(log U / log(1-p)),
@@ -942,9 +930,6 @@ hipError_t launch_init(const RunView &R, hipStream_t s)
     } else if (R.N > 0) {
         RVEA_SEG_DISPATCH(S, k_init, R.N, s, R);
     }
-    const int64_t empty = R.K - R.N;
-    const unsigned g = (unsigned)((empty > 0 ? empty : 1) + 255) / 256;
-    k_init_empty<<<g, 256, 0, s>>>(R);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && R.problem == kPolicy)  // objectives of the initial slots by rollouts
         e = launch_rollout(R, s, false);

@@ -234,9 +234,6 @@ struct rvea_batch_s {
 
 namespace {
 
-// the index's scaling before any adaptation (and after a host-set V)
-const double kUnitScale[3] = {1.0, 1.0, 1.0};
-
 // message of the last failed rvea_create on this thread (no handle exists)
 thread_local char g_create_err[512] = "";
 
@@ -519,8 +516,8 @@ rvea_status create_run(int problem, int m, int d, int64_t N, int64_t K, uint64_t
     R.t_done = (int64_t *)(w + L.off[B_TDONE]);
     R.counters = (unsigned long long *)(w + L.off[B_COUNTERS]);
     R.vchanged = (int32_t *)(w + L.off[B_VCHANGED]);
-    hipError_t e = hipMemsetAsync(R.zbits, 0xff, (size_t)3 * m * 4, r->stream);
-    if (e == hipSuccess && problem == kPolicy) {
+    hipError_t e = hipSuccess;
+    if (problem == kPolicy) {
         float *lq = (float *)(w + L.off[B_LQ]);
         R.lq = lq;
         R.lq_E = sys->E;
@@ -536,22 +533,9 @@ rvea_status create_run(int problem, int m, int d, int64_t N, int64_t K, uint64_t
         if (e == hipSuccess) e = hipStreamSynchronize(r->stream);
     }
 
-    if (e == hipSuccess)
-        e = hipMemsetAsync(R.counters, 0, 3 * sizeof(unsigned long long), r->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(R.vchanged, 0, 4, r->stream);
     if (e == hipSuccess && R.Vel)  // every individual starts at rest
         e = hipMemsetAsync(R.Vel, 0, (size_t)(K + N) * L.ld * 4, r->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(R.ndone, 0, 4, r->stream);
-    if (e == hipSuccess)
-        e = hipMemsetAsync(R.stamp, 0xff, (size_t)(K + N) * 4, r->stream);
-    if (e == hipSuccess && R.gG > 0) {  // the index starts unscaled, with no vectors counted
-        e = hipMemcpyAsync(R.gr, kUnitScale, (size_t)m * sizeof(double), hipMemcpyHostToDevice,
-                           r->stream);
-        if (e == hipSuccess)
-            e = hipMemsetAsync(R.gcnt, 0, (size_t)index_cells(m, R.gG) * 4, r->stream);
-        if (e == hipSuccess) e = hipMemsetAsync(R.gtot, 0, 32, r->stream);
-    }
-    if (e == hipSuccess) e = launch_lattice(R, r->stream, r->H);
+    if (e == hipSuccess) e = launch_lattice(R, r->stream, r->H);  // with the fresh state
     if (e == hipSuccess)  // the index's build gives gamma too
         e = R.gG > 0 ? launch_grid_build(R, r->stream) : launch_gamma(R, r->stream, 1);
     if (e == hipSuccess) e = launch_init(R, r->stream);
