@@ -220,9 +220,12 @@ __device__ __forceinline__ double wave_sum(double v)
 // and stops as soon as Y_t <= y_t: Y_t only falls, so every
 // further strip adds nothing; on a front of n points that is some sqrt(n)
 // positions past t.  Skipped strips add exact zeros, so the term is the full
-// pass's.  10,011 rows: 302 -> 64 us, now the longest right scans (rows with
-// small y_t), a chain of wavefront minima.
-constexpr int kTermRows = 16;
+// pass's.  10,011 rows: 302 -> 47 us, now the longest right scans (rows with
+// small y_t), a chain of wavefront minima.  More rows share the left pass's
+// reads but a workgroup lasts as long as the longest scan of its rows: 64 us
+// with 16 rows, 52 with 8, 47 with 4, 55 with 2; from the last rows on, whose left
+// passes are the longest, 50 against 46 (8 rows).
+constexpr int kTermRows = 4;
 __global__ __launch_bounds__(64 * kTermRows) void k_hv_terms(int64_t n, HvSpace S)
 {
     __shared__ double left_of[kTermRows][kTermRows];
