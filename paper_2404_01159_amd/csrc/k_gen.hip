@@ -274,10 +274,12 @@ __device__ __forceinline__ double sbx_half_beta(uint32_t u, int nrt)
     const bool lo = u < 0x800000u;
     const uint32_t v = lo ? u : 0x1000000u - u;
     // a 2^(n-2): v times a power of two, exact in binary32 (n <= 64)
-    const float af = (float)v * __int_as_float((n - 25 + 127) << 23);
+    const float one = __int_as_float((n - 25 + 127) << 23);
+    const float af = (float)v * one;
     const float ninv = 1.0f / (float)n;
-    // log2(a) = log2(af) - (n - 2); the minimum keeps u = 0 finite
-    const float l = fminf(fmaf(-ninv, __builtin_amdgcn_logf(af), ((float)(n - 2)) * ninv - 1.0f), 2.0f);
+    // log2(a) = log2(af) - (n - 2); u = 0 takes the root of v = 1, which keeps zh
+    // and its power finite (the exponent may reach 23/n - 1: no other bound)
+    const float l = fmaf(-ninv, __builtin_amdgcn_logf(fmaxf(af, one)), ((float)(n - 2)) * ninv - 1.0f);
     const double zh = (double)__builtin_amdgcn_exp2f(l);
     double p;  // zh^(n-1)
     if (n == 21) {
