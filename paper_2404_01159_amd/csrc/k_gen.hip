@@ -15,6 +15,7 @@
 // are summed on the fly so evaluation costs no extra pass over the genes.
 #include "rvea_dev.h"
 #include "rvea_problems.h"
+#include "rvea_spread.h"
 #include "rvea_internal.h"
 
 namespace rvea {
@@ -153,23 +154,6 @@ __device__ __forceinline__ void stamp_body(const RunView &R, int64_t bx)
 __global__ __launch_bounds__(256) void k_stamp(RunView R) { stamp_body(R, blockIdx.x); }
 
 // --------------------------------------------------------------- helpers
-// z^n for a positive integer n (square and multiply, n uniform); the
-// default distribution index eta = 20 (n = 21) gets straight-line code
-__device__ __forceinline__ double ipow(double z, int n)
-{
-    if (n == 21) {
-        const double z2 = z * z, z4 = z2 * z2, z8 = z4 * z4, z16 = z8 * z8;
-        return (z16 * z4) * z;
-    }
-    double r = 1.0, b = z;
-    while (n) {
-        if (n & 1) r *= b;
-        n >>= 1;
-        if (n) b *= b;
-    }
-    return r;
-}
-
 // 1/z for z in (0, 4): hardware estimate plus two Newton-Raphson steps,
 // within one binary64 ulp
 __device__ __forceinline__ double recip(double z)
@@ -254,19 +238,15 @@ __device__ __attribute__((noinline)) double sbx_beta_pow(double mc, double eta)
 
 // Half of the spread factor, B/2, from the 24-bit variate u (M_c = u 2^-24) for
 // a positive integer n = eta + 1 (NR > 0: n = NR fixed at compile time).  Both
-// branches are one root of a = v 2^-23, v = u below 1/2 and 2^24 - u above: with
-// z a binary32 estimate of a^(-1/n), t = a z^(n-1) and e = 1 - t z (a few 1e-6),
-//   above 1/2: a^(-1/n) = z (1 - e)^(-1/n),
-//   below:     a^(1/n)  = t (1 - e)^(-(n-1)/n)
-// (the rounding of t enters e too and cancels but for its n-th part), each by
-// its second-order expansion (the third term is below 1e-16), so no reciprocal
-// is taken.  z is halved (zh) and a scaled by 2^(n-2) (th = t/2), which gives
-// B/2 without a product; u = 0 (spread 0) comes out as th = 0 exactly.  With the
+// branches are one root of a = v 2^-23, v = u below 1/2 and 2^24 - u above, from a
+// binary32 estimate of a^(-1/n) (half_spread), so no reciprocal is taken.  The
+// estimate is halved and a scaled by 2^(n-2), which gives B/2 without a product;
+// u = 0 (spread 0) comes out as 0 exactly.  With the
 // reciprocal and its two Newton steps, the signs as factors and two-step clips
 // and exclusive-ors the streaming loop had 480 vector instructions per quad;
 // 343 so: 911 -> 844 us at 100,128 x 5,000 (a copy of the same bytes: 840),
 // 23.2 -> 21.4 us at 10,011 x 500.  Genes equal the rounded 64-bit value as
-// often as before (all of 6 million).
+// often as before (all of 6 million at eta = 20).
 template <int NR>
 __device__ __forceinline__ double sbx_half_beta(uint32_t u, int nrt)
 {
@@ -280,26 +260,7 @@ __device__ __forceinline__ double sbx_half_beta(uint32_t u, int nrt)
     // log2(a) = log2(af) - (n - 2); u = 0 takes the root of v = 1, which keeps zh
     // and its power finite (the exponent may reach 23/n - 1: no other bound)
     const float l = fmaf(-ninv, __builtin_amdgcn_logf(fmaxf(af, one)), ((float)(n - 2)) * ninv - 1.0f);
-    const double zh = (double)__builtin_amdgcn_exp2f(l);
-    double p;  // zh^(n-1)
-    if (n == 21) {
-        const double z2 = zh * zh, z4 = z2 * z2, z8 = z4 * z4, z16 = z8 * z8;
-        p = z16 * z4;
-    } else {
-        p = ipow(zh, n - 1);
-    }
-    const double th = (double)af * p;             // t / 2
-    const double e4 = fma(-th, zh, 0.25);         // e / 4
-    const double dn = (double)n;
-    // coefficients of e4: 4 c1 and 16 c2, c1 = s/n, c2 = s (s + n)/(2 n^2) with
-    // s = n - 1 below 1/2 and 1 above (the second needs 20 bits only)
-    const double c1 = lo ? 4.0 * (dn - 1.0) / dn : 4.0 / dn;
-    const double c2 = __hiloint2double(
-        lo ? __double2hiint(8.0 * (dn - 1.0) * (2.0 * dn - 1.0) / (dn * dn))
-           : __double2hiint(8.0 * (dn + 1.0) / (dn * dn)),
-        0);
-    const double base = lo ? th : zh;
-    return fma(base * e4, fma(e4, c2, c1), base);
+    return half_spread<NR>(lo, af, (double)__builtin_amdgcn_exp2f(l), n);
 }
 
 // ------------------------------------------------------------------- init
