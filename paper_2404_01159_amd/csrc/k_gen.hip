@@ -15,7 +15,7 @@
 // are summed on the fly so evaluation costs no extra pass over the genes.
 #include "rvea_dev.h"
 #include "rvea_problems.h"
-#include "rvea_spread.h"
+#include "rvea_variation.h"
 #include "rvea_internal.h"
 
 namespace rvea {
@@ -313,12 +313,12 @@ __global__ __launch_bounds__(kBlock) void k_init(RunView R)
 // Mutation sites of child o: events e = 0,1,... with counter (e, o, t,
 // TAG_MUT); U = 1 - u53(w0,w1) in (0,1], gap = floor(log U / log(1-p)),
 // site_e = site_{e-1} + 1 + gap while it stays below d; M_mut = u53(w2,w3).
-// Both children of a pair are drawn at once, S/2 lanes each per round.  rlq is
-// 1 / log(1-p); prefix sums by DPP and counts by ballots (shuffles through LDS, a
+// Both children of a pair are drawn at once, S/2 lanes each per round.  lq is
+// log(1-p); prefix sums by DPP and counts by ballots (shuffles through LDS, a
 // dozen a round, were half of the 2.5 us that the sites took a wavefront).
 template <int S>
 __device__ void draw_sites(const RunView &R, uint32_t t, int64_t o1, int64_t o2, bool has2,
-                           double rlq, int lane, int32_t *s1, double *m1, int32_t *s2, double *m2,
+                           double lq, int lane, int32_t *s1, double *m1, int32_t *s2, double *m2,
                            int *n1, int *n2)
 {
     constexpr int H2 = S / 2;
@@ -339,10 +339,7 @@ __device__ void draw_sites(const RunView &R, uint32_t t, int64_t o1, int64_t o2,
         if (!done) {
             const W4 w = draw(R, e, (uint32_t)o, t, TAG_MUT);
             const double U = 1.0 - unif53(w.w[0], w.w[1]);
-            double q = log(U) * rlq;
-            if (!(q >= 0.0)) q = 0.0;
-            const double gap = floor(q);
-            step = gap >= (double)R.d ? R.d + 1 : 1 + (int)gap;
+            step = 1 + mutation_gap(log(U), lq, R.d);
             mag = unif53(w.w[2], w.w[3]);
         }
         const int pos = cur + group_incl_scan<H2>(step, hl);
@@ -466,9 +463,9 @@ __device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx, Off
     int n1 = 0, n2 = 0;
     const double pr = R.p_m / (double)R.d;
     if (pr > 0.0) {
-        const double rlq = 1.0 / log1p(-(pr > 1.0 ? 1.0 : pr));
+        const double lq = log1p(-(pr > 1.0 ? 1.0 : pr));
         if (active)
-            draw_sites<S>(R, t, o1, o2, has2, rlq, lane, L.sites[seg][0], L.mags[seg][0],
+            draw_sites<S>(R, t, o1, o2, has2, lq, lane, L.sites[seg][0], L.mags[seg][0],
                           L.sites[seg][1], L.mags[seg][1], &n1, &n2);
     }
     wave_sync();

@@ -1,5 +1,5 @@
-// rvea_spread.h -- the spread factor's arithmetic in binary64, for the device and
-// for host checks of its error.
+// rvea_variation.h -- binary64 arithmetic of crossover and mutation, for the
+// device and for host checks of its error.
 #pragma once
 
 #include <cmath>
@@ -81,6 +81,17 @@ RVEA_HD double half_spread(bool lo, float af, double zh, int n)
     }
     const double base = lo ? th : zh;
     return std::fma(base * e4, std::fma(e4, c2, c1), base);
+}
+
+// Genes between two mutation sites: floor(log U / log(1-p)), at most d.  A
+// quotient, not a product with the reciprocal, whose second rounding can leave
+// the floor one lower at whole numbers.
+RVEA_HD int mutation_gap(double logu, double lq, int d)
+{
+    double q = logu / lq;
+    if (!(q >= 0.0)) q = 0.0;
+    q = std::floor(q);
+    return q >= (double)d ? d : (int)q;
 }
 
 }  // namespace rvea

@@ -1,11 +1,13 @@
-// Largest relative error of half_spread (rvea_spread.h) against long double, in
-// units of 2^-53, for n = argv[1]: all variates that are a multiple of argv[2],
-// and the 64 next to 0, 1/2 and 1.  The binary32 estimate is that of the device
-// with correctly rounded log2 and exp2.
+// Host checks of rvea_variation.h.
+//   spread n step   largest relative error of half_spread against long double, in
+//                   units of 2^-53: all variates that are a multiple of step, and
+//                   the 64 next to 0, 1/2 and 1.  The binary32 estimate is that of
+//                   the device with correctly rounded log2 and exp2.
+//   gap             "log(U) log(1-p) d" lines from the input, a gap each
 #include <cstdio>
 #include <cstdlib>
 
-#include "rvea_spread.h"
+#include "rvea_variation.h"
 
 static double error_of(uint32_t u, int n)
 {
@@ -24,9 +26,16 @@ static double error_of(uint32_t u, int n)
 
 int main(int argc, char **argv)
 {
-    if (argc != 3) return 2;
-    const int n = std::atoi(argv[1]);
-    const uint32_t step = (uint32_t)std::atoi(argv[2]);
+    if (argc == 2) {
+        double logu, lq;
+        int d;
+        while (std::scanf("%la %la %d", &logu, &lq, &d) == 3)
+            std::printf("%d\n", rvea::mutation_gap(logu, lq, d));
+        return 0;
+    }
+    if (argc != 4) return 2;
+    const int n = std::atoi(argv[2]);
+    const uint32_t step = (uint32_t)std::atoi(argv[3]);
     double worst = 0.0;
     auto take = [&](uint32_t u) {
         const double e = error_of(u, n);
