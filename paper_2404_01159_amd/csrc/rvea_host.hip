@@ -991,12 +991,15 @@ rvea_status rvea_set_velocities(rvea_run r, const float *Vel)
     if (st != RVEA_OK) return st;
     std::vector<int32_t> rows(R.K);
     HIPCHK(r, hipMemcpy(rows.data(), slot_rows_at(R, td), R.K * 4, hipMemcpyDeviceToHost));
+    // an empty slot's row may be another individual's by now
+    std::vector<uint8_t> vh(R.K);
+    HIPCHK(r, hipMemcpy(vh.data(), valids_at(R, td), R.K, hipMemcpyDeviceToHost));
     // the pool through host memory: the slots' rows are scattered over it
     const size_t pool_bytes = (size_t)(R.K + R.N) * R.ld * 4;
     std::vector<float> pool((size_t)(R.K + R.N) * R.ld);
     HIPCHK(r, hipMemcpy(pool.data(), R.Vel, pool_bytes, hipMemcpyDeviceToHost));
     for (int64_t j = 0; j < R.K; ++j)
-        std::memcpy(pool.data() + (size_t)rows[j] * R.ld, Vel + j * R.d, (size_t)R.d * 4);
+        if (vh[j]) std::memcpy(pool.data() + (size_t)rows[j] * R.ld, Vel + j * R.d, (size_t)R.d * 4);
     HIPCHK(r, hipMemcpy(R.Vel, pool.data(), pool_bytes, hipMemcpyHostToDevice));
     return RVEA_OK;
 }

@@ -291,3 +291,20 @@ def test_velocities_only_for_swarms(P):
     with pytest.raises(P.RveaError):
         g.get_velocities()
     g.close()
+
+
+@pytest.mark.parametrize("op", ["pso", "cso"])
+@pytest.mark.parametrize("K", [300, 16400])
+def test_velocities_set_with_empty_slots(P, op, K):
+    """Rows given for empty slots are ignored: those slots' places in the pool
+    are other individuals' after some generations."""
+    run = P.Run(1, 2, 24, K, K, seed=7, params=P.default_params(op, t_max=20, fr=0.2))
+    run.run(3)
+    valid = run.get_state(genes=False)["valid"].astype(bool)
+    assert not valid.all()
+    V = np.random.default_rng(3).random((K, 24), np.float32)
+    run.set_velocities(V)
+    got = run.get_velocities()
+    run.close()
+    assert np.array_equal(got[valid], V[valid])
+    assert not got[~valid].any()
