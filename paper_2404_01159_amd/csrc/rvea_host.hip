@@ -1285,10 +1285,14 @@ rvea_status rvea_autotune(rvea_run r, rvea_tuning *out)
     R.gCS = g_cs;
     R.gKC = (int)((R.K + g_cs - 1) / g_cs);
     R.gG = gG0;
-    HIPCHK(r, hipMemcpy(R.counters, saved, sizeof saved, hipMemcpyHostToDevice));
-    // the trial's preparation handed out free rows: the real one starts over
-    if (!R.turn) HIPCHK(r, hipMemsetAsync(R.freecnt, 0, 4, r->stream));
+    // the trial lowered the next generation's minima (per vector, ideal point) and
+    // handed out rows for children that need not come again (velocities set
+    // meanwhile): the preparation starts over
+    HIPCHK(r, hipMemsetAsync(R.zbits, 0xff, (size_t)3 * R.m * 4, r->stream));
+    HIPCHK(r, launch_stamp(R, r->stream));
+    if (R.turn) HIPCHK(r, launch_prepare(R, r->stream));
     HIPCHK(r, hipStreamSynchronize(r->stream));
+    HIPCHK(r, hipMemcpy(R.counters, saved, sizeof saved, hipMemcpyHostToDevice));
     drop_graphs(r);            // captured with the old launch shapes
     r->has_selection = false;  // the trial overwrote the last selection's buffers
     if (out) {

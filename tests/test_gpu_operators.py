@@ -308,3 +308,32 @@ def test_velocities_set_with_empty_slots(P, op, K):
     run.close()
     assert np.array_equal(got[valid], V[valid])
     assert not got[~valid].any()
+
+
+# vectors on both sides of the rule by which the kernel that writes the new
+# population also prepares the next generation
+@pytest.mark.parametrize("op", ["pso", "cso"])
+@pytest.mark.parametrize("K", [300, 16400])
+@pytest.mark.parametrize("at", [0, 3])
+def test_velocities_set_after_a_trial(P, op, K, at):
+    """A run tuned and then given other velocities goes on as one that was not
+    tuned: the children that the tuning's trial drew leave no minima behind."""
+    prm = P.default_params(op, t_max=20, fr=0.2)
+    seen = []
+    for tuned in (False, True):
+        run = P.Run(1, 2, 24, K, K, seed=7, params=prm)
+        run.run(at)
+        if tuned:
+            run.autotune()
+        r = np.random.default_rng(3)
+        run.set_velocities((2 * r.random((K, 24)) - 1).astype(np.float32))
+        run.run(1)
+        sel = run.get_selection()
+        run.run(2)
+        seen.append((sel, run.get_state()))
+        run.close()
+    (sa, a), (sb, b) = seen
+    for k in ("zstar", "assoc", "apd", "surv"):
+        assert np.array_equal(sa[k], sb[k]), k
+    for k in ("X", "F", "valid", "V", "gamma"):
+        assert np.array_equal(a[k], b[k], equal_nan=True), k
