@@ -76,6 +76,19 @@ constexpr int kSlot = 24;      // list records per cell (longer lists: a full sc
 constexpr int kChamps = 6;     // champions per cell: five vertices and the centre
 constexpr int kGridRowLanes = 4;  // lanes per row of the association
 constexpr double kDomMargin = 1e-12;
+// Vectors that a scan for gamma takes at once: with eight the shared scans of
+// 100,128 vectors take 2.5 ms instead of 3.7, but the kernel has a wavefront per
+// SIMD less and every rebuild pays for it (186 instead of 170 us there).
+constexpr int kScan = 4;
+constexpr int kGammaLanes = 4;    // lanes per vector of the line's gamma
+constexpr int kKeepGamma = 2;     // gate of a build that leaves gamma as it is
+// Scaling below which the launch shares the scans for gamma: from about there on
+// cells are too flat for their neighbourhoods to hold the nearest vector, and most
+// vectors are left.  Each cell scanning its own / shared, microseconds of an
+// adaptation: 100,128 vectors at ranges 1 : 0.15 : 0.15 757 / 3,730, 1 : 1 : 0.1
+// 5,351 / 3,700, 1 : 1e-4 : 1e-4 7,764 / 3,640; 10,011 vectors at 1 : 0.15 : 0.15
+// 88 / 68, 1 : 1 : 0.03 153 / 70.
+constexpr double kFlat = 0.125;
 
 struct D3 {
     double x, y, z;
@@ -315,21 +328,6 @@ __device__ __forceinline__ void grid_fill_body(const RunView &R, int64_t bx, int
     reinterpret_cast<double4 *>(R.gvh)[p] = make_double4(R.V[j * 2], R.V[j * 2 + 1], 0.0, R.vn[j]);
 }
 
-// Eq. 5's gamma of vector id by the whole wavefront: the largest binary64
-// cosine to another vector that is not parallel to it, over all vectors (as the
-// full gamma pass computes it).
-// (Out of line: rare, and inlined it would keep the callers' registers; it takes
-// the arrays, not the run's view, which would have to be copied to memory.)
-template <int M>
-__device__ __attribute__((noinline)) void gamma_scan_call(const double *V, const double *vn,
-                                                          double *gamma, int64_t K, int32_t id,
-                                                          int lane);
-template <int M>
-__device__ __forceinline__ void gamma_scan(const RunView &R, int32_t id, int lane)
-{
-    gamma_scan_call<M>(R.V, R.vn, R.gamma, R.K, id, lane);
-}
-
 // Wavefront-wide minimum / best (largest value, lowest id on ties) over
 // the 64 lanes (every lane active): the pairings of partner32 within each
 // half, then the two halves' results read out and combined (the result is
@@ -348,23 +346,100 @@ __device__ __forceinline__ double wave_fmin(double v)
                                       __builtin_amdgcn_readlane(__double2loint(v), 32));
     return fmin(a, b);
 }
-template <int M>
-__device__ __attribute__((noinline)) void gamma_scan_call(const double *V, const double *vn,
-                                                          double *gamma, int64_t K, int32_t id,
-                                                          int lane)
+__device__ __forceinline__ double first_lane(double v)
 {
-    double vi[M], best = -INFINITY;
-    for (int k = 0; k < M; ++k) vi[k] = V[(int64_t)id * M + k];
-    const double vni = vn[id];
-    for (int64_t j = lane; j < K; j += 64) {
-        double s = vi[0] * V[j * M];
-        for (int k = 1; k < M; ++k) s = fma(vi[k], V[j * M + k], s);
-        const double cv = s / (vni * vn[j]);
-        if (j != id && cv < 1.0) best = fmax(best, cv);
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                            __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+
+// Eq. 5's gamma of up to kScan vectors by the whole wavefront, the ids that the
+// lowest lanes of `mask` hold: the largest binary64 cosine to another vector that
+// is not parallel to it, over all vectors (as the full gamma pass computes it).
+// The vectors themselves are scalars; a loaded vector serves all, and a cosine
+// is divided out only where it may be above the best so far.  The 64 vectors
+// around the id come first: in a lattice they hold its nearest or nearly so, and
+// few divisions are left.
+template <int M>
+__device__ __forceinline__ void gamma_block(const double *V, const double *vn, double *gamma,
+                                            int64_t K, unsigned long long mask, int32_t id, int lane)
+{
+    constexpr int B = kScan;
+    int32_t ids[B], mine = -1;
+    double vi[B][M], vni[B], best[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {  // the last one again where the mask has fewer
+        ids[b] = b == 0 || mask ? __builtin_amdgcn_readlane(id, __ffsll(mask) - 1) : ids[b > 0 ? b - 1 : 0];
+        if (mask && lane == b) mine = ids[b];
+        mask &= mask - 1;
+#pragma unroll
+        for (int k = 0; k < M; ++k) vi[b][k] = first_lane(V[(int64_t)ids[b] * M + k]);
+        vni[b] = first_lane(vn[ids[b]]);
     }
-    best = -wave_fmin(-best);
-    if (lane == 0)
-        gamma[id] = best > -INFINITY ? acos(best < -1.0 ? -1.0 : best) : 1.5707963267948966;
+    auto dot = [&](int b, const double (&w)[M]) {
+        double s = vi[b][0] * w[0];
+#pragma unroll
+        for (int k = 1; k < M; ++k) s = fma(vi[b][k], w[k], s);
+        return s;
+    };
+    // a bound that s / n exceeds if its cosine is above the best so far, whatever
+    // the rounding of the products
+    auto below = [](double x) { return x - fabs(x) * 0x1p-50; };
+    double low[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        const int64_t j = (int64_t)ids[b] - 32 + lane;
+        best[b] = -INFINITY;
+        if (j >= 0 && j < K && j != ids[b]) {
+            double w[M];
+#pragma unroll
+            for (int k = 0; k < M; ++k) w[k] = V[j * M + k];
+            const double cv = dot(b, w) / (vni[b] * vn[j]);
+            if (cv < 1.0) best[b] = cv;
+        }
+        best[b] = -wave_fmin(-best[b]);
+        low[b] = below(best[b] * vni[b]);
+    }
+#pragma unroll 1
+    for (int64_t j = lane; j < K; j += 64) {
+        double w[M];
+#pragma unroll
+        for (int k = 0; k < M; ++k) w[k] = V[j * M + k];
+        const double n = vn[j];
+        bool any = false;
+#pragma unroll
+        for (int b = 0; b < B; ++b) any |= fma(-low[b], n, dot(b, w)) > 0.0;
+        if (!any) continue;
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const double s = dot(b, w);
+            if (!(fma(-low[b], n, s) > 0.0) || j == ids[b]) continue;
+            const double cv = s / (vni[b] * n);
+            if (cv < 1.0 && cv > best[b]) {
+                best[b] = cv;
+                low[b] = below(cv * vni[b]);
+            }
+        }
+    }
+    double c = 0.0;
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        const double v = -wave_fmin(-best[b]);
+        if (lane == b) c = v;
+    }
+    if (mine >= 0)
+        gamma[mine] = c > -INFINITY ? acos(c < -1.0 ? -1.0 : c) : 1.5707963267948966;
+}
+
+// the same for every lane of `mask`, whatever their number (last in a kernel:
+// nothing else should be live beside it)
+template <int M>
+__device__ __forceinline__ void gamma_scan(const RunView &R, unsigned long long mask, int32_t id, int lane)
+{
+    while (mask) {  // uniform
+        gamma_block<M>(R.V, R.vn, R.gamma, R.K, mask, id, lane);
+#pragma unroll
+        for (int b = 0; b < kScan; ++b) mask &= mask - 1;
+    }
 }
 
 // The vectors of the (2 kStage + 1)^2 cells around a cell, staged in LDS by
@@ -407,7 +482,7 @@ __device__ __forceinline__ int64_t tri_start(int G, int ci)
 {
     return ci == 0 ? 0 : (int64_t)G + (int64_t)(ci - 1) * (G + 1) - (int64_t)(ci - 1) * ci / 2;
 }
-static int64_t grid_live_cells(int G) { return (int64_t)G + (int64_t)G * (G + 1) / 2 - 1; }
+__host__ __device__ __forceinline__ int64_t grid_live_cells(int G) { return (int64_t)G + (int64_t)G * (G + 1) / 2 - 1; }
 
 // One wavefront per cell (the simplex's cells only, in row order): the
 // neighbourhood staged in LDS; each lane's three entries in binary32 registers
@@ -425,7 +500,7 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
     if (!gate && *R.vchanged == 0) return;
     const int G = R.gG;
     const int lane = threadIdx.x;
-    if (bx >= (int64_t)G + (int64_t)G * (G + 1) / 2 - 1) return;  // uniform
+    if (bx >= grid_live_cells(G)) return;  // uniform
     int ci = 0;  // the row of cell bx: the last row starting at or before it
     for (int hi = G - 1; ci < hi;) {
         const int mid = (ci + hi + 1) >> 1;
@@ -497,20 +572,22 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
     // holds that vector (the nearest staged one is closer than the
     // neighbourhood's boundary: every own vector lies within rho of u_c, so
     // its distance to that boundary is at least u_c's less rho); otherwise
-    // by a scan of all vectors
-    if (full && own_cnt > 0) {  // uniform; own vectors past the bucket by their cell
-        if (own_cnt <= kBucket) {
-            for (int o = 0; o < own_cnt; ++o) gamma_scan<3>(R, R.gvec[(int64_t)c * kBucket + o], lane);
-        } else {
-            for (int64_t j0 = 0; j0 < R.K; j0 += 64) {
-                unsigned long long b = __ballot(j0 + lane < R.K && R.gcell[j0 + lane] == c);
-                for (; b; b &= b - 1) gamma_scan<3>(R, (int32_t)(j0 + __ffsll(b) - 1), lane);
-            }
-        }
-    }
-    {
+    // by a scan of all vectors.  Where many are to be expected (a cell with more
+    // vectors than places, flat scaling) the whole launch shares them evenly, so
+    // that no cell's are one wavefront's: 10,011 vectors of ranges 1 : 1e-3 : 1e-3
+    // under unit scaling took 223 ms with each cell scanning its own, one after the
+    // other, 0.27 so.
+    const bool shared = R.gtot[2] != 0 || fmin(R.gr[0], fmin(R.gr[1], R.gr[2])) < kFlat;
+    // vectors left to scans at the end: `shared` ones, or the lanes of left_mask
+    unsigned long long left_mask = 0;
+    int32_t left_id = 0;
+    if (gate == kKeepGamma || shared) {
+    } else if (full) {
+        left_mask = (1ull << own_cnt) - 1;  // no crowded cell: at most kBucket
+        if (lane < own_cnt) left_id = R.gvec[(int64_t)c * kBucket + lane];
+    } else {
         const int oq0 = __builtin_amdgcn_readlane(incl0 - mine0, own);
-        const int on = full ? 0 : own_cnt;
+        const int on = own_cnt;
         const float lo = bsm - rho - kSlack;
         double gmine = 0.0;  // own vector oq0 + lane: its largest cosine
         bool gok = false;
@@ -536,13 +613,14 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
             gb = -wave_fmin(-gb);
             dmin = fsqrt(__uint_as_float(wave_min(__float_as_uint(dmin))));
             const bool ok = dmin < INFINITY && lo > dmin + 2.0f * kSlack;
-            if (!ok) gamma_scan<3>(R, st.j[o], lane);
             if (lane == o - oq0) {
                 gmine = gb;
                 gok = ok;
             }
         }
         if (gok) R.gamma[st.j[oq0 + lane]] = acos(gmine < -1.0 ? -1.0 : gmine);
+        left_mask = __ballot(lane < on && !gok);
+        if (lane < on) left_id = st.j[oq0 + lane];
     }
     // b: the vector that covers the cell best
     float cover = INFINITY;
@@ -634,6 +712,16 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
         }
     }
     if (full && lane == 0) R.lcnt[c] = -1;
+    // the scans
+    if (gate == kKeepGamma) return;
+    if (!shared) {
+        gamma_scan<3>(R, left_mask, left_id, lane);
+        return;
+    }
+    for (int64_t j = kScan * bx; j < R.K; j += kScan * grid_live_cells(G)) {
+        const int64_t left = R.K - j;
+        gamma_scan<3>(R, (1ull << (left < kScan ? left : kScan)) - 1, (int32_t)(j + lane), lane);
+    }
 }
 
 // ----------------------------------------------------------- association
@@ -883,7 +971,8 @@ __device__ __forceinline__ void assoc_line_body(const RunView &R, int64_t bx)
     atomicMin(&key_of(R, pop + 1)[bj], ((ab >> R.kb) << R.kb) | (unsigned long long)i);
 }
 
-// Eq. 5's gamma of each vector on the line (one lane per vector): the walk
+// Eq. 5's gamma of each vector on the line (by the first of kGammaLanes lanes,
+// which leaves a wavefront few vectors to scan where walks fail): the walk
 // of the association with the vector as the row, skipping itself and the
 // vectors exactly parallel to it (binary64 cosine 1 or more), as the full
 // gamma pass does; the largest cosine's angle (pi/2 without another
@@ -892,8 +981,8 @@ __device__ __forceinline__ void assoc_line_body(const RunView &R, int64_t bx)
 __device__ __forceinline__ void line_gamma_body(const RunView &R, int64_t bx, int gate)
 {
     if (!gate && *R.vchanged == 0) return;
-    const int64_t i = bx * 256 + threadIdx.x;
-    const bool in = i < R.K;
+    const int64_t i = (bx * 256 + threadIdx.x) / kGammaLanes;
+    const bool in = i < R.K && threadIdx.x % kGammaLanes == 0;
     const double f0 = in ? R.V[i * 2] : 1.0, f1 = in ? R.V[i * 2 + 1] : 0.0, nrm = in ? R.vn[i] : 1.0;
     const int G = R.gG;
     const double *r = R.gr;
@@ -930,11 +1019,9 @@ __device__ __forceinline__ void line_gamma_body(const RunView &R, int64_t bx, in
         scan(++hi);
         full = ++steps > kLineWalk;
     }
-    // the wavefront's lanes again together: the vectors left, one by one
-    const int lane = threadIdx.x & 63;
-    for (unsigned long long b = __ballot(full); b; b &= b - 1)
-        gamma_scan<2>(R, (int32_t)(i - lane + __ffsll(b) - 1), lane);
     if (in && !full) R.gamma[i] = best > -INFINITY ? acos(best < -1.0 ? -1.0 : best) : 1.5707963267948966;
+    // the wavefront's lanes again together: the vectors left
+    gamma_scan<2>(R, __ballot(full), (int32_t)i, threadIdx.x & 63);
 }
 
 // ------------------------------------------------------------- kernels
@@ -951,7 +1038,7 @@ __global__ __launch_bounds__(256) void k_grid_fill(RunView R, int gate)
 {
     grid_fill_body(R, blockIdx.x, gate);
 }
-__global__ __launch_bounds__(64) void k_grid_cells(RunView R, int gate)
+__global__ __launch_bounds__(64, 5) void k_grid_cells(RunView R, int gate)
 {
     grid_cells_body(R, blockIdx.x, gate);
 }
@@ -976,7 +1063,7 @@ __global__ __launch_bounds__(256) void kb_grid_fill(const RunView *runs, const S
 }
 // one cell per workgroup: more per workgroup would keep more registers live
 // in this heavy body, and it is the open generations' cost that matters here
-__global__ __launch_bounds__(64) void kb_grid_cells(const RunView *runs, const Span *sp, int n)
+__global__ __launch_bounds__(64, 5) void kb_grid_cells(const RunView *runs, const Span *sp, int n)
 {
     const int s = find_span(sp, n, blockIdx.x);
     grid_cells_body(runs[sp[s].run], blockIdx.x - sp[s].start, 0);
@@ -999,6 +1086,8 @@ __global__ __launch_bounds__(256) void kb_line_gamma(const RunView *runs, const 
 }
 
 // ------------------------------------------------------------- launchers
+static int64_t line_gamma_blocks(const RunView &R) { return (R.K * kGammaLanes + 255) / 256; }
+
 static hipError_t launch_grid_rest(const RunView &R, hipStream_t s, int gate)
 {
     const unsigned vb = (unsigned)((R.K + 255) / 256);
@@ -1007,18 +1096,18 @@ static hipError_t launch_grid_rest(const RunView &R, hipStream_t s, int gate)
     } else {
         k_grid_ranges<<<(unsigned)((R.gG + 255) / 256), 256, 0, s>>>(R, gate);
         k_grid_fill<<<vb, 256, 0, s>>>(R, gate);
-        k_line_gamma<<<vb, 256, 0, s>>>(R, gate);
+        if (gate != kKeepGamma) k_line_gamma<<<(unsigned)line_gamma_blocks(R), 256, 0, s>>>(R, gate);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_grid_build(const RunView &R, hipStream_t s)
+hipError_t launch_grid_build(const RunView &R, hipStream_t s, bool keep_gamma)
 {
     if (R.gG <= 0) return hipSuccess;
     const unsigned vb = (unsigned)((R.K + 255) / 256);
     if (R.m == 3) k_grid_clear<<<vb, 256, 0, s>>>(R);
     k_grid_bucket<<<vb, 256, 0, s>>>(R);
-    return launch_grid_rest(R, s, 1);
+    return launch_grid_rest(R, s, keep_gamma ? kKeepGamma : 1);
 }
 
 hipError_t launch_grid_rebuild(const RunView &R, hipStream_t s)
@@ -1063,7 +1152,7 @@ int64_t grid_phase_blocks(int phase, const RunView &R)
     case BP_ASSOC: return (R.M * kGridRowLanes + 255) / 256;
     case BP_GRID_FILL: return R.m == 3 ? 0 : (R.K + 255) / 256;
     case BP_GRID_RANGES: return R.m == 3 ? 0 : (cells + 255) / 256;
-    case BP_GRID_CELLS: return R.m == 3 ? grid_live_cells(R.gG) : (R.K + 255) / 256;
+    case BP_GRID_CELLS: return R.m == 3 ? grid_live_cells(R.gG) : line_gamma_blocks(R);
     }
     return 0;
 }

@@ -67,16 +67,17 @@ struct RunView {
     int gG;             // cells per side (0: association by full scan)
     int64_t gcap;       // list records: a slot of equal size per cell (grid only)
     double *gr;         // m: the scaling r the cells' coordinates divide by
-    int32_t *gcell;     // K: cell of each vector (-1: outside the line)
+    int32_t *gcell;     // K: cell of each vector (-1: outside the line; line only)
     int32_t *gcnt;      // cells: vectors per cell (line: then fill cursors)
     int32_t *gstart;    // cells: first position of each cell's vectors (line only)
     int32_t *gnum;      // cells: vectors of each cell (line only)
     int32_t *gvec;      // vector ids by cell: kBucket places per cell (grid), K (line)
     double *gvh;        // x 4: (v, |v|) of each
     int32_t *lcnt;      // cells: candidate-list length (-1: full scan; grid only)
-    unsigned long long *gtot;  // line only: the allocator of the cells' vector
-                               // ranges (build), 1 when some vector is outside
-                               // the line (every row then scans all vectors)
+    unsigned long long *gtot;  // line: the allocator of the cells' vector ranges
+                               // (build), 1 when some vector is outside the line
+                               // (every row then scans all vectors); grid: [2], 1
+                               // when some cell has more vectors than places
     double *lrec;       // gcap x 4: (v, |v|) of the list entries
     int32_t *lidx;      // gcap: vector id of each record
     int32_t *vs;        // K x 2: valid slots, ascending, each with its physical row
@@ -222,6 +223,7 @@ __device__ __forceinline__ bool gamma_open(const RunView &R) { return *R.vchange
 __device__ __forceinline__ void clear_counts(const RunView &R, int64_t tid, int64_t threads)
 {
     if (R.m != 3 || R.gG == 0) return;
+    if (tid == 0) R.gtot[2] = 0;
     for (int64_t c = tid; c < (int64_t)R.gG * R.gG; c += threads) R.gcnt[c] = 0;
 }
 

@@ -846,13 +846,11 @@ rvea_status rvea_set_state(rvea_run r, const float *X, const float *F, const uin
     const RunView &R = r->R;
     const size_t K = (size_t)R.K, m = (size_t)R.m;
     const bool build = V && r->L.gG > 0;  // a host-set V: the index unscaled and rebuilt
-    const bool late_gamma = gamma && build && R.gG > 0;  // the build writes gamma from V
-    const StateArray given = {R.gamma, 0, const_cast<double *>(gamma), K * 8};
     StateArray arrays[4] = {{fm_at(R, t), 0, const_cast<float *>(F), K * m * 4},
                             {valids_at(R, t), 0, const_cast<uint8_t *>(valid), K}};
     int n = 2;
     if (V) arrays[n++] = {R.V, 0, const_cast<double *>(V), K * m * 8};
-    if (gamma && !late_gamma) arrays[n++] = given;
+    if (gamma) arrays[n++] = {R.gamma, 0, const_cast<double *>(gamma), K * 8};
     const bool long_rows = (size_t)R.d * 4 > kStageBytes;  // a row per chunk at most
     HIPCHK(r, transfer_state(R, arrays, n, long_rows ? nullptr : const_cast<float *>(X), false,
                              r->stream));
@@ -862,8 +860,7 @@ rvea_status rvea_set_state(rvea_run r, const float *X, const float *F, const uin
     HIPCHK(r, launch_set_reset(R, r->stream, t, build ? 1 : 0));
     if (V) HIPCHK(r, launch_vec_aux(R, r->stream));
     if (V && !gamma && R.gG == 0) HIPCHK(r, launch_gamma(R, r->stream, 1));
-    if (build && R.gG > 0) HIPCHK(r, launch_grid_build(R, r->stream));
-    if (late_gamma) HIPCHK(r, transfer_state(R, &given, 1, nullptr, false, r->stream));
+    if (build && R.gG > 0) HIPCHK(r, launch_grid_build(R, r->stream, gamma != nullptr));
     if (R.Vel) HIPCHK(r, hipMemsetAsync(R.Vel, 0, (size_t)(R.K + R.N) * R.ld * 4, r->stream));
     HIPCHK(r, launch_stamp(R, r->stream));
     if (R.turn) HIPCHK(r, launch_prepare(R, r->stream));
@@ -1031,20 +1028,10 @@ rvea_status rvea_set_index(rvea_run r, int enable)
     const int G = enable ? r->L.gG : 0;
     if (G == r->R.gG) return RVEA_OK;
     HIPCHK(r, hipStreamSynchronize(r->stream));
-    // V may have changed while the index was off; the build also writes gamma,
-    // which stays as it is (the host may have set it)
-    if (G > 0) {
-        std::vector<double> gamma;
-        try {
-            gamma.resize((size_t)r->R.K);
-        } catch (const std::bad_alloc &) {
-            return RVEA_ENOMEM;
-        }
-        const StateArray keep = {r->R.gamma, 0, gamma.data(), gamma.size() * 8};
-        HIPCHK(r, transfer_state(r->R, &keep, 1, nullptr, true, r->stream));
-        r->R.gG = G;
-        HIPCHK(r, launch_grid_build(r->R, r->stream));
-        HIPCHK(r, transfer_state(r->R, &keep, 1, nullptr, false, r->stream));
+    if (G > 0) {  // V may have changed while the index was off; gamma stays as it is
+        RunView on = r->R;
+        on.gG = G;
+        HIPCHK(r, launch_grid_build(on, r->stream, true));
     }
     r->R.gG = G;
     drop_graphs(r);  // they hold the old launch sequence

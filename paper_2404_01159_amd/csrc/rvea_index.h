@@ -41,9 +41,11 @@ constexpr int kBucket = 16;
 __device__ __forceinline__ void bucket_vector(const RunView &R, int64_t j, int c, const double *v,
                                               double vn)
 {
-    R.gcell[j] = c;
     const int k = atomicAdd(&R.gcnt[c], 1);
-    if (k >= kBucket) return;
+    if (k >= kBucket) {
+        R.gtot[2] = 1;
+        return;
+    }
     const int64_t p = (int64_t)c * kBucket + k;
     R.gvec[p] = (int32_t)j;
     reinterpret_cast<double4 *>(R.gvh)[p] = make_double4(v[0], v[1], v[2], vn);

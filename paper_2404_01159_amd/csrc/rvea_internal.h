@@ -49,10 +49,10 @@ hipError_t launch_batch_operator(int cls, const RunView *runs, const Span *spans
                                  int64_t blocks, hipStream_t s);
 hipError_t launch_assoc(const RunView &R, hipStream_t s);
 // indexed association (two and three objectives): the index of V, rebuilt
-// when V changes, with gamma, and the association
+// when V changes, with gamma (unless that is to stay as it is), and the association
 int grid_side(int m, int64_t K);  // cells per side (0: not indexed)
 int grid_slot();                  // list records per cell
-hipError_t launch_grid_build(const RunView &R, hipStream_t s);
+hipError_t launch_grid_build(const RunView &R, hipStream_t s, bool keep_gamma = false);
 // the rebuild after an adaptation, which has already put each vector into its
 // cell (runs only when the vectors changed)
 hipError_t launch_grid_rebuild(const RunView &R, hipStream_t s);

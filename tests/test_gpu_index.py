@@ -6,6 +6,8 @@ phases keep the index rebuilt as each run adapts) and after a run leaves the
 batch.  Both paths are
 also checked against the oracle by the other GPU tests (the index is the
 default for m = 3)."""
+import time
+
 import numpy as np
 import pytest
 
@@ -304,3 +306,67 @@ def test_crowded_cell(P, m, H, crowd):
     # acos near 1 turns the cosine's rounding (2^-52) into sqrt(2 * 2^-52)/angle
     want = gamma_brute(V)
     assert np.all(np.abs(a["gamma"] - want) <= 4 * 2.0 ** -52 / np.maximum(want, 1e-8))
+
+
+def scaled_vectors(P, m, K, scale):
+    run = P.Run(1, m, 8, 1, K, seed=1)
+    V0 = run.get_state(genes=False)["V0"]
+    run.close()
+    V = V0 * np.asarray(scale)[:m]
+    return V0, V / np.linalg.norm(V, axis=1, keepdims=True)
+
+
+# vectors that the index leaves to scans of all of them: cells with more
+# neighbours than a workgroup holds, cells with more vectors than places, nearly
+# all vectors in one corner; at the ends of the scans' steps
+SCALES = [(1, 0.5, 0.5), (1, 0.1, 0.01), (1, 1e-3, 1e-3), (1, 1, 1e-4), (1e-8, 1, 1e-8)]
+
+
+@pytest.mark.parametrize("m,K", [(3, 6), (3, 66), (3, 496), (3, 2080), (2, 5), (2, 64), (2, 999)])
+@pytest.mark.parametrize("scale", SCALES)
+def test_gamma_of_crowded_vectors(P, m, K, scale):
+    """With the index, gamma of a host-set V equals the full pass's, and of an
+    adapted V too (objectives of those ranges, an adaptation a generation)."""
+    V0, V = scaled_vectors(P, m, K, scale)
+    r = np.random.default_rng(K)
+    X, valid = r.random((K, 8), np.float32), np.ones(K, np.uint8)
+    F = (V0 * np.asarray(scale)[:m]).astype(np.float32)
+    got = []
+    for on in (True, False):
+        run = P.Run(2, m, 8, 1, K, seed=3, params=P.default_params(t_max=50, fr=0.02))
+        run.set_index(on)
+        run.set_state(X, F, valid, V, t=2)
+        host = run.get_state(genes=False)["gamma"]
+        run.set_state(X, F, valid, V0, t=2)
+        run.generation()
+        st = run.get_state(genes=False)
+        run.close()
+        got.append((host, st["gamma"], st["V"]))
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("given", [False, True])
+def test_crowded_vectors_are_set_in_time(P, given):
+    """Setting vectors that are nearly all in one corner of the index takes less
+    than twenty times as long as vectors that fill it (a serial scan per vector
+    took 1,500 times); a given gamma is stored, not computed."""
+    K = 10011
+    V0, V = scaled_vectors(P, 3, K, (1, 1e-3, 1e-3))
+    r = np.random.default_rng(0)
+    X, F, valid = r.random((K, 8), np.float32), r.random((K, 3), np.float32), np.ones(K, np.uint8)
+    run = P.Run(2, 3, 8, 1, K, seed=3)
+    gamma = np.linspace(0.1, 0.2, K) if given else None
+    best = []
+    for v in (V0, V):
+        times = []
+        for _ in range(5):
+            run.synchronize()
+            t0 = time.perf_counter()
+            run.set_state(X, F, valid, v, gamma, 2)
+            times.append(time.perf_counter() - t0)
+        best.append(min(times))
+    if given:
+        assert np.array_equal(run.get_state(genes=False)["gamma"], gamma)
+    run.close()
+    assert best[1] < 20 * best[0], best
