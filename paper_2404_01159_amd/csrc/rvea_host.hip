@@ -740,6 +740,31 @@ rvea_status rvea_run_generations(rvea_run r, int n)
 
 static hipStream_t active_stream(rvea_run r) { return r->batch ? r->batch->stream : r->stream; }
 
+namespace {
+
+// The device of the run's stream (of the run, for a null stream) made current for
+// one call: the state transfers' events and launches are bound to it, and the
+// calling thread may be on another.
+struct OnDevice {
+    int before = -1;
+    hipError_t error;
+    OnDevice(rvea_run r, hipStream_t s)
+    {
+        int cur = 0, want = r->device;
+        error = hipGetDevice(&cur);
+        if (error == hipSuccess && s) error = hipStreamGetDevice(s, &want);
+        if (error != hipSuccess || cur == want) return;
+        error = hipSetDevice(want);
+        if (error == hipSuccess) before = cur;
+    }
+    ~OnDevice()
+    {
+        if (before >= 0) (void)hipSetDevice(before);
+    }
+};
+
+}  // namespace
+
 rvea_status rvea_synchronize(rvea_run r)
 {
     if (!r) return RVEA_EINVAL;
@@ -810,6 +835,8 @@ rvea_status rvea_get_state(rvea_run r, float *X, float *F, uint8_t *valid, doubl
 {
     if (!r) return RVEA_EINVAL;
     const RunView &R = r->R;
+    const OnDevice on(r, active_stream(r));
+    HIPCHK(r, on.error);
     // everything in one pass over the stream: the kernels find the current
     // population's buffers from the device's own generation counter
     int64_t td = 0;
@@ -844,6 +871,8 @@ rvea_status rvea_set_state(rvea_run r, const float *X, const float *F, const uin
     if (!r || !X || !F || !valid || t < 0) return RVEA_EINVAL;
     if (r->phase != 0 || r->batch) return RVEA_ESTATE;
     const RunView &R = r->R;
+    const OnDevice on(r, r->stream);
+    HIPCHK(r, on.error);
     const size_t K = (size_t)R.K, m = (size_t)R.m;
     const bool build = V && r->L.gG > 0;  // a host-set V: the index unscaled and rebuilt
     StateArray arrays[4] = {{fm_at(R, t), 0, const_cast<float *>(F), K * m * 4},
