@@ -76,18 +76,17 @@ constexpr int kSlot = 24;      // list records per cell (longer lists: a full sc
 constexpr int kChamps = 6;     // champions per cell: five vertices and the centre
 constexpr int kGridRowLanes = 4;  // lanes per row of the association
 constexpr double kDomMargin = 1e-12;
-// Vectors that a scan for gamma takes at once: with eight the shared scans of
-// 100,128 vectors take 2.5 ms instead of 3.7, but the kernel has a wavefront per
-// SIMD less and every rebuild pays for it (186 instead of 170 us there).
+// Vectors that a scan for gamma takes at once, the most that leaves the kernel six
+// wavefronts per SIMD without spills: with eight the shared scans of 100,128
+// vectors take 2.7 ms instead of 4.0, but every rebuild pays for it.
 constexpr int kScan = 4;
 constexpr int kGammaLanes = 4;    // lanes per vector of the line's gamma
 constexpr int kKeepGamma = 2;     // gate of a build that leaves gamma as it is
 // Scaling below which the launch shares the scans for gamma: from about there on
 // cells are too flat for their neighbourhoods to hold the nearest vector, and most
-// vectors are left.  Each cell scanning its own / shared, microseconds of an
-// adaptation: 100,128 vectors at ranges 1 : 0.15 : 0.15 757 / 3,730, 1 : 1 : 0.1
-// 5,351 / 3,700, 1 : 1e-4 : 1e-4 7,764 / 3,640; 10,011 vectors at 1 : 0.15 : 0.15
-// 88 / 68, 1 : 1 : 0.03 153 / 70.
+// vectors are left.  An adaptation of 100,128 vectors takes 4.0 ms shared, and
+// with each cell scanning its own 0.65 at ranges 1 : 0.15 : 0.15, 5.4 at
+// 1 : 1 : 0.1 and 7.8 at 1 : 1e-4 : 1e-4; 10,011 vectors 78 us, and 88, 111 and 112.
 constexpr double kFlat = 0.125;
 
 struct D3 {
@@ -352,24 +351,25 @@ __device__ __forceinline__ double first_lane(double v)
                             __builtin_amdgcn_readfirstlane(__double2loint(v)));
 }
 
-// Eq. 5's gamma of up to kScan vectors by the whole wavefront, the ids that the
-// lowest lanes of `mask` hold: the largest binary64 cosine to another vector that
-// is not parallel to it, over all vectors (as the full gamma pass computes it).
+// The cosine of Eq. 5's gamma of up to kScan vectors by the whole wavefront, those
+// whose ids the lowest lanes of `mask` hold, into these lanes: the largest binary64
+// cosine to another vector that is not parallel to it, over all vectors (as the
+// full gamma pass computes it).
 // The vectors themselves are scalars; a loaded vector serves all, and a cosine
 // is divided out only where it may be above the best so far.  The 64 vectors
 // around the id come first: in a lattice they hold its nearest or nearly so, and
 // few divisions are left.
 template <int M>
-__device__ __forceinline__ void gamma_block(const double *V, const double *vn, double *gamma,
-                                            int64_t K, unsigned long long mask, int32_t id, int lane)
+__device__ __forceinline__ void gamma_block(const double *V, const double *vn, int64_t K,
+                                            unsigned long long mask, int32_t id, int lane, double &cosine)
 {
     constexpr int B = kScan;
-    int32_t ids[B], mine = -1;
+    int32_t ids[B], at[B];
     double vi[B][M], vni[B], best[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) {  // the last one again where the mask has fewer
-        ids[b] = b == 0 || mask ? __builtin_amdgcn_readlane(id, __ffsll(mask) - 1) : ids[b > 0 ? b - 1 : 0];
-        if (mask && lane == b) mine = ids[b];
+        at[b] = b == 0 || mask ? __ffsll(mask) - 1 : at[b > 0 ? b - 1 : 0];
+        ids[b] = __builtin_amdgcn_readlane(id, at[b]);
         mask &= mask - 1;
 #pragma unroll
         for (int k = 0; k < M; ++k) vi[b][k] = first_lane(V[(int64_t)ids[b] * M + k]);
@@ -420,26 +420,25 @@ __device__ __forceinline__ void gamma_block(const double *V, const double *vn, d
             }
         }
     }
-    double c = 0.0;
 #pragma unroll
     for (int b = 0; b < B; ++b) {
         const double v = -wave_fmin(-best[b]);
-        if (lane == b) c = v;
+        if (lane == at[b]) cosine = v;
     }
-    if (mine >= 0)
-        gamma[mine] = c > -INFINITY ? acos(c < -1.0 ? -1.0 : c) : 1.5707963267948966;
 }
 
-// the same for every lane of `mask`, whatever their number (last in a kernel:
-// nothing else should be live beside it)
-template <int M>
-__device__ __forceinline__ void gamma_scan(const RunView &R, unsigned long long mask, int32_t id, int lane)
+// the angle of that cosine; pi/2 without another vector
+__device__ __forceinline__ double gamma_of(double cosine)
 {
-    while (mask) {  // uniform
-        gamma_block<M>(R.V, R.vn, R.gamma, R.K, mask, id, lane);
+    return cosine > -INFINITY ? acos(cosine < -1.0 ? -1.0 : cosine) : 1.5707963267948966;
+}
+
+// the lanes left after a block took its kScan lowest
+__device__ __forceinline__ unsigned long long past_block(unsigned long long mask)
+{
 #pragma unroll
-        for (int b = 0; b < kScan; ++b) mask &= mask - 1;
-    }
+    for (int b = 0; b < kScan; ++b) mask &= mask - 1;
+    return mask;
 }
 
 // The vectors of the (2 kStage + 1)^2 cells around a cell, staged in LDS by
@@ -576,20 +575,24 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
     // vectors than places, flat scaling) the whole launch shares them evenly, so
     // that no cell's are one wavefront's: 10,011 vectors of ranges 1 : 1e-3 : 1e-3
     // under unit scaling took 223 ms with each cell scanning its own, one after the
-    // other, 0.27 so.
+    // other, 0.28 so.
     const bool shared = R.gtot[2] != 0 || fmin(R.gr[0], fmin(R.gr[1], R.gr[2])) < kFlat;
-    // vectors left to scans at the end: `shared` ones, or the lanes of left_mask
-    unsigned long long left_mask = 0;
-    int32_t left_id = 0;
-    if (gate == kKeepGamma || shared) {
-    } else if (full) {
-        left_mask = (1ull << own_cnt) - 1;  // no crowded cell: at most kBucket
-        if (lane < own_cnt) left_id = R.gvec[(int64_t)c * kBucket + lane];
+    // this lane's vector and its cosine, and the lanes left to scans at the end
+    int32_t gid = -1;
+    double gcos = 0.0;
+    unsigned long long left = 0;
+    if (gate == kKeepGamma) {
+    } else if (shared) {  // a scan for each of up to half of the workgroups
+        const int64_t first = kScan * bx;
+        if (lane < kScan && first + lane < R.K) gid = (int32_t)(first + lane);
+        left = __ballot(gid >= 0);
+    } else if (full) {  // no crowded cell: at most kBucket
+        if (lane < own_cnt) gid = R.gvec[(int64_t)c * kBucket + lane];
+        left = __ballot(gid >= 0);
     } else {
         const int oq0 = __builtin_amdgcn_readlane(incl0 - mine0, own);
         const int on = own_cnt;
         const float lo = bsm - rho - kSlack;
-        double gmine = 0.0;  // own vector oq0 + lane: its largest cosine
         bool gok = false;
         for (int o = oq0; o < oq0 + on; ++o) {  // uniform
             const double4 v = st.rec[o];
@@ -614,13 +617,12 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
             dmin = fsqrt(__uint_as_float(wave_min(__float_as_uint(dmin))));
             const bool ok = dmin < INFINITY && lo > dmin + 2.0f * kSlack;
             if (lane == o - oq0) {
-                gmine = gb;
+                gcos = gb;
                 gok = ok;
             }
         }
-        if (gok) R.gamma[st.j[oq0 + lane]] = acos(gmine < -1.0 ? -1.0 : gmine);
-        left_mask = __ballot(lane < on && !gok);
-        if (lane < on) left_id = st.j[oq0 + lane];
+        if (lane < on) gid = st.j[oq0 + lane];
+        left = __ballot(lane < on && !gok);
     }
     // b: the vector that covers the cell best
     float cover = INFINITY;
@@ -712,16 +714,8 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
         }
     }
     if (full && lane == 0) R.lcnt[c] = -1;
-    // the scans
-    if (gate == kKeepGamma) return;
-    if (!shared) {
-        gamma_scan<3>(R, left_mask, left_id, lane);
-        return;
-    }
-    for (int64_t j = kScan * bx; j < R.K; j += kScan * grid_live_cells(G)) {
-        const int64_t left = R.K - j;
-        gamma_scan<3>(R, (1ull << (left < kScan ? left : kScan)) - 1, (int32_t)(j + lane), lane);
-    }
+    for (; left; left = past_block(left)) gamma_block<3>(R.V, R.vn, R.K, left, gid, lane, gcos);
+    if (gid >= 0) R.gamma[gid] = gamma_of(gcos);
 }
 
 // ----------------------------------------------------------- association
@@ -1019,9 +1013,10 @@ __device__ __forceinline__ void line_gamma_body(const RunView &R, int64_t bx, in
         scan(++hi);
         full = ++steps > kLineWalk;
     }
-    if (in && !full) R.gamma[i] = best > -INFINITY ? acos(best < -1.0 ? -1.0 : best) : 1.5707963267948966;
     // the wavefront's lanes again together: the vectors left
-    gamma_scan<2>(R, __ballot(full), (int32_t)i, threadIdx.x & 63);
+    for (unsigned long long left = __ballot(full); left; left = past_block(left))
+        gamma_block<2>(R.V, R.vn, R.K, left, (int32_t)i, threadIdx.x & 63, best);
+    if (in) R.gamma[i] = gamma_of(best);
 }
 
 // ------------------------------------------------------------- kernels
@@ -1038,8 +1033,7 @@ __global__ __launch_bounds__(256) void k_grid_fill(RunView R, int gate)
 {
     grid_fill_body(R, blockIdx.x, gate);
 }
-// (six wavefronts per SIMD, as without the scans: an adaptation of 10,011 vectors
-// takes 34.2 us, 36.2 with the registers that the scans would take)
+// (six wavefronts per SIMD, as without the scans for gamma)
 __global__ __launch_bounds__(64, 6) void k_grid_cells(RunView R, int gate)
 {
     grid_cells_body(R, blockIdx.x, gate);
