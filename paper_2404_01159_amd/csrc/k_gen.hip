@@ -43,12 +43,13 @@ __device__ __forceinline__ void prep_body(const RunView &R, int64_t bx)
     const int64_t j = bx * 256 + threadIdx.x;
     // every load first: the row stamp and the earlier blocks' counts do not
     // depend on the generation counter; the slot's flag, objectives and row do
-    const int32_t stampj = j < R.K + R.N ? R.stamp[j] : 0;
+    int32_t stampj = !R.turn && j < R.K + R.N ? R.stamp[j] : 0;
     int pre = 0;  // valid slots of the earlier blocks (partial sum)
     for (int b = threadIdx.x; b < (int)bx && b < (int)((R.K + 255) / 256); b += 256)
         pre += R.bcount[b];
     const int64_t p = *R.t_done;
     const int32_t gen = (int32_t)(p + 1);
+    if (R.turn && j < R.K + R.N) stampj = stamp_of(R, p)[j];
     const float *Fm = fm_of(R, p);
     int v = 0;
     int32_t rowj = 0;
@@ -137,7 +138,7 @@ __device__ __forceinline__ void stamp_body(const RunView &R, int64_t bx)
     int v = 0;
     if (j < R.K && valid_of(R, p)[j]) {
         v = 1;
-        R.stamp[slot_row_of(R, p)[j]] = (int32_t)(p + 1);
+        stamp_of(R, p)[slot_row_of(R, p)[j]] = (int32_t)(p + 1);
     }
     const unsigned long long b = __ballot(v);
     __shared__ int wc[4];

@@ -37,12 +37,12 @@
 //          found from binary32 chords)
 // Lists longer than kSlot, cells whose ball passes the box, cells with no
 // vector in the box and cells near one with more
-// vectors than its kBucket places are marked for a full scan (correct for any
+// vectors than places are marked for a full scan (correct for any
 // vector set, counted as full rescans).  The same pass gives Eq. 5's gamma of
 // the cell's vectors: from the staged neighbourhood where that provably holds
 // the nearest other vector (the nearest staged one is closer than the
 // neighbourhood's boundary), else by a scan of all vectors.  A cell's vectors
-// have kBucket places and its list kSlot records at fixed positions; the order
+// have fixed places and its list kSlot records; the order
 // of a cell's vectors varies from build to build (no result depends on it).
 // After an adaptation the rebuild is one kernel, the adaptation having put each
 // vector into its cell; with ranges allocated to the cells, a fill and the full
@@ -473,22 +473,12 @@ __device__ float box_side(const RunView &R, int ci, int cj, int side, const F3 &
     return farc_chord_of(u, a, b);
 }
 
-// The cells a row or a vector can land in: ci + cj <= G (cell_of clamps q
-// to the simplex, so floor(q1 G) + floor(q2 G) <= G); the others lie outside
-// it, hold no vector and are never read.  Row ci of them holds G cells for
-// ci <= 1 and G - ci + 1 after; t-th such cell in row order.
-__device__ __forceinline__ int64_t tri_start(int G, int ci)
-{
-    return ci == 0 ? 0 : (int64_t)G + (int64_t)(ci - 1) * (G + 1) - (int64_t)(ci - 1) * ci / 2;
-}
-__host__ __device__ __forceinline__ int64_t grid_live_cells(int G) { return (int64_t)G + (int64_t)G * (G + 1) / 2 - 1; }
-
 // One wavefront per cell (the simplex's cells only, in row order): the
 // neighbourhood staged in LDS; each lane's three entries in binary32 registers
 // with their squared chords to the five vertices and u_c, which serve b, P and
 // the champions; the list from P, written into the cell's slot at each lane's
 // prefix.
-// A neighbourhood over kStageCap vectors or with a cell over kBucket, or a ball
+// A neighbourhood over kStageCap vectors or with a cell over its places, or a ball
 // of radius b + rho that leaves it, marks the cell for a full scan.
 // Bound by vector instructions at four wavefronts per SIMD: with exact distances
 // to the cell's edges, the smallest of five boxes, binary64 champions and the
@@ -499,19 +489,20 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
     if (!gate && *R.vchanged == 0) return;
     const int G = R.gG;
     const int lane = threadIdx.x;
-    if (bx >= grid_live_cells(G)) return;  // uniform
+    if (bx >= index_cells(3, G)) return;  // uniform
     int ci = 0;  // the row of cell bx: the last row starting at or before it
     for (int hi = G - 1; ci < hi;) {
         const int mid = (ci + hi + 1) >> 1;
-        if (tri_start(G, mid) <= bx) ci = mid; else hi = mid - 1;
+        if ((int64_t)grid_row(G, mid) <= bx) ci = mid; else hi = mid - 1;
     }
-    const int cj = (int)(bx - tri_start(G, ci));
-    const int c = ci * G + cj;
+    const int cj = (int)(bx - grid_row(G, ci));
+    const int64_t c = bx;
     __shared__ CellGeo g;
     __shared__ double champ[kChamps][kNv];  // products of the champions and the vertices
     __shared__ Stage st;
     // stage: each lane's cells of the neighbourhood, their vector counts
     // scanned over the wave, then the vectors
+    const int places = bucket_places(R.K);
     int cnt[2] = {0, 0}, from[2] = {0, 0};
     bool over = false;
 #pragma unroll
@@ -519,10 +510,11 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
         const int t = lane + 64 * u;
         if (t < kStageW * kStageW) {
             const int i = ci - kStage + t / kStageW, jj = cj - kStage + t % kStageW;
-            if (i >= 0 && i < G && jj >= 0 && jj < G) {
-                from[u] = (i * G + jj) * kBucket;
-                cnt[u] = R.gcnt[i * G + jj];
-                over = over || cnt[u] > kBucket;
+            if (i >= 0 && i < G && jj >= 0 && jj < G && i + jj <= G) {
+                const int near = (int)(grid_row(G, i) + (uint32_t)jj);
+                from[u] = near * places;
+                cnt[u] = R.gcnt[near];
+                over = over || cnt[u] > places;
             }
         }
     }
@@ -532,7 +524,7 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
     const int mine0 = crowded ? 0 : cnt[0] + cnt[1];
     const int incl0 = wave_incl_scan(mine0);
     const int nst = __builtin_amdgcn_readlane(incl0, 63);
-    cell_geo(R, c, g, lane);
+    cell_geo(R, ci * G + cj, g, lane);
     bool full = crowded || nst > kStageCap;
     if (!full) {
         int q = incl0 - mine0;
@@ -586,8 +578,8 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
         const int64_t first = kScan * bx;
         if (lane < kScan && first + lane < R.K) gid = (int32_t)(first + lane);
         left = __ballot(gid >= 0);
-    } else if (full) {  // no crowded cell: at most kBucket
-        if (lane < own_cnt) gid = R.gvec[(int64_t)c * kBucket + lane];
+    } else if (full) {  // no crowded cell: at most its places
+        if (lane < own_cnt) gid = R.gvec[c * places + lane];
         left = __ballot(gid >= 0);
     } else {
         const int oq0 = __builtin_amdgcn_readlane(incl0 - mine0, own);
@@ -699,7 +691,7 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
         const int n = __builtin_amdgcn_readlane(incl, 63);
         full = n > kSlot;
         // the cell's records in its own slot, each lane at its prefix
-        const int64_t base = (int64_t)c * kSlot;
+        const int64_t base = c * kSlot;
         if (!full) {
             int64_t o = base + incl - mine;
 #pragma unroll
@@ -1088,7 +1080,7 @@ static hipError_t launch_grid_rest(const RunView &R, hipStream_t s, int gate)
 {
     const unsigned vb = (unsigned)((R.K + 255) / 256);
     if (R.m == 3) {
-        k_grid_cells<<<(unsigned)grid_live_cells(R.gG), 64, 0, s>>>(R, gate);
+        k_grid_cells<<<(unsigned)index_cells(3, R.gG), 64, 0, s>>>(R, gate);
     } else {
         k_grid_ranges<<<(unsigned)((R.gG + 255) / 256), 256, 0, s>>>(R, gate);
         k_grid_fill<<<vb, 256, 0, s>>>(R, gate);
@@ -1148,7 +1140,7 @@ int64_t grid_phase_blocks(int phase, const RunView &R)
     case BP_ASSOC: return (R.M * kGridRowLanes + 255) / 256;
     case BP_GRID_FILL: return R.m == 3 ? 0 : (R.K + 255) / 256;
     case BP_GRID_RANGES: return R.m == 3 ? 0 : (cells + 255) / 256;
-    case BP_GRID_CELLS: return R.m == 3 ? grid_live_cells(R.gG) : line_gamma_blocks(R);
+    case BP_GRID_CELLS: return R.m == 3 ? index_cells(3, R.gG) : line_gamma_blocks(R);
     }
     return 0;
 }

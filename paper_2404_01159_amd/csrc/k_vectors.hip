@@ -41,7 +41,7 @@ __device__ __forceinline__ void write_aux(const RunView &R, int64_t j, const dou
 // 105 individuals and its 100 generations took 2.20 ms, 2.11 so.)
 __device__ __forceinline__ void fresh_state(const RunView &R, int64_t tid, int64_t step)
 {
-    for (int64_t j = tid; j < R.M; j += step) R.stamp[j] = -1;
+    for (int64_t j = tid; j < R.M; j += step) stamp_of(R, 0)[j] = -1;
     for (int64_t j = R.N + tid; j < R.K; j += step) {
         R.valids[j] = 0;
         R.slot_rows[j] = (int32_t)j;

@@ -67,11 +67,12 @@ struct RunView {
     int gG;             // cells per side (0: association by full scan)
     int64_t gcap;       // list records: a slot of equal size per cell (grid only)
     double *gr;         // m: the scaling r the cells' coordinates divide by
-    int32_t *gcell;     // K: cell of each vector (-1: outside the line; line only)
+    int32_t *gcell;     // K: cell of each vector (-1: outside the line; line only,
+                        // for the build alone, so it shares the chunk maxima's place)
     int32_t *gcnt;      // cells: vectors per cell (line: then fill cursors)
     int32_t *gstart;    // cells: first position of each cell's vectors (line only)
     int32_t *gnum;      // cells: vectors of each cell (line only)
-    int32_t *gvec;      // vector ids by cell: kBucket places per cell (grid), K (line)
+    int32_t *gvec;      // vector ids by cell: bucket_places per cell (grid), K (line)
     double *gvh;        // x 4: (v, |v|) of each
     int32_t *lcnt;      // cells: candidate-list length (-1: full scan; grid only)
     unsigned long long *gtot;  // line: the allocator of the cells' vector ranges
@@ -83,7 +84,8 @@ struct RunView {
     int32_t *vs;        // K x 2: valid slots, ascending, each with its physical row
     int32_t *nvalid;    // 2: individuals of population p, by its parity
     int32_t *stamp;     // K+N: the generation that will read the row (rows of
-                        // the current population carry t_done + 1)
+                        // the current population carry t_done + 1); turn: none
+                        // of its own (stamp_of)
     int32_t *bcount;    // per-256-slot-block valid counts of the current population
     int32_t *freecnt;   // 2: free rows handed out (turn: by the parity of the generation that counts them)
     double *V0, *V;     // K x m
@@ -150,16 +152,29 @@ __device__ __forceinline__ unsigned long long *key_of(const RunView &R, int64_t 
 {
     return R.key + (R.turn ? (gen & 1) * R.K : 0);
 }
+// Row stamps of population p.  Runs with `turn` need them only until its offspring
+// are prepared, and keep them in the keys of generation p, which that leaves
+// alone (k_turn clears them after): K+N words, both all ones when cleared.
+__device__ __forceinline__ int32_t *stamp_of(const RunView &R, int64_t p)
+{
+    return R.turn ? reinterpret_cast<int32_t *>(R.key + (p & 1) * R.K) : R.stamp;
+}
 __device__ __forceinline__ uint32_t *rbits_of(const RunView &R, int64_t gen)
 {
     return R.rbits + (gen & 1) * 2 * R.m;
 }
 
-// cells of an index of side G: a G x G grid for three objectives, a line of
-// G cells for two
+// Cells of an index of side G: a line of G for two objectives; for three the cells
+// (ci, cj) of a G x G grid with ci + cj <= G, where the simplex's directions can
+// land, row after row.  Row ci has G of them for ci <= 1 and G - ci + 1 after.
 __host__ __device__ inline int64_t index_cells(int m, int G)
 {
-    return m == 3 ? (int64_t)G * G : (int64_t)G;
+    return m == 3 ? (int64_t)G + (int64_t)G * (G + 1) / 2 - 1 : (int64_t)G;
+}
+// first cell of row ci (G < 2^16, so the product fits)
+__host__ __device__ inline uint32_t grid_row(int G, int ci)
+{
+    return ci == 0 ? 0u : (uint32_t)G + (uint32_t)(ci - 1) * (uint32_t)(2 * G + 2 - ci) / 2;
 }
 
 // One run's share of a batched launch: blocks [start, next start) belong to
@@ -224,7 +239,8 @@ __device__ __forceinline__ void clear_counts(const RunView &R, int64_t tid, int6
 {
     if (R.m != 3 || R.gG == 0) return;
     if (tid == 0) R.gtot[2] = 0;
-    for (int64_t c = tid; c < (int64_t)R.gG * R.gG; c += threads) R.gcnt[c] = 0;
+    const int64_t cells = index_cells(3, R.gG);
+    for (int64_t c = tid; c < cells; c += threads) R.gcnt[c] = 0;
 }
 
 // ---------------------------------------------------------------- Philox

@@ -29,7 +29,7 @@ enum Buf {
     B_NVALID, B_STAMP, B_V0, B_V, B_V32, B_VN, B_GAMMA, B_ZBITS, B_RBITS, B_PMAX, B_PMASK,
     B_ASSOC, B_APD, B_KEY, B_SURV, B_TDONE, B_COUNTERS, B_VCHANGED, B_BCOUNT, B_FREECNT, B_PEN,
     B_NDONE, B_LQ, B_GPART, B_VEL,
-    B_GR, B_GCELL, B_GCNT, B_GSTART, B_GNUM, B_GVEC, B_GVH, B_LCNT, B_GTOT,
+    B_GR, B_GCNT, B_GSTART, B_GNUM, B_GVEC, B_GVH, B_LCNT, B_GTOT,
     B_LREC, B_LIDX, B_COUNT
 };
 
@@ -139,19 +139,19 @@ void make_layout(int problem, int m, int d, int64_t N, int64_t K, int op, Layout
     L.KC = (int)((K + cs - 1) / cs);
     const int64_t P = (N + 1) / 2;
     L.osplit = op == OP_GA ? offspring_splits(d, N) : 1;
-    // index of the vectors: for three objectives G x G cells, G = sqrt(K)
-    // (about two vectors per cell inside the simplex), each with a slot of
-    // grid_slot() list records (the lists average about eight); for two a
-    // line of G = K cells, no lists
+    // index of the vectors: for three objectives the simplex's cells of a G x G
+    // grid, G = sqrt(K) (about two vectors per cell), each with bucket_places() and
+    // a slot of grid_slot() list records (the lists average about eight); for two
+    // a line of G = K cells, no lists; for more none
     L.gG = grid_side(m, K);
     const size_t cells = (size_t)index_cells(m, L.gG);
-    const size_t places = m == 3 ? cells * kBucket : (size_t)K;  // of the vectors, by cell
+    const size_t places = m == 3 ? cells * bucket_places(K) : m == 2 ? (size_t)K : 0;  // of the vectors, by cell
     L.gcap = m == 3 ? (int64_t)grid_slot() * (int64_t)cells : 0;
     const size_t sz[] = {
         (size_t)(K + N) * L.ld * 4, (size_t)2 * K * 4,
         turn_rule(K) ? (size_t)2 * M * 4 : (size_t)N * 4, (size_t)2 * K,
         (size_t)2 * M * m * 4, (size_t)M,
-        (size_t)P * 2 * 4, (size_t)K * 8, 8, (size_t)(K + N) * 4, (size_t)K * m * 8,
+        (size_t)P * 2 * 4, (size_t)K * 8, 8, turn_rule(K) ? 0 : (size_t)M * 4, (size_t)K * m * 8,
         (size_t)K * m * 8, (size_t)K * L.stride * 4, (size_t)K * 8, (size_t)K * 8,
         (size_t)3 * m * 4, (size_t)4 * m * 4, (size_t)L.KC * M * 4, (size_t)L.KC * M * 4,
         (size_t)M * 4, (size_t)M * 8, (size_t)K * (turn_rule(K) ? 16 : 8), (size_t)K * 4, 8, 3 * 8, 4,
@@ -159,7 +159,7 @@ void make_layout(int problem, int m, int d, int64_t N, int64_t K, int op, Layout
         problem == kPolicy ? (size_t)kLqFloats * 4 : 0,
         L.osplit > 1 ? (size_t)P * L.osplit * 2 * 8 : 8,
         swarm(op) ? (size_t)(K + N) * L.ld * 4 : 8,
-        (size_t)m * 8, (size_t)K * 4, cells * 4, m == 3 ? 0 : cells * 4, m == 3 ? 0 : cells * 4,
+        (size_t)m * 8, cells * 4, m == 3 ? 0 : cells * 4, m == 3 ? 0 : cells * 4,
         places * 4, places * 32, m == 3 ? cells * 4 : 0, 32, (size_t)L.gcap * 32, (size_t)L.gcap * 4};
     static_assert(sizeof(sz) / sizeof(sz[0]) == B_COUNT, "one size per buffer");
     size_t o = 0;
@@ -480,7 +480,7 @@ rvea_status create_run(int problem, int m, int d, int64_t N, int64_t K, uint64_t
     R.gcap = L.gcap;
     if (L.gG > 0) {
         R.gr = (double *)(w + L.off[B_GR]);
-        R.gcell = (int32_t *)(w + L.off[B_GCELL]);
+        R.gcell = (int32_t *)(w + L.off[B_PMAX]);  // the scans and the build take turns
         R.gcnt = (int32_t *)(w + L.off[B_GCNT]);
         R.gstart = (int32_t *)(w + L.off[B_GSTART]);
         R.gnum = (int32_t *)(w + L.off[B_GNUM]);
@@ -1304,7 +1304,12 @@ rvea_status rvea_autotune(rvea_run r, rvea_tuning *out)
     // the trial lowered the next generation's minima (per vector, ideal point) and
     // handed out rows for children that need not come again (velocities set
     // meanwhile): the preparation starts over
+    int64_t td = 0;
+    rvea_status st = device_t(r, &td);
+    if (st != RVEA_OK) return st;
     HIPCHK(r, hipMemsetAsync(R.zbits, 0xff, (size_t)3 * R.m * 4, r->stream));
+    if (R.turn)  // the row stamps' place
+        HIPCHK(r, hipMemsetAsync(R.key + (td & 1) * R.K, 0xff, (size_t)R.K * 8, r->stream));
     HIPCHK(r, launch_stamp(R, r->stream));
     if (R.turn) HIPCHK(r, launch_prepare(R, r->stream));
     HIPCHK(r, hipStreamSynchronize(r->stream));

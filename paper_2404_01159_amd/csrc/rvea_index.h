@@ -11,7 +11,7 @@
 
 namespace rvea {
 
-// cell of a direction x >= 0 (x != 0); q pulled onto the simplex if rounding
+// cell (its place in row order) of a direction x >= 0 (x != 0); q pulled onto the simplex if rounding
 // left it just outside.  -1 if the coordinates are not finite.
 __device__ __forceinline__ int cell_of(double x0, double x1, double x2, const double *r, int G)
 {
@@ -26,15 +26,19 @@ __device__ __forceinline__ int cell_of(double x0, double x1, double x2, const do
     }
     int ci = (int)floor(q1 * G), cj = (int)floor(q2 * G);
     ci = ci < 0 ? 0 : (ci > G - 1 ? G - 1 : ci);
-    cj = cj < 0 ? 0 : (cj > G - 1 ? G - 1 : cj);
-    return ci * G + cj;
+    const int end = ci <= 1 ? G - 1 : G - ci;
+    cj = cj < 0 ? 0 : (cj > end ? end : cj);
+    return (int)(grid_row(G, ci) + (uint32_t)cj);
 }
 
-// Vectors that a grid cell holds (two on average; a cell with more leaves the
-// cells around it to full scans).  Fixed places, cell c's from c * kBucket on,
-// let the pass that writes a vector put it there at once: with ranges sized to
-// the cells a rebuild needed two kernels more.
-constexpr int kBucket = 16;
+// Vectors that a grid cell holds (two on average, at most four of a lattice under
+// its own scaling; a cell with more leaves the cells around it to full scans).
+// Fixed places, cell c's from c * bucket_places on, let the pass that writes a
+// vector put it there at once: with ranges sized to the cells a rebuild needed two
+// kernels more.  Half as many for few vectors, where a full scan is short and
+// sixteen places a cell would be more memory than those ranges took.
+constexpr int kBucket = 16;  // at most
+__host__ __device__ inline int bucket_places(int64_t K) { return K <= 128 ? kBucket / 2 : kBucket; }
 
 // Vector j = v (norm vn) into cell c of the grid: counted, and its id and (v,
 // |v|) at the next place (counts start at zero).
@@ -42,11 +46,12 @@ __device__ __forceinline__ void bucket_vector(const RunView &R, int64_t j, int c
                                               double vn)
 {
     const int k = atomicAdd(&R.gcnt[c], 1);
-    if (k >= kBucket) {
+    const int places = bucket_places(R.K);
+    if (k >= places) {
         R.gtot[2] = 1;
         return;
     }
-    const int64_t p = (int64_t)c * kBucket + k;
+    const int64_t p = (int64_t)c * places + k;
     R.gvec[p] = (int32_t)j;
     reinterpret_cast<double4 *>(R.gvh)[p] = make_double4(v[0], v[1], v[2], vn);
 }

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void k_set_reset(RunView R, int64_t t, int uns
         uint8_t *v = valid_of(R, t) + j;
         *v = *v ? 1 : 0;
     }
-    if (j < R.M) R.stamp[j] = -1;
+    if (j < R.M) stamp_of(R, t)[j] = -1;
     if (j < 3 * R.m) R.zbits[j] = 0xffffffffu;
     if (unscale && j < R.m) R.gr[j] = 1.0;
     if (j == 0) *R.t_done = t;
