@@ -179,6 +179,9 @@ struct rvea_run_s {
     int device;
     int H;
     int64_t t;  // completed generations (host mirror)
+    // a caller captured generations of the run: its replays count on the device
+    // only, so the mirror may be behind
+    bool captured = false;
     int phase;  // 0 ready, 1 stepped, 2 selected
     bool has_selection;
     rvea_params params;
@@ -311,6 +314,13 @@ rvea_status timed(rvea_run r, int id, Fn fn, const char *what)
         ev.keep();
     }
     return RVEA_OK;
+}
+
+// whether the caller is capturing stream s (the null stream cannot be)
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    return s && hipStreamIsCapturing(s, &c) == hipSuccess && c != hipStreamCaptureStatusNone;
 }
 
 rvea_status counters_status(rvea_run r, const unsigned long long *c)
@@ -601,6 +611,7 @@ rvea_status rvea_select(rvea_run r)
     st = timed(r, 2, [&] { return launch_rerank(r->R, r->stream); }, "rerank");
     if (st != RVEA_OK) return st;
     HIPCHK(r, launch_select_back(r->R, r->stream));
+    r->captured = r->captured || capturing(r->stream);
     r->t += 1;
     r->phase = 2;
     r->has_selection = true;
@@ -726,6 +737,7 @@ rvea_status rvea_run_generations(rvea_run r, int n)
     if (r->use_graphs && r->timing == 0 && n > 0) {
         rvea_status st = graph_launches(r, n, true);
         if (st != RVEA_OK) return st;
+        r->captured = r->captured || capturing(r->stream);
         r->has_selection = true;
         return RVEA_OK;
     }
@@ -895,6 +907,7 @@ rvea_status rvea_set_state(rvea_run r, const float *X, const float *F, const uin
     if (R.turn) HIPCHK(r, launch_prepare(R, r->stream));
     HIPCHK(r, hipStreamSynchronize(r->stream));
     r->t = t;
+    r->captured = false;
     r->has_selection = false;
     return RVEA_OK;
 }
@@ -1436,8 +1449,8 @@ rvea_status rebuild_plan(rvea_batch b)
 }
 
 // The phases from BP_ADAPT on do nothing unless some run adapts (each run's
-// adaptation is decided on the device): a generation in which none does leaves
-// them out.  Their launches, up to nine, cost 4.7 us each even so, 45 of 390 us
+// adaptation is decided on the device): a generation in which none does, by the
+// host's counts, leaves them out.  Their launches, up to nine, cost 4.7 us each even so, 45 of 390 us
 // a generation at sixteen served runs.
 hipError_t enqueue_batch_generation(rvea_batch b, hipStream_t s, bool adapt)
 {
@@ -1514,8 +1527,14 @@ rvea_status rvea_batch_step(rvea_batch b)
         if (st != RVEA_OK) return st;
     }
     if (b->runs.empty()) return RVEA_OK;
-    bool adapt = false;  // some run's generation is a multiple of its period
-    for (rvea_run r : b->runs) adapt = adapt || (r->t + 1) % r->R.period == 0;
+    // some run's generation is a multiple of its period, or may be: replays of a
+    // captured step come at any generation
+    const bool cap_step = capturing(b->stream);
+    bool adapt = cap_step;
+    for (rvea_run r : b->runs) {
+        r->captured = r->captured || cap_step;
+        adapt = adapt || r->captured || (r->t + 1) % r->R.period == 0;
+    }
     rvea_batch_s::Captured &cap = b->captured[adapt ? 1 : 0];
     const bool again = cap.seen == b->version;
     cap.seen = b->version;

@@ -302,3 +302,51 @@ def test_runs_that_share_launches_equal_alone(P, index, eta):
         assert same(a, b) is None, (a.m, a.d, same(a, b))
         a.close()
         b.close()
+
+
+def test_captured_step_adapts_on_replay(P):
+    """A batch step that the caller captures adapts each run in its own
+    generations when it is replayed, and steps after the replays do so too."""
+    shapes = [(1, 3, 20, 105, 0.1), (2, 2, 15, 60, 0.15), (3, 5, 12, 126, 0.2)]
+
+    def make(k, stream=None):
+        problem, m, d, K, fr = shapes[k]
+        return P.Run(problem, m, d, K, K, seed=60 + k, params=P.default_params(t_max=30, fr=fr), stream=stream)
+
+    s = torch.cuda.Stream()
+    runs = [make(k, s) for k in range(3)]
+    batch = P.Batch(3, stream=s)
+    batch.set_graphs(False)
+    for r in runs:
+        batch.admit(r)
+    batch.step()
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        batch.step()
+    done = 1
+    for replays, steps in ((4, 1), (5, 3)):
+        for _ in range(replays):
+            with torch.cuda.stream(s):
+                g.replay()
+            done += 1
+        torch.cuda.synchronize()
+        check(P, runs, make, done)
+        batch.step(steps)
+        done += steps
+        check(P, runs, make, done)
+    for r in list(runs):
+        batch.retire(r)
+        r.close()
+    batch.close()
+
+
+def check(P, runs, make, done):
+    for k, r in enumerate(runs):
+        want = make(k)
+        want.run(done)
+        a, b = r.get_state(), want.get_state()
+        want.close()
+        assert a["t"] == done
+        for key in ("X", "F", "valid", "V", "gamma"):
+            assert np.array_equal(a[key], b[key], equal_nan=True), (done, k, key)
