@@ -130,6 +130,14 @@ __device__ __forceinline__ F3 funit(const F3 &a)
     const float inv = __builtin_amdgcn_rcpf(fsqrt(fdot(a, a)));
     return f3(a.x * inv, a.y * inv, a.z * inv);
 }
+// unit direction of a record (v, |v|) for the geometric tests, from binary64 (a
+// norm may be outside binary32's range); the hardware's reciprocal is off by less
+// than 2^-24 (over 5e8 arguments of every size)
+__device__ __forceinline__ F3 unit_of(const double4 &r)
+{
+    const double inv = __builtin_amdgcn_rcp(r.w);
+    return f3((float)(r.x * inv), (float)(r.y * inv), (float)(r.z * inv));
+}
 // squared chord, and the chord (minima and maxima of chords are taken on
 // the squares, with one square root at the end: the square root is
 // monotone, so the result moves by at most its last-bit rounding)
@@ -552,8 +560,7 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
         const int q = lane + 64 * u;
         const bool has = !full && q < nst;
         const double4 r = st.rec[has ? q : 0];
-        const float inv = __builtin_amdgcn_rcpf((float)r.w);
-        vf[u] = f3((float)r.x * inv, (float)r.y * inv, (float)r.z * inv);
+        vf[u] = unit_of(r);
 #pragma unroll
         for (int e = 0; e <= kNv; ++e) c2[u][e] = has ? fchord2(ld3(g.Xf[e]), vf[u]) : INFINITY;
     }
@@ -588,8 +595,7 @@ __device__ __forceinline__ void grid_cells_body(const RunView &R, int64_t bx, in
         bool gok = false;
         for (int o = oq0; o < oq0 + on; ++o) {  // uniform
             const double4 v = st.rec[o];
-            const float inv = __builtin_amdgcn_rcpf((float)v.w);
-            const F3 ui = f3((float)v.x * inv, (float)v.y * inv, (float)v.z * inv);
+            const F3 ui = unit_of(v);
             double gb = -INFINITY;
             float dmin = INFINITY;  // squared
 #pragma unroll

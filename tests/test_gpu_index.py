@@ -370,3 +370,24 @@ def test_crowded_vectors_are_set_in_time(P, given):
         assert np.array_equal(run.get_state(genes=False)["gamma"], gamma)
     run.close()
     assert best[1] < 20 * best[0], best
+
+
+@pytest.mark.parametrize("K", [105, 2016])
+@pytest.mark.parametrize("power", [-140, 140])
+def test_vectors_of_any_length(P, K, power):
+    """A host-set V whose norms are outside binary32's range (an exact power of
+    two longer) gives the associations of the unit vectors, without full scans."""
+    seen = []
+    for scale in (1.0, 2.0 ** power):
+        run = P.Run(1, 3, 20, K, K, seed=4)
+        st = run.get_state()
+        run.set_state(st["X"], st["F"], st["valid"], st["V"] * scale)
+        run.step()
+        run.select()
+        run.adapt()
+        seen.append((run.get_selection(), run.get_state(genes=False)["gamma"], run.counters()["full_rescans"]))
+        run.close()
+    (a, ga, na), (b, gb, nb) = seen
+    for k in ("assoc", "apd", "surv"):
+        assert np.array_equal(a[k], b[k]), k
+    assert np.array_equal(ga, gb) and na == nb
