@@ -840,16 +840,28 @@ __device__ __forceinline__ void assoc_grid_body(const RunView &R, int64_t bx)
     atomicMin(&key_of(R, pop + 1)[bj], ((ab >> R.kb) << R.kb) | (unsigned long long)i);
 }
 
-// kGridRowLanes lanes per merged row (two objectives): f' and |f'| as the
-// re-rank forms them, the row's cell on the line, its own cell and two on each
-// side at once (lane 0 the row's, lanes 1 and 2 a side each), then the walk
-// outward on both sides side by side (or a scan of every vector if a walk is
-// too long or the line incomplete), then as the re-rank: angle, APD of Eq. 4
+// L = 4 or 1 lanes per merged row (two objectives): f' and |f'| as the
+// re-rank forms them, the row's cell on the line, that cell and its neighbours (of
+// four lanes at once: lane 0 the row's own, lanes 1 and 2 two cells of a side
+// each), then the walk outward on both sides (or a scan of every vector if a walk
+// is too long or the line incomplete), then as the re-rank: angle, APD of Eq. 4
 // and the per-vector minimum of (APD, row).  Bound by its chain of memory round
-// trips and binary64 divisions: one lane per row took the cells one after the
-// other, 10.8 us at 10,000 rows (8.6 at 8,192 policies); 9.0 (6.0) so.
+// trips and binary64 divisions: one lane per row takes the cells one after the
+// other, 10.8 us at 10,000 rows (8.6 at 8,192 policies) against 9.0 (6.0).
+//
+// From 100,000 to 350,000 rows the launch is bound by issue instead, and one lane
+// per row has a quarter of the wavefronts to issue for (200,000 rows: 14.1 us,
+// four lanes 16.5; 320,000: 22.4 and 23.3).  With more rows the walks' loads miss
+// the L2 cache and four lanes have more of them in flight (400,000: 28.3 us, one
+// lane 33.6).
+__host__ __device__ __forceinline__ int line_lanes(int64_t rows)
+{
+    return rows >= 100000 && rows < 350000 ? 1 : kGridRowLanes;
+}
+template <int L>
 __device__ __forceinline__ void line_combine(double &best, int64_t &bj)
 {
+    if (L == 1) return;
     double ob = partner32<0>(best);
     int64_t oj = partner32<0>(bj);
     if (ob > best || (ob == best && oj < bj)) {
@@ -864,10 +876,11 @@ __device__ __forceinline__ void line_combine(double &best, int64_t &bj)
     }
 }
 
+template <int L>
 __device__ __forceinline__ void assoc_line_body(const RunView &R, int64_t bx)
 {
-    const int sub = threadIdx.x % kGridRowLanes;
-    const int64_t i = (bx * 256 + threadIdx.x) / kGridRowLanes;
+    const int sub = threadIdx.x % L;
+    const int64_t i = (bx * 256 + threadIdx.x) / L;
     const bool in = i < R.M;
     const int64_t pop = *R.t_done;
     const uint32_t *zb = zbuf(R, pop + 1);
@@ -902,26 +915,10 @@ __device__ __forceinline__ void assoc_line_body(const RunView &R, int64_t bx)
         for (int e = 0; e < n; ++e) take(rec[st + e], R.gvec[st + e]);
     };
     const bool walk = live && !full;
-    const int side = sub == 1 ? -1 : sub == 2 ? 1 : 0;
-    if (walk && sub < 3) {
-        // this lane's cells, their ranges read together, then their first
-        // vectors together
-        const int ca = c + side, cb = side == 0 ? -1 : c + 2 * side;
-        const bool ha = ca >= 0 && ca < G, hb = cb >= 0 && cb < G;
-        const int sa = ha ? R.gstart[ca] : 0, na = ha ? R.gnum[ca] : 0;
-        const int sb = hb ? R.gstart[cb] : 0, nb = hb ? R.gnum[cb] : 0;
-        const double4 va = rec[na > 0 ? sa : 0], vb = rec[nb > 0 ? sb : 0];
-        const int32_t ja = R.gvec[na > 0 ? sa : 0], jb = R.gvec[nb > 0 ? sb : 0];
-        if (na > 0) take(va, ja);
-        if (nb > 0) take(vb, jb);
-        for (int e = 1; e < na; ++e) take(rec[sa + e], R.gvec[sa + e]);
-        for (int e = 1; e < nb; ++e) take(rec[sb + e], R.gvec[sb + e]);
-    }
-    line_combine(best, bj);
-    // beyond those cells while the boundary direction (moved outward by
-    // kLineEps in u) could still tie
-    if (walk && side != 0) {
-        int at = c + 2 * side, steps = 2;
+    // `done` cells on a side taken: beyond those while the boundary direction
+    // (moved outward by kLineEps in u) could still tie
+    auto outward = [&](int side, int done) {
+        int at = c + done * side, steps = done;
         while (at > 0 && at < G - 1 && !full) {
             const double edge = side < 0 ? (double)at / G + kLineEps : (double)(at + 1) / G - kLineEps;
             if (line_bound(f0, f1, nrm, edge, r) + kLineTau < best) break;
@@ -929,16 +926,43 @@ __device__ __forceinline__ void assoc_line_body(const RunView &R, int64_t bx)
             scan(at);
             full = ++steps > kLineWalk;
         }
+    };
+    if constexpr (L == 1) {
+        if (walk) {
+            scan(c);
+            if (c > 0) scan(c - 1);
+            if (c < G - 1) scan(c + 1);
+            outward(-1, 1);
+            outward(1, 1);
+        }
+    } else {
+        const int side = sub == 1 ? -1 : sub == 2 ? 1 : 0;
+        if (walk && sub < 3) {
+            // this lane's cells, their ranges read together, then their first
+            // vectors together
+            const int ca = c + side, cb = side == 0 ? -1 : c + 2 * side;
+            const bool ha = ca >= 0 && ca < G, hb = cb >= 0 && cb < G;
+            const int sa = ha ? R.gstart[ca] : 0, na = ha ? R.gnum[ca] : 0;
+            const int sb = hb ? R.gstart[cb] : 0, nb = hb ? R.gnum[cb] : 0;
+            const double4 va = rec[na > 0 ? sa : 0], vb = rec[nb > 0 ? sb : 0];
+            const int32_t ja = R.gvec[na > 0 ? sa : 0], jb = R.gvec[nb > 0 ? sb : 0];
+            if (na > 0) take(va, ja);
+            if (nb > 0) take(vb, jb);
+            for (int e = 1; e < na; ++e) take(rec[sa + e], R.gvec[sa + e]);
+            for (int e = 1; e < nb; ++e) take(rec[sb + e], R.gvec[sb + e]);
+        }
+        line_combine<L>(best, bj);
+        if (walk && side != 0) outward(side, 2);
+        const int any = (int)full | partner32<0>((int)full);
+        full = (any | partner32<1>(any)) != 0;  // of the row's lanes
     }
-    const int any = (int)full | partner32<0>((int)full);
-    full = (any | partner32<1>(any)) != 0;  // of the row's lanes
     if (full) {
         best = -INFINITY;
         bj = R.K;
-        for (int64_t j = sub; j < R.K; j += kGridRowLanes)
+        for (int64_t j = sub; j < R.K; j += L)
             take(make_double4(R.V[j * 2], R.V[j * 2 + 1], 0.0, R.vn[j]), j);
     }
-    line_combine(best, bj);
+    line_combine<L>(best, bj);
     if (!in || sub != 0) return;
     if (!act) {
         R.assoc[i] = -1;
@@ -1037,7 +1061,8 @@ __global__ __launch_bounds__(64, 6) void k_grid_cells(RunView R, int gate)
     grid_cells_body(R, blockIdx.x, gate);
 }
 __global__ __launch_bounds__(256) void k_assoc_grid(RunView R) { assoc_grid_body(R, blockIdx.x); }
-__global__ __launch_bounds__(256) void k_assoc_line(RunView R) { assoc_line_body(R, blockIdx.x); }
+template <int L>
+__global__ __launch_bounds__(256) void k_assoc_line(RunView R) { assoc_line_body<L>(R, blockIdx.x); }
 __global__ __launch_bounds__(256) void k_line_gamma(RunView R, int gate)
 {
     line_gamma_body(R, blockIdx.x, gate);
@@ -1070,8 +1095,10 @@ __global__ __launch_bounds__(256) void kb_assoc_index(const RunView *runs, const
     const RunView &R = runs[sp[s].run];
     if (R.m == 3)
         assoc_grid_body(R, blockIdx.x - sp[s].start);
+    else if (line_lanes(R.M) == 1)  // uniform
+        assoc_line_body<1>(R, blockIdx.x - sp[s].start);
     else
-        assoc_line_body(R, blockIdx.x - sp[s].start);
+        assoc_line_body<kGridRowLanes>(R, blockIdx.x - sp[s].start);
 }
 __global__ __launch_bounds__(256) void kb_line_gamma(const RunView *runs, const Span *sp, int n)
 {
@@ -1111,11 +1138,11 @@ hipError_t launch_grid_rebuild(const RunView &R, hipStream_t s)
 
 hipError_t launch_assoc_grid(const RunView &R, hipStream_t s)
 {
-    const unsigned g = (unsigned)((R.M * kGridRowLanes + 255) / 256);
+    const unsigned g = (unsigned)grid_phase_blocks(BP_ASSOC, R);
     if (R.m == 3)
         k_assoc_grid<<<g, 256, 0, s>>>(R);
     else
-        k_assoc_line<<<g, 256, 0, s>>>(R);
+        (line_lanes(R.M) == 1 ? k_assoc_line<1> : k_assoc_line<kGridRowLanes>)<<<g, 256, 0, s>>>(R);
     return hipGetLastError();
 }
 
@@ -1143,7 +1170,7 @@ int64_t grid_phase_blocks(int phase, const RunView &R)
     if (R.gG <= 0) return 0;
     const int64_t cells = index_cells(R.m, R.gG);
     switch (phase) {
-    case BP_ASSOC: return (R.M * kGridRowLanes + 255) / 256;
+    case BP_ASSOC: return (R.M * (R.m == 3 ? kGridRowLanes : line_lanes(R.M)) + 255) / 256;
     case BP_GRID_FILL: return R.m == 3 ? 0 : (R.K + 255) / 256;
     case BP_GRID_RANGES: return R.m == 3 ? 0 : (cells + 255) / 256;
     case BP_GRID_CELLS: return R.m == 3 ? index_cells(3, R.gG) : line_gamma_blocks(R);

@@ -391,3 +391,24 @@ def test_vectors_of_any_length(P, K, power):
     for k in ("assoc", "apd", "surv"):
         assert np.array_equal(a[k], b[k]), k
     assert np.array_equal(ga, gb) and na == nb
+
+
+# one lane per row of the line between 100,000 and 350,000 rows, four else: both
+# sides of both ends, alone and in a batch
+@pytest.mark.parametrize("K,N", [(50000, 49999), (50000, 50000), (175000, 174999), (175000, 175000)])
+def test_line_lanes_match_full_scan(P, K, N):
+    runs = [P.Run(1, 2, 4, N, K, seed=K, params=P.default_params(t_max=4, fr=0.5)) for _ in range(3)]
+    runs[2].set_index(False)
+    batch = P.Batch(1)
+    batch.admit(runs[1])
+    for t in range(3):
+        batch.step()
+        for r in (runs[0], runs[2]):
+            r.generation()
+        same_selection(runs[0], runs[2], t)
+        same_selection(runs[1], runs[2], t)
+    assert runs[0].counters()["full_rescans"] == 0
+    batch.retire(runs[1])
+    batch.close()
+    for r in runs:
+        r.close()
