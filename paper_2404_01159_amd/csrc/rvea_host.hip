@@ -100,9 +100,13 @@ rvea_status check_args(int problem, int m, int d, int64_t N, int64_t K, const rv
 // device no better, and every chunk leaves a maximum and a tile mask per row for
 // the re-rank to read: at 3,876 vectors of five objectives four rows per lane and
 // 122 chunks took 13.2 + 16.2 us, one row and 16 chunks 11.0 + 7.8; at 8 objectives
-// and 6,435 vectors 58.7 and 37.2 us together, at 84 vectors 10.7 and 9.7.  More
-// rows per lane share a vector's read once one row per lane gives more
-// workgroups than that by itself.
+// and 6,435 vectors 58.7 and 37.2 us together, at 84 vectors 10.7 and 9.7.  Where
+// chunks of 1,024 give more workgroups than that, just under the next multiple of
+// the 256 CUs: at 17,550 vectors of five objectives 98.7 us, 110 with the 630
+// workgroups that 1,024 gives.  More rows per lane share a vector's read: with one
+// (two) up to 16,384 (32,768) rows, 7,315 vectors of five objectives took 34.8 us,
+// 29.5 so, 12,650 65.3 and 54.6, and 14,706 of three without the index 75.8 and
+// 53.3.
 constexpr int64_t kScanGroups = 512;
 struct ScanShape {
     int rr, cs, kc;
@@ -110,9 +114,10 @@ struct ScanShape {
 ScanShape scan_shape(int64_t rows, int64_t K, int CS0)
 {
     ScanShape s;
-    s.rr = rows <= 16384 ? 1 : rows <= 32768 ? 2 : 4;
+    s.rr = rows <= 10000 ? 1 : rows <= 20000 ? 2 : 4;
     const int64_t nbi = (rows + 256 * s.rr - 1) / (256 * s.rr);
-    const int64_t kc = std::max<int64_t>(1, kScanGroups / nbi);
+    const int64_t least = nbi * ((K + 32 * kTile - 1) / (32 * kTile));
+    const int64_t kc = std::max<int64_t>(1, std::max<int64_t>(kScanGroups, (least + 255) / 256 * 256) / nbi);
     int64_t cs = ((K + kc - 1) / kc + kTile - 1) / kTile * kTile;
     cs = std::min<int64_t>(std::max<int64_t>(cs, CS0), 32 * kTile);
     s.cs = (int)cs;
@@ -127,8 +132,9 @@ void make_layout(int problem, int m, int d, int64_t N, int64_t K, int op, Layout
     const int64_t M = K + N;
     L.ld = (d + 31) / 32 * 32;
     L.stride = m <= 4 ? 4 : 8;
-    // association grid: enough (row block x vector chunk) workgroups to fill
-    // the 256 CUs several times over, chunks of at most 32 tiles
+    // room for the partials of the shortest chunks that a full scan may take: some
+    // 2,048 (row block x vector chunk) workgroups, chunks of at most 32 tiles
+    // (scan_shape chooses the default within it, the autotuner any)
     const int64_t nbi = (M + assoc_rows_per_block() - 1) / assoc_rows_per_block();
     int64_t kc0 = (2048 + nbi - 1) / nbi;
     if (kc0 < 1) kc0 = 1;

@@ -412,3 +412,13 @@ def test_line_lanes_match_full_scan(P, K, N):
     batch.close()
     for r in runs:
         r.close()
+
+
+# default shapes of the full scan: one, two and four rows per lane at the rows
+# where they change, and more workgroups than two per CU (17,020 vectors)
+@pytest.mark.parametrize("K,N", [(5050, 4950), (5050, 4951), (10011, 9989), (10011, 9990), (17020, 17020)])
+def test_scan_shapes_match_index(P, K, N):
+    a, b = twin(P, 1, 3, 5, N, K, K, 2)
+    lock(a, b, 2)
+    a.close()
+    b.close()
