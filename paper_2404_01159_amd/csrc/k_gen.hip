@@ -464,7 +464,11 @@ __device__ __forceinline__ void offspring_body(const RunView &R, int64_t bx, Off
     int n1 = 0, n2 = 0;
     const double pr = R.p_m / (double)R.d;
     if (pr > 0.0) {
-        const double lq = log1p(-(pr > 1.0 ? 1.0 : pr));
+        double rate = fmin(pr, 1.0);
+        // kept a value of the lanes: the logarithm of a uniform one is compiled to
+        // scalar branches (11.5 us a launch at 3,876 children x 301 genes, 11.3 so)
+        asm volatile("" : "+v"(rate));
+        const double lq = log1p(-rate);
         if (active)
             draw_sites<S>(R, t, o1, o2, has2, lq, lane, L.sites[seg][0], L.mags[seg][0],
                           L.sites[seg][1], L.mags[seg][1], &n1, &n2);
