@@ -223,7 +223,8 @@ rvea_status rvea_set_graphs(rvea_run run, int enable);
  * generations and outside a batch (RVEA_ESTATE). */
 rvea_status rvea_set_index(rvea_run run, int enable);
 
-/* Copies the run state to host memory (waits for the stream).  Any pointer
+/* Copies the run state to host memory (waits for the stream; the calling
+ * thread's current device may be any, here and in rvea_set_state).  Any pointer
  * may be NULL.  Layouts, row-major: X K x d float, F K x m float,
  * valid K bytes (1 = slot holds an individual), V and V0 K x m double,
  * gamma K double; *t = completed generations.  Empty slots hold NaN in F. */
@@ -344,8 +345,9 @@ rvea_status rvea_destroy(rvea_run run);
  * generation per rvea_batch_step: each phase of the generation is one launch
  * covering every admitted run (runs grouped by segment width or objective
  * count; runs with the index of rvea_set_index associate through it and keep
- * it rebuilt in phases of their own), and the launch sequence is captured into one HIP graph that is
- * replayed until the membership changes.  Each run keeps its own workspace,
+ * it rebuilt in phases of their own), and the launch sequences, with the phases of an adaptation
+ * and without, are captured into a HIP graph each that is replayed until the membership changes
+ * (a step enqueued on a stream that the caller captures holds those phases).  Each run keeps its own workspace,
  * state and Philox stream, so a run's results do not depend on what else is
  * in the batch.  Adaptation is decided on the device per run.
  *   workspace   device memory of rvea_batch_footprint(max_runs) bytes,

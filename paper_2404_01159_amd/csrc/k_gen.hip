@@ -754,8 +754,10 @@ __host__ __device__ int pick_segment(int d)
     return S;
 }
 
-// The offspring kernel runs 4 wavefronts per SIMD (its register use), so
-// 256 CUs hold 4,096 at once.  Rows of 256 genes or more take 32-lane
+// The offspring kernel ran 4 wavefronts per SIMD (its register use) when this rule
+// was measured, so 256 CUs held 4,096 at once; it now has registers for 5, and
+// with 5,120 here its launches take the same time (10,011 x 500 17.6 us, 3,876 x
+// 301 11.4, 100 x 131,072 32.4, either way).  Rows of 256 genes or more take 32-lane
 // segments (two pairs per wavefront, twice the quads per lane) instead of
 // 64-lane ones when there are more pairs than resident wavefronts, and,
 // for rows under 2,048 genes, already above a quarter of that: a pair's own

@@ -704,7 +704,7 @@ __device__ __forceinline__ void next_resets(const RunView &R, int64_t g)
 // the one counter, smaller ones spread the scattered reads over more CUs: 20
 // generations of 2,048 x 100 took 467, 455 and 459 us with 1,024, 512 and 256
 // threads, of 10,011 x 500 782, 781 and 796.  Two kernels in its place took 5.6 +
-// 4.9 us at 10,011 vectors and 4.0 + 3.8 at 36; it takes 8.1 and 4.8.
+// 4.9 us at 10,011 vectors and 4.0 + 3.8 at 36; it takes 7.5 and 4.8.
 constexpr int kTurnBlock = 512, kTurnWaves = kTurnBlock / 64;
 __device__ __forceinline__ void turn_body(const RunView &R, int64_t bx)
 {
