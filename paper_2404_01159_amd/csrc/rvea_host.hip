@@ -1196,6 +1196,15 @@ rvea_status rvea_autotune(rvea_run r, rvea_tuning *out)
     HIPCHK(r, hipStreamSynchronize(r->stream));
     unsigned long long saved[3];
     HIPCHK(r, hipMemcpy(saved, R.counters, sizeof saved, hipMemcpyDeviceToHost));
+    // the gamma pass is timed on the current vectors and writes their gamma, which
+    // need not be the one that the host set
+    std::vector<double> gamma;
+    try {
+        gamma.resize((size_t)R.K);
+    } catch (const std::bad_alloc &) {
+        return RVEA_ENOMEM;
+    }
+    HIPCHK(r, hipMemcpy(gamma.data(), R.gamma, gamma.size() * 8, hipMemcpyDeviceToHost));
     // the next generation's offspring and ideal point give the association
     // its real input; nothing is committed, so the state is unchanged
     if (!R.turn) HIPCHK(r, launch_prepare(R, r->stream));
@@ -1288,8 +1297,7 @@ rvea_status rvea_autotune(rvea_run r, rvea_tuning *out)
     }
     R.rk = rk_win;
     // the gamma pass (rows = vectors, at adaptations): its own chunking and
-    // rows per lane, timed on the current vectors (it rewrites the same
-    // gamma every time)
+    // rows per lane, timed on the current vectors
     const int grr0 = R.grr, gcs0 = R.gCS;
     double g_def = -1.0, g_best = 1e30;
     int g_rr = grr0, g_cs = gcs0;
@@ -1333,6 +1341,7 @@ rvea_status rvea_autotune(rvea_run r, rvea_tuning *out)
     if (R.turn) HIPCHK(r, launch_prepare(R, r->stream));
     HIPCHK(r, hipStreamSynchronize(r->stream));
     HIPCHK(r, hipMemcpy(R.counters, saved, sizeof saved, hipMemcpyHostToDevice));
+    HIPCHK(r, hipMemcpy(R.gamma, gamma.data(), gamma.size() * 8, hipMemcpyHostToDevice));
     drop_graphs(r);            // captured with the old launch shapes
     r->has_selection = false;  // the trial overwrote the last selection's buffers
     if (out) {

@@ -126,3 +126,17 @@ def test_refused_on_a_capturing_stream(P):
     for k in ("X", "F", "valid", "V", "gamma", "t"):
         assert np.array_equal(after[k], before[k]), k
     run.close()
+
+
+@pytest.mark.parametrize("m,K", [(2, 64), (3, 105), (5, 126)])
+def test_autotuning_keeps_a_gamma_set_from_the_host(P, m, K):
+    run = P.Run(2, m, 20, K, K, seed=2)
+    st = run.get_state()
+    g = np.linspace(0.1, 0.2, K)
+    run.set_state(st["X"], st["F"], st["valid"], st["V"], g, 3)
+    run.autotune()
+    got = run.get_state()
+    run.close()
+    assert np.array_equal(got["gamma"], g)
+    for k in ("X", "F", "valid", "V"):
+        assert np.array_equal(got[k], st[k], equal_nan=True), k
